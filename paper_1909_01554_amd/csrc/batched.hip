@@ -16,7 +16,7 @@
 // other waves through LDS.  A one-workgroup kernel zeroes the queue counters
 // before each launch, so the pair can be captured into a HIP graph and
 // replayed.
-#include "mfma_tile.h"
+#include "panel_tile.h"
 
 namespace bmm {
 namespace {
@@ -69,15 +69,23 @@ __device__ __forceinline__ void resolve_item(const BatchedSeg* __restrict__ segs
   }
 }
 
+// Row and column of a problem's item (32-bit divisions where the band fits).
+__device__ __forceinline__ void item_coord(const BatchedDesc& d, uint32_t item, int64_t& im,
+                                           int64_t& in) {
+  if ((uint32_t)d.items_n < (1u << 28))
+    band_coord<uint32_t>(item, (uint32_t)d.items_m, (uint32_t)d.items_n, im, in);
+  else
+    band_coord<int64_t>((int64_t)item, d.items_m, d.items_n, im, in);
+}
+
 // The register-fed items keep the 32-bit operand expansion: the persistent loop's own
-// state leaves no room for the wide form's registers.  The LDS-shared items widen their
-// shorter side (its two B^T rows; int8 33.0 -> 32.1 ms, fp4 24.2 -> 23.8 ms).
+// state leaves no room for the wide form's registers.
 constexpr bool kWide = false;
 
 template <int RA, int RB, int FMT>
-__device__ __forceinline__ void run_item(const BatchedDesc& d, int64_t item, int w) {
+__device__ __forceinline__ void run_item(const BatchedDesc& d, uint32_t item, int w) {
   int64_t im, in;
-  band_coord(item, d.items_m, d.items_n, im, in);
+  item_coord(d, item, im, in);
   const int64_t tm = 2 * im + (w >> 1), tn = 2 * in + (w & 1);
   if (tm >= d.tiles_m || tn >= d.tiles_n) return;  // uniform per wave
   // (the tile reads and writes through global-memory pointers: the table's
@@ -96,17 +104,14 @@ __device__ __forceinline__ void run_item(const BatchedDesc& d, int64_t item, int
   }
 }
 
-// LDS-staged items (tile 4): mfma::lds_item (operand rows of the workgroup's 2 x 2
-// wave tiles staged through LDS once per stage and shared by the four waves).  (Loading
-// the next item's first stage during the current item's epilogue measured slower: wave
-// 0 then has to name the next item before the last stage's barrier, which the other
-// waves wait for.)
+// LDS-staged items (tile 4): the workgroup tile of panel_tile.h, 2 x 2 waves of 128 x 64 (the wide
+// shape would spill in the persistent loop).
 template <int FMT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void batched_lds_kernel(
     const BatchedDesc* __restrict__ descs, const BatchedSeg* __restrict__ segs,
     BatchedQueues qs, unsigned int* __restrict__ counters) {
   __shared__ int slots[2][2];
-  __shared__ __attribute__((aligned(16))) unsigned char smem[mfma::kLdsItemBytes];
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[panel::lds_bytes(4, 2)];
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   int q = blockIdx.x % kXcds, visited = 0;  // wave 0's queue state
   if (w == 0) {
@@ -115,7 +120,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void b
     resolve_item(segs, qs, counters, __shfl(v, 0), q, visited, lane, slots[0]);
   }
   __syncthreads();
-  mfma::LdsStage stage;
   for (int it = 0;; ++it) {
     const int* cur = slots[it & 1];
     const int p = __builtin_amdgcn_readfirstlane(cur[0]);
@@ -126,10 +130,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void b
       v = atomicAdd(&counters[q * kBatchedCounterStride], 1u);
     const BatchedDesc& d = descs[p];
     int64_t im, in;
-    band_coord(item, d.items_m, d.items_n, im, in);
-    mfma::lds_item<mfma::SEMI_ANY, FMT, true, true>(
-        d.A, d.lda, d.BT, d.ldbt, d.C, d.ldc, d.m, d.k, d.n, im, in, d.tiles_m, d.tiles_n,
-        d.aligned != 0, 0, d.semiring, w, smem, stage);
+    item_coord(d, item, im, in);
+    // (the barrier below is also what frees the item's LDS for the next one)
+    panel::tile<mfma::SEMI_ANY, FMT, 4, 2, false>(d.A, d.lda, d.BT, d.ldbt, d.C, d.ldc, d.m, d.k,
+                                                  d.n, im, in, 0, d.semiring, w, smem);
     if (w == 0) resolve_item(segs, qs, counters, __shfl(v, 0), q, visited, lane, slots[(it + 1) & 1]);
     __syncthreads();
   }

@@ -37,7 +37,7 @@ struct Plan {
   int device = 0;
   int leaf = BMM_LEAF_MFMA_I8;  // BMM_LEAF_MFMA_I8 or BMM_LEAF_MFMA_F4
   int tile = 4;                 // 1: 128 x 64 per wave, 2: 64 x 64, 3: 64 x 128,
-                                // 4: 128 x 64 with LDS-shared operand rows
+                                // 4: the LDS-staged 128 x 64 of panel_tile.h
 };
 
 bool capturing(hipStream_t s) {
@@ -200,7 +200,7 @@ struct PlanSet {
 
 // Choices per problem: opt's leaf and tile where given; else the autotuner's per-class
 // record for plans of this count and total work, else its plan-wide record, else int8
-// with the LDS-shared 128 x 64 item (tile 4).  force_* (>= 0) override everything.
+// with the LDS-staged 128 x 64 item (tile 4).  force_* (>= 0) override everything.
 int build_set(const bmm_problem* problems, int64_t count, const bmm_options* opt,
               int force_leaf, int force_tile, int force_wpc, PlanSet* out) {
   if (count < 0 || (count > 0 && !problems)) return bfail(BMM_E_INVAL, "bad problem list");
@@ -236,6 +236,9 @@ int build_set(const bmm_problem* problems, int64_t count, const bmm_options* opt
                                                 p.m, p.k, p.n, 1, 0}});
       continue;
     }
+    // the register-fed 128 x 64 item where tile 4's int32 sums of 2^7 or 32-bit row offsets
+    // could overflow
+    if (tile == 4 && (p.k >= kPanelMaxK || p.lda >= kNearPitch || p.ldb >= kNearPitch)) tile = 1;
     auto it = std::find_if(groups.begin(), groups.end(),
                            [&](const auto& g) { return g.first == std::make_pair(leaf, tile); });
     if (it == groups.end()) {

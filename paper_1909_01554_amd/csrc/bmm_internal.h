@@ -55,42 +55,51 @@ struct TileCoord {
 };
 
 // Banded order of a grid_m x grid_n tile grid: bands of kGroupRows tile rows,
-// each walked column by column, so consecutive tiles share operand panels.
-__device__ __forceinline__ void band_coord(int64_t r, int64_t grid_m, int64_t grid_n,
-                                           int64_t& tm, int64_t& tn) {
-  const int64_t band = (int64_t)kGroupRows * grid_n;
-  const int64_t first = (r / band) * kGroupRows;
-  const int64_t rows = grid_m - first < kGroupRows ? grid_m - first : kGroupRows;
-  const int64_t q = r - (r / band) * band;
-  tm = first + q % rows;
-  tn = q / rows;
+// each walked column by column, so consecutive tiles share operand panels.  T is 32 bits
+// wide where kGroupRows * grid_n and r fit: a 64-bit division is about 100 instructions,
+// and a short tile would spend a tenth of its time on five of them.
+template <class T>
+__device__ __forceinline__ void band_coord(T r, T grid_m, T grid_n, int64_t& tm, int64_t& tn) {
+  const T band = (T)kGroupRows * grid_n;
+  const T b = r / band, first = b * (T)kGroupRows;
+  const T rows = grid_m - first < (T)kGroupRows ? grid_m - first : (T)kGroupRows;
+  const T q = r - b * band, col = q / rows;
+  tm = first + (q - col * rows);
+  tn = col;
 }
 
-__device__ __forceinline__ TileCoord xcd_tile(int64_t g, int64_t total, int64_t grid_m,
+// (a launch has fewer than 2^26 workgroups, grid_fits, so 32 bits hold every product here)
+__device__ __forceinline__ TileCoord xcd_tile(uint32_t g, uint32_t total, int64_t grid_m,
                                               int64_t grid_n) {
-  const int64_t x = g % kXcds, j = g / kXcds;
-  const int64_t per = total / kXcds, rem = total % kXcds;
-  const int64_t t = x * per + (x < rem ? x : rem) + j;
-  const int64_t per_item = grid_m * grid_n;
+  const uint32_t x = g % kXcds, j = g / kXcds;
+  const uint32_t per = total / kXcds, rem = total % kXcds;
+  const uint32_t t = x * per + (x < rem ? x : rem) + j;
+  const uint32_t per_item = (uint32_t)grid_m * (uint32_t)grid_n;
   TileCoord c;
-  c.b = t / per_item;
-  band_coord(t - c.b * per_item, grid_m, grid_n, c.tm, c.tn);
+  const uint32_t b = t / per_item;
+  c.b = b;
+  band_coord<uint32_t>(t - b * per_item, (uint32_t)grid_m, (uint32_t)grid_n, c.tm, c.tn);
   return c;
 }
 
-// MFMA leaf variants (rows x cols of C per wave).
+// MFMA leaf variants (rows x cols of C per wave, or per workgroup for the last and the
+// fifth).  64 x 64 and 64 x 32 are the register-fed tiles for small products, and int8 has
+// the unrolled register-fed 128 x 64 pipeline (k = 2048 and 4096) and the chunked 64 x 128
+// loop (k >= 2^24); every other choice is the panel leaf, which picks its shape itself.
 enum MfmaTile { MFMA_128x64 = 0, MFMA_64x64 = 1, MFMA_64x128 = 2, MFMA_64x32 = 3,
-                MFMA_LDS_256x256 = 4,
-                MFMA_DEEP_128x64 = 5,  // 128 x 64, 3-deep unrolled pipeline for k = 2048, 4096
-                MFMA_CHUNK_64x128 = 6,  // 64 x 128, 2-deep pipeline in unrolled 12-step chunks
-                MFMA_LDS4_256x128 = 7,  // 2 x 2 waves of 128 x 64, operand rows shared in LDS
-                MFMA_NUM_TILES };
+                MFMA_LDS_256x256 = 4, MFMA_DEEP_128x64 = 5, MFMA_CHUNK_64x128 = 6,
+                MFMA_LDS4_256x128 = 7, MFMA_NUM_TILES };
 
 hipError_t launch_leaf_mfma(int semiring, const LeafBatch& p, int tile, hipStream_t s);
 // The same tiles on E2M1 (fp4) operands with exact fp32 sums; requires k < 2^24.
 hipError_t launch_leaf_mfma_f4(int semiring, const LeafBatch& p, int tile, hipStream_t s);
-// The 8-wave workgroup variant that shares operand panels through LDS (fmt 0: int8, 1: fp4).
-hipError_t launch_leaf_mfma_lds(int semiring, int fmt, const LeafBatch& p, hipStream_t s);
+// The panel leaf counts exactly below this k; it addresses a tile's rows (at most 256) with
+// 32-bit byte offsets where pitches (words) are below kNearPitch.
+constexpr int64_t kPanelMaxK = (int64_t)1 << 24;
+constexpr int64_t kNearPitch = (int64_t)1 << 20;
+// The LDS-staged leaf of panel_tile.h (fmt: mfma::MfmaFormat) on 2 x 2 wave tiles of 64 x 128
+// or 128 x 64, whichever the shape pads less; k < kPanelMaxK.
+hipError_t launch_leaf_panel(int semiring, int fmt, const LeafBatch& p, hipStream_t s);
 hipError_t launch_leaf_valu(int semiring, const LeafBatch& p, int tile, hipStream_t s);
 // The VALU leaf in outer-product form (tile 2): B row-major (k x n, pitch ldb words), one
 // product; k = 0 leaves C zero (or unchanged when accumulating).
@@ -215,7 +224,8 @@ struct BatchedQueues {
   uint32_t seg_off[kXcds], seg_count[kXcds], items[kXcds];
 };
 constexpr int kBatchedCounterStride = 64;  // uint32s between queue counters (256 bytes)
-// tile 1: 128 x 64 per wave, 2: 64 x 64, 3: 64 x 128; fmt: mfma::MfmaFormat (0 int8, 1 E2M1).
+// tile 1: 128 x 64 per wave, 2: 64 x 64, 3: 64 x 128, 4: the panel leaf's 128 x 64
+// (k < kPanelMaxK, pitches below kNearPitch); fmt: mfma::MfmaFormat (0 int8, 1 E2M1).
 // counters: kXcds * kBatchedCounterStride uint32s, zeroed by the launch itself.
 hipError_t launch_batched_persistent(const BatchedDesc* descs, const BatchedSeg* segs,
                                      const BatchedQueues& queues, unsigned int* counters,

@@ -1,0 +1,56 @@
+// Cubic leaf on the matrix cores with operand rows staged in LDS by direct loads (see
+// panel_tile.h for the tile and its operands): one workgroup per 128 x 256 or 256 x 128
+// tile of C, two workgroups per CU.
+#include "panel_tile.h"
+
+namespace bmm {
+namespace {
+
+template <int SEMI, int FMT, int RA, int RB, bool FAR>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void leaf_panel_kernel(
+    LeafBatch p, int64_t grid_m, int64_t grid_n) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[panel::lds_bytes(RA, RB)];
+  const TileCoord c = xcd_tile(blockIdx.x, gridDim.x, grid_m, grid_n);
+  panel::tile<SEMI, FMT, RA, RB, FAR>(
+      p.A + c.b * p.strideA, p.lda, p.BT + c.b * p.strideB, p.ldbt, p.C + c.b * p.strideC, p.ldc,
+      p.m, p.k, p.n, c.tm, c.tn, p.accumulate, SEMI,
+      __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), smem);
+}
+
+template <int SEMI, int FMT, int RA, int RB, bool FAR>
+hipError_t launch_shape(const LeafBatch& p, hipStream_t s) {
+  const int64_t grid_m = (p.m + 64 * RA - 1) / (64 * RA);
+  const int64_t grid_n = (p.n + 64 * RB - 1) / (64 * RB);
+  const int64_t blocks = grid_m * grid_n * p.batch;
+  if (!grid_fits(blocks, 256)) return kGridTooLarge;
+  hipLaunchKernelGGL((leaf_panel_kernel<SEMI, FMT, RA, RB, FAR>), dim3((unsigned)blocks),
+                     dim3(256), 0, s, p, grid_m, grid_n);
+  return hipGetLastError();
+}
+
+template <int SEMI, int FMT>
+hipError_t launch_semi(const LeafBatch& p, hipStream_t s) {
+  // 64-bit row addresses take registers that only the tall shape has left
+  if (p.lda >= kNearPitch || p.ldbt >= kNearPitch) return launch_shape<SEMI, FMT, 4, 2, true>(p, s);
+  // Wide wave tiles (64 x 128) are 2 to 6% faster than tall ones (n = 4096: 23.6 against
+  // 24.3 us, 16384: 1.20 against 1.21 ms in fp4): C's rows are stored 16 bytes at a time.
+  // Tall ones where they need fewer workgroups (n up to 128 columns past a multiple of 256).
+  const bool wide = ((p.m + 127) / 128) * ((p.n + 255) / 256) <=
+                    ((p.m + 255) / 256) * ((p.n + 127) / 128);
+  return wide ? launch_shape<SEMI, FMT, 2, 4, false>(p, s)
+              : launch_shape<SEMI, FMT, 4, 2, false>(p, s);
+}
+
+}  // namespace
+
+hipError_t launch_leaf_panel(int semiring, int fmt, const LeafBatch& p, hipStream_t s) {
+  if (p.m <= 0 || p.n <= 0 || p.batch <= 0) return hipSuccess;
+  if (p.k >= panel::kMaxK) return hipErrorInvalidValue;  // counts would not be exact
+  if (fmt == mfma::FMT_F4)
+    return semiring == GF2 ? launch_semi<GF2, mfma::FMT_F4>(p, s)
+                           : launch_semi<BOOLEAN, mfma::FMT_F4>(p, s);
+  return semiring == GF2 ? launch_semi<GF2, mfma::FMT_I8>(p, s)
+                         : launch_semi<BOOLEAN, mfma::FMT_I8>(p, s);
+}
+
+}  // namespace bmm

@@ -1,0 +1,441 @@
+// Device code of one workgroup tile of the matrix-core leaves whose operand rows go to LDS
+// by direct loads and become matrix-core operands by masks alone.
+//
+// Tile and staging.  Four waves (2 x 2) own 64 RA rows by 64 RB columns of C, 32 RA x 32 RB
+// each.  A stage is 8 words of k (512 bits) of the tile's rows of A and of B^T: 24 KB, two
+// buffers.  A stage is loaded with global_load_lds_dwordx4, which needs no registers, so the 128 counts, two sets of raw
+// words and the expanded operands fit in 256 registers (two workgroups per CU) without
+// scratch.  A row's four 16-byte chunks are stored rotated by an XOR with bits 1..2 of the
+// row, so that the 8 lanes served together by a 16-byte LDS read hit distinct banks; the
+// direct loads write LDS linearly, so it is the lane's source address that is permuted.
+// A stage is two rounds of 256 bits; round 0 of the next stage is read from LDS while the
+// last round of this one is computed, and one barrier per stage, before that read, both
+// publishes the next stage and frees this one's buffer for the stage after.
+//
+// Operands.  The order of k inside a dot product is free as long as both sides use the
+// same one.  Lane half h of a round holds 128 consecutive bits (4 dwords) of its row; one
+// matrix-core step takes bit plane d of all four dwords, i.e. 128 / planes bits per lane:
+//   E2M1: nibble bit d, d = 0..2, is the value 0.5, 1 or 2 where it lies, so one AND makes
+//   an operand; bit 3 (the sign) is moved to bit 1 first.  The products 0.25, 1, 4 and 1
+//   are brought to 1 by the instruction's block scales, and the fp32 sum is the count,
+//   exact below 2^24.  4.5 VALU instructions per 32 bits of a row instead of 7.
+//   int8: byte bit d of one side is 2^d; the other side has the bits of each byte reversed
+//   (2 instructions per dword, once for all planes), so its mask gives 2^(7-d) and every
+//   product is 2^7.  For GF(2) the signs of the planes 0 and 7 do not matter (the parity
+//   is bit 7 of the sum); for OR these two planes are moved one bit inward, so that all
+//   products are positive.  Exact while 2^7 k < 2^31, i.e. k < 2^24.  8 to 10 VALU
+//   instructions per 32 bits of a row instead of 11.5 to 15.
+//
+// Bound by the matrix cores: 2401 fp4 products of 2048^3 on dense bits take 6.6 ms (6.2e15
+// bit ops/s; 5.3e15 before, with register-fed 128 x 64 tiles), one of 16384^3 1.20 ms on
+// dense bits (7.2e15) and 1.06 ms on sparse ones (8.2e15), where a kernel of nothing but
+// these instructions reaches 9.3e15; dense bits lower the clock.  int8: 4.6e15 of 4.7e15.
+#pragma once
+
+#include <type_traits>
+
+#include "mfma_tile.h"
+
+namespace bmm {
+namespace panel {
+
+using mfma::FMT_F4;
+using mfma::FMT_I8;
+using mfma::SEMI_ANY;
+using mfma::v16f;
+using mfma::v16i;
+using mfma::v4i;
+using mfma::v8i;
+
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+
+constexpr int kWords = 8;               // words of k per stage
+constexpr int kRowBytes = 8 * kWords;   // LDS row
+constexpr int64_t kMaxK = kPanelMaxK;
+
+constexpr int lds_bytes(int RA, int RB) { return 2 * 64 * (RA + RB) * kRowBytes; }
+
+// 16 bytes per lane from base + voff to LDS at lds + 16 * lane (base and lds uniform).
+// The caller waits with stage_sync() before anyone reads them.  Global addresses need
+// 8-byte alignment only, which rows of odd pitch have.
+__device__ __forceinline__ void load_lds16(const void* base, uint32_t voff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds),
+               "v"(voff), "s"(base)
+               : "memory");
+}
+
+__device__ __forceinline__ void load_lds16(const void* addr, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds),
+               "v"(addr)
+               : "memory");
+}
+
+// This wave's LDS reads, LDS writes and direct loads are done, then everyone's.
+__device__ __forceinline__ void stage_sync() {
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// ---- operands ----
+
+// Bits of each byte reversed.
+__device__ __forceinline__ u4 reverse_bytes(u4 x) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    x[i] = __builtin_amdgcn_perm(0, __builtin_bitreverse32(x[i]), 0x00010203u);
+  return x;
+}
+
+// (x << -S or x >> S) & mask, two dwords per 64-bit shift: the bits that cross dwords or
+// fields are outside the masks used here.
+template <int S>
+__device__ __forceinline__ v4i shift_mask(u4 x, uint32_t mask) {
+  v4i o;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const uint64_t q = ((uint64_t)x[2 * i + 1] << 32) | x[2 * i];
+    const uint64_t y = S > 0 ? q >> (S > 0 ? S : 0) : q << (S > 0 ? 0 : -S);
+    o[2 * i] = (int)((uint32_t)y & mask);
+    o[2 * i + 1] = (int)((uint32_t)(y >> 32) & mask);
+  }
+  return o;
+}
+
+template <int FMT>
+struct Planes;
+template <>
+struct Planes<FMT_F4> {
+  static constexpr int N = 4;
+};
+template <>
+struct Planes<FMT_I8> {
+  static constexpr int N = 8;
+};
+
+// Plane D of 128 bits of a row.  REV (int8): the side with reversed bytes.
+template <int FMT, int D, bool REV, bool SIGNED_OK>
+__device__ __forceinline__ v4i plane(u4 x) {
+  if constexpr (FMT == FMT_F4) {
+    if constexpr (D == 3) return shift_mask<2>(x, 0x22222222u);
+    else return __builtin_bit_cast(v4i, x & (0x11111111u << D));
+  } else {
+    if constexpr (!SIGNED_OK && D == (REV ? 7 : 0)) return shift_mask<-1>(x, 0x02020202u);
+    else if constexpr (!SIGNED_OK && D == (REV ? 0 : 7)) return shift_mask<1>(x, 0x40404040u);
+    else return __builtin_bit_cast(v4i, x & (0x01010101u << (REV ? 7 - D : D)));
+  }
+}
+
+__device__ __forceinline__ v8i widen(v4i x) {
+  return __builtin_shufflevector(x, x, 0, 1, 2, 3, -1, -1, -1, -1);
+}
+
+template <int FMT, int D>
+__device__ __forceinline__ typename mfma::Acc<FMT>::type step(
+    v4i a, v4i b, typename mfma::Acc<FMT>::type acc) {
+  if constexpr (FMT == FMT_F4) {
+    // E8M0 scales 2^(s - 127) on both sides: 0.25, 1, 4, 1 become 1
+    constexpr int s = D == 0 ? 128 : D == 2 ? 126 : 127;
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen(a), widen(b), acc, 4, 4, 0, s, 0,
+                                                           s);
+  } else {
+    return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, acc, 0, 0, 0);
+  }
+}
+
+// The lane index as a fresh value: what is derived from it (addresses, selectors) is not
+// computed earlier than here and kept in registers across a main loop or a persistent one.
+__device__ __forceinline__ int fresh_lane() {
+  int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  asm volatile("" : "+v"(lane));
+  return lane;
+}
+
+// ---- results ----
+
+// 32 x 32 bit transposes over the 32 lanes of each wave half, by five exchanges between
+// lanes 16, 8, 4, 2 and 1 apart (3 VALU instructions each, where a ballot and two selects
+// per count take 7 per count); the selectors depend on the lane only.
+struct Transpose {
+  uint32_t s16, s8, r4, m4, r2, m2, r1, m1;
+  __device__ __forceinline__ explicit Transpose(int lane) {
+    s16 = (lane & 16) ? 0x07060302u : 0x05040100u;
+    s8 = (lane & 8) ? 0x03070105u : 0x06020400u;
+    r4 = (lane & 4) ? 4 : 28;
+    m4 = (lane & 4) ? 0x0f0f0f0fu : 0xf0f0f0f0u;
+    r2 = (lane & 2) ? 2 : 30;
+    m2 = (lane & 2) ? 0x33333333u : 0xccccccccu;
+    r1 = (lane & 1) ? 1 : 31;
+    m1 = (lane & 1) ? 0x55555555u : 0xaaaaaaaau;
+  }
+  template <int CTRL>
+  static __device__ __forceinline__ uint32_t dpp(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, true);
+  }
+  static __device__ __forceinline__ uint32_t merge(uint32_t m, uint32_t y, uint32_t r, uint32_t x) {
+    return (m & __builtin_amdgcn_alignbit(y, y, r)) | (~m & x);
+  }
+  __device__ __forceinline__ uint32_t operator()(uint32_t x) const {
+    const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = __builtin_amdgcn_perm(r[1], r[0], s16);
+    x = __builtin_amdgcn_perm(dpp<0x128>(x), x, s8);        // row_ror:8
+    x = merge(m4, dpp<0x1B>(dpp<0x141>(x)), r4, x);         // half mirror, then 3 - i
+    x = merge(m2, dpp<0x4E>(x), r2, x);                     // quad_perm [2,3,0,1]
+    x = merge(m1, dpp<0xB1>(x), r1, x);                     // quad_perm [1,0,3,2]
+    return x;
+  }
+};
+
+// The 16 result bits of a lane's column of one 32 x 32 block, bit v of the upper half of
+// the dword (E2M1 parity) or of the lower half (else): two instructions per count, one
+// that brings the bit to an end of a register and one that shifts it in.
+template <int FMT>
+__device__ __forceinline__ constexpr bool packs_high(bool gf2) {
+  return FMT == FMT_F4 && gf2;
+}
+template <int FMT>
+__device__ __forceinline__ uint32_t pack16(const typename mfma::Acc<FMT>::type& acc, bool gf2) {
+  uint32_t w = 0;
+  if (packs_high<FMT>(gf2)) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) w = __builtin_amdgcn_alignbit((uint32_t)acc[v], w, 1);
+  } else {
+#pragma unroll
+    for (int v = 15; v >= 0; --v) {
+      uint32_t c;  // the result bit in bit 31
+      if constexpr (FMT == FMT_F4) c = __float_as_uint(0.0f - acc[v]);  // a sign iff acc > 0
+      else c = gf2 ? (uint32_t)acc[v] << 24 : 0u - (uint32_t)acc[v];
+      w = __builtin_amdgcn_alignbit(w, c, 31);
+    }
+  }
+  return w;
+}
+
+template <int SEMI, int FMT, int RA, int RB>
+__device__ __forceinline__ void store_tile(const typename mfma::Acc<FMT>::type (&acc)[RA][RB],
+                                           uint64_t* C, int64_t ldc, int64_t m, int64_t n,
+                                           int64_t row0, int64_t word0, int accumulate,
+                                           int semiring) {
+  static_assert(RA % 2 == 0 && RB % 2 == 0, "blocks are packed in pairs");
+  const bool gf2 = SEMI == SEMI_ANY ? semiring == GF2 : SEMI == GF2;
+  const int lane = fresh_lane(), half = lane >> 5, li = lane & 31;
+  const Transpose tr(lane);
+  const int64_t n_words = (n + 63) >> 6;
+  // after the transposition lane li of half h holds row r(li) of block f + h
+  const int r = ((li >> 2) & 3) * 8 + (li >> 4) * 4 + (li & 3);
+  const bool vec16 = RB == 4 && word0 + 1 < n_words &&
+                     ((reinterpret_cast<uintptr_t>(C) & 15) | (uintptr_t)(ldc & 1)) == 0;
+#pragma unroll
+  for (int f = 0; f < RA; f += 2) {
+    __builtin_amdgcn_sched_barrier(0);  // one row block at a time, to keep registers
+    uint64_t word[RB / 2];
+#pragma unroll
+    for (int g = 0; g < RB; ++g) {
+      const auto s = __builtin_amdgcn_permlane32_swap(
+          pack16<FMT>(acc[f][g], gf2), pack16<FMT>(acc[f + 1][g], gf2), false, false);
+      const uint32_t x =
+          tr(__builtin_amdgcn_perm(s[1], s[0], packs_high<FMT>(gf2) ? 0x07060302u : 0x05040100u));
+      if (g & 1) word[g / 2] |= (uint64_t)x << 32;
+      else word[g / 2] = x;
+    }
+    const int64_t row = row0 + 32 * (f + half) + r;
+    if (row < m) {
+#pragma unroll
+      for (int h = 0; h < RB / 2; ++h) {
+        const int64_t valid = n - 64 * (word0 + h);
+        word[h] &= valid >= 64 ? ~0ull : valid > 0 ? ((uint64_t)1 << valid) - 1 : 0ull;
+      }
+      const mfma::gw_ptr dst = (mfma::gw_ptr)C + row * ldc + word0;
+      if (RB == 4 && vec16) {
+        const mfma::gw2_ptr d2 = (mfma::gw2_ptr)dst;
+        mfma::cpair_t x = {word[0], word[RB / 2 - 1]};
+        if (accumulate) x = gf2 ? (x ^ *d2) : (x | *d2);
+        *d2 = x;
+      } else {
+#pragma unroll
+        for (int h = 0; h < RB / 2; ++h) {
+          if (word0 + h >= n_words) break;  // uniform
+          uint64_t x = word[h];
+          if (accumulate) x = gf2 ? (x ^ dst[h]) : (x | dst[h]);
+          dst[h] = x;
+        }
+      }
+    }
+  }
+}
+
+// ---- one workgroup tile ----
+
+// Rows [64 RA im, ...) x columns [64 RB in, ...) of C = A B, by the four waves w = 0..3 of
+// a workgroup (all of them call it; every one takes part in loads and barriers).  Needs
+// k < 2^24 and lds_bytes(RA, RB) of LDS, which nobody reads any more when it is called.
+// FAR: pitches of kNearPitch words and more (64-bit row addresses).
+// (Workgroups that took several tiles in turn, the next one's first stage loaded during
+// the last stage of this one, were 7 to 10% slower than one workgroup per tile, which the
+// hardware hands out as CUs come free: 62.8 against 57.8 ms for the n = 65536 recursion.)
+template <int SEMI, int FMT, int RA, int RB, bool FAR>
+__device__ __forceinline__ void tile(const uint64_t* __restrict__ A, int64_t lda,
+                                     const uint64_t* __restrict__ BT, int64_t ldbt, uint64_t* C,
+                                     int64_t ldc, int64_t m, int64_t k, int64_t n, int64_t im,
+                                     int64_t in, int accumulate, int semiring, int w,
+                                     unsigned char* smem) {
+  constexpr int TM = 64 * RA, TN = 64 * RB, NL = (TM + TN) / 64;
+  constexpr int STAGE = (TM + TN) * kRowBytes;
+  constexpr bool SIGNED_OK = SEMI == GF2;
+  const int wy = w >> 1, wx = w & 1;
+  const int64_t kw = (k + 63) >> 6;
+  const int64_t stages = (kw + kWords - 1) / kWords;
+  const int64_t row0 = im * TM, col0 = in * TN;
+  const uint64_t* Ab = A + row0 * lda;
+  const uint64_t* Bb = BT + col0 * ldbt;
+
+  // Load i of wave w fills LDS rows 16 (4 i + w) .. + 15, 4 lanes per row; rows past the
+  // end of an operand repeat its last one (their results are not stored).
+  auto chunk_of = [](int ln) { return (ln & 3) ^ ((ln >> 3) & 3); };  // of a lane's slot
+  uint32_t voff[NL];  // byte offset of the lane's chunk, or (FAR) its row
+  {
+    const int lane = fresh_lane();
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const bool isA = 64 * i < TM;
+      const int64_t lim = isA ? m - 1 - row0 : n - 1 - col0;
+      int r = 16 * (4 * i + w) + (lane >> 2) - (isA ? 0 : TM);
+      r = r < lim ? r : (int)lim;
+      voff[i] = FAR ? (uint32_t)r
+                    : (uint32_t)r * ((uint32_t)(isA ? lda : ldbt) * 8) + 16 * chunk_of(lane);
+    }
+  }
+  // the lane's chunk of load i in the stage at word w0
+  auto source = [&](int i, int64_t w0) -> const uint64_t* {
+    const bool isA = 64 * i < TM;
+    const uint64_t* base = (isA ? Ab : Bb) + w0;
+    if (FAR) return base + (int64_t)voff[i] * (isA ? lda : ldbt) + 2 * chunk_of(fresh_lane());
+    return (const uint64_t*)((const char*)base + voff[i]);
+  };
+  typedef __attribute__((address_space(3))) unsigned char* lds_ptr;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr)smem + w * 1024;
+  auto load = [&](int64_t st, int buf) {
+    const int64_t w0 = st * kWords;
+    if (w0 + kWords <= kw) {  // uniform
+#pragma unroll
+      for (int i = 0; i < NL; ++i) {
+        const uint32_t dst = lds0 + buf * STAGE + i * 4096;
+        if (FAR) load_lds16(source(i, w0), dst);
+        else load_lds16((64 * i < TM ? Ab : Bb) + w0, voff[i], dst);
+      }
+      return;
+    }
+    // the last, shorter stage: words past the end of k read as zero (the loads themselves
+    // stay inside the row)
+    const int lane = fresh_lane();
+    const int left = (int)(kw - w0) - 2 * chunk_of(lane);  // words of the lane's chunk and after
+    const int o0 = left > 0 ? 0 : left - 1, o1 = left > 1 ? 1 : left - 1;
+    // (two loads at a time: the counts leave no registers for all of them)
+#pragma unroll
+    for (int i = 0; i < NL; i += 2) {
+      __builtin_amdgcn_sched_barrier(0);
+      uint64_t x[2][2] = {};
+      if (kw > 0) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const mfma::gq_ptr src = (mfma::gq_ptr)source(i + j, w0);
+          x[j][0] = src[o0];
+          x[j][1] = src[o1];
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        ulonglong2 v;
+        v.x = left > 0 ? x[j][0] : 0ull;
+        v.y = left > 1 ? x[j][1] : 0ull;
+        *reinterpret_cast<ulonglong2*>(smem + w * 1024 + buf * STAGE + (i + j) * 4096 + lane * 16) = v;
+      }
+    }
+  };
+
+  // raw words of two rounds: lane half h takes chunk 2 s + h of round s
+  const int lane = fresh_lane(), half = lane >> 5, li = lane & 31;
+  const int slot = (half ^ ((li >> 1) & 3)) * 16;
+  const int abase = (wy * 32 * RA + li) * kRowBytes + slot;
+  const int bbase = (TM + wx * 32 * RB + li) * kRowBytes + slot;
+  u4 xa[2][RA], xb[2][RB];
+  auto read = [&](int buf, int s) {
+#pragma unroll
+    for (int f = 0; f < RA; ++f)
+      xa[s][f] = *reinterpret_cast<const u4*>(smem + buf * STAGE + (abase ^ (32 * s)) + 2048 * f);
+#pragma unroll
+    for (int g = 0; g < RB; ++g)
+      xb[s][g] = *reinterpret_cast<const u4*>(smem + buf * STAGE + (bbase ^ (32 * s)) + 2048 * g);
+  };
+  using AccV = typename mfma::Acc<FMT>::type;
+  AccV acc[RA][RB];
+  auto round = [&](int s) {
+    constexpr bool REV_A = RA < RB;  // int8: the side with fewer rows is reversed
+    if constexpr (FMT == FMT_I8) {
+#pragma unroll
+      for (int f = 0; f < RA; ++f)
+        if (REV_A) xa[s][f] = reverse_bytes(xa[s][f]);
+#pragma unroll
+      for (int g = 0; g < RB; ++g)
+        if (!REV_A) xb[s][g] = reverse_bytes(xb[s][g]);
+    }
+    auto one = [&](auto dc) {
+      constexpr int D = decltype(dc)::value;
+      if constexpr (D < Planes<FMT>::N) {
+        v4i eb[RB];
+#pragma unroll
+        for (int g = 0; g < RB; ++g) eb[g] = plane<FMT, D, !REV_A, SIGNED_OK>(xb[s][g]);
+#pragma unroll
+        for (int f = 0; f < RA; ++f) {
+          const v4i ea = plane<FMT, D, REV_A, SIGNED_OK>(xa[s][f]);
+#pragma unroll
+          for (int g = 0; g < RB; ++g) acc[f][g] = step<FMT, D>(ea, eb[g], acc[f][g]);
+        }
+      }
+    };
+    one(std::integral_constant<int, 0>{});
+    one(std::integral_constant<int, 1>{});
+    one(std::integral_constant<int, 2>{});
+    one(std::integral_constant<int, 3>{});
+    one(std::integral_constant<int, 4>{});
+    one(std::integral_constant<int, 5>{});
+    one(std::integral_constant<int, 6>{});
+    one(std::integral_constant<int, 7>{});
+    // the round ends here: the compiler would otherwise sink it below the next barrier,
+    // and the LDS reads issued before it would have nothing to hide behind
+#pragma unroll
+    for (int f = 0; f < RA; ++f)
+#pragma unroll
+      for (int g = 0; g < RB; ++g) asm volatile("" ::"v"(acc[f][g]));
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+#pragma unroll
+  for (int f = 0; f < RA; ++f)
+#pragma unroll
+    for (int g = 0; g < RB; ++g) acc[f][g] = AccV{};
+  load(0, 0);
+  stage_sync();
+  if (stages > 1) load(1, 1);
+  read(0, 0);
+  // waves in their main loop go before the other workgroup's first loads and epilogue
+  __builtin_amdgcn_s_setprio(1);
+  int cur = 0;
+  for (int64_t st = 0; st < stages; ++st) {
+    read(cur, 1);
+    round(0);
+    if (st + 1 < stages) {
+      stage_sync();
+      if (st + 2 < stages) load(st + 2, cur);
+      read(cur ^ 1, 0);
+    }
+    if (st * kWords + 4 < kw) round(1);  // else only zero words are left
+    cur ^= 1;
+  }
+  __builtin_amdgcn_s_setprio(0);
+  store_tile<SEMI, FMT, RA, RB>(acc, C, ldc, m, n, row0 + wy * 32 * RA,
+                                (col0 >> 6) + wx * (RB / 2), accumulate, semiring);
+}
+
+}  // namespace panel
+}  // namespace bmm
