@@ -56,7 +56,9 @@ typedef enum { BMM_GF2 = 0, BMM_BOOLEAN = 1 } bmm_semiring;
 
 /* Leaf kernels for the cubic product. */
 typedef enum {
-  BMM_LEAF_AUTO = 0,    /* autotuner's choice */
+  BMM_LEAF_AUTO = 0,    /* autotuner's choice: the table's entry for the shape, else its
+                           auto_leaf line (the shipped gfx950 table: fp4 while k < 2^24),
+                           else int8 */
   BMM_LEAF_VALU = 1,    /* bitwise vector ALU leaf (v_bitop3_b32) */
   BMM_LEAF_MFMA_I8 = 2, /* int8 matrix-core leaf, exact int32 counts */
   BMM_LEAF_MFMA_F4 = 3  /* E2M1 (fp4) matrix-core leaf, exact fp32 counts; k < 2^24,
@@ -247,8 +249,8 @@ void bmm_batched_plan_destroy(void* plan);
  * through LDS and shared by its four waves); BMM_LEAF_VALU: the VALU leaf, one launch
  * per problem); 0 / AUTO take the autotuner's record for plans of the same problem
  * count and total work (to a factor of two): its choice per size class of k
- * (k < 1024, < 4096, larger) where it recorded one, else its single choice, else int8
- * with tile 4.  Problems with the same matrix-core choice share one persistent launch
+ * (k < 1024, < 4096, larger) where it recorded one, else its single choice, else the
+ * table's auto_leaf (int8 without one) with tile 4.  Problems with the same matrix-core choice share one persistent launch
  * (workgroups per CU from the same record, else 4); a plan's launch enqueues the VALU
  * products, then each persistent group. */
 

@@ -135,6 +135,11 @@ struct TuneVal {
   int tile[4] = {0, 0, 0, 0};
 };
 std::map<TuneKey, TuneVal> g_tune;
+// Leaf kind of BMM_LEAF_AUTO for shapes without an entry ("auto_leaf" line of a table; 0:
+// none, int8).  The shipped gfx950 table names the fp4 leaf: its counts are exact too, and
+// on the panel kernel it takes 0.55 to 0.65 of the int8 leaf's time at every size measured
+// from 4096 up (n = 4096: 23.6 against 38.2 us, 16384 sparse: 1.06 against 1.97 ms).
+int g_auto_leaf = 0;
 // Strassen (depth, serial depth, shifted leaf level) per shape, from bmm_autotune_strassen.
 std::map<std::tuple<int64_t, int64_t, int64_t>, std::tuple<int, int, int>> g_depth;
 // Cubic k-panel schedule per (semiring, m, k, n): panel length in bits, from
@@ -164,6 +169,11 @@ int64_t batch_bucket(int64_t b) {
   return q;
 }
 
+int auto_leaf_locked(int64_t k) {
+  const int leaf = g_auto_leaf > 0 ? g_auto_leaf : BMM_LEAF_MFMA_I8;
+  return leaf == BMM_LEAF_MFMA_F4 && k >= kPanelMaxK ? BMM_LEAF_MFMA_I8 : leaf;
+}
+
 void pick_leaf(int semiring, int64_t m, int64_t k, int64_t n, int64_t batch,
                const bmm_options& o, int* leaf, int* tile) {
   *leaf = o.leaf;
@@ -175,8 +185,8 @@ void pick_leaf(int semiring, int64_t m, int64_t k, int64_t n, int64_t batch,
       if (*leaf == BMM_LEAF_AUTO && it->second.best_leaf > 0) *leaf = it->second.best_leaf;
       if (*tile <= 0 && *leaf >= 1 && *leaf <= 3) *tile = it->second.tile[*leaf];
     }
+    if (*leaf == BMM_LEAF_AUTO) *leaf = auto_leaf_locked(k);
   }
-  if (*leaf == BMM_LEAF_AUTO) *leaf = BMM_LEAF_MFMA_I8;
   if (*tile <= 0) {
     // default MFMA tile for shapes the table lacks, from the gfx950 timings: when 128 x 64
     // wave tiles give fewer than 16 waves per CU over the whole launch, 64 x 64 tiles fill
@@ -233,6 +243,11 @@ int validate_product(const uint64_t* A, int64_t lda, const uint64_t* B, int64_t 
 }  // namespace
 
 namespace bmm {
+
+int auto_leaf(int64_t k) {
+  std::lock_guard<std::mutex> lock(g_mu);
+  return auto_leaf_locked(k);
+}
 
 // Panel length (bits) of a cubic product's k: the options' own (rounded up to whole
 // words; negative = one panel), else the k-panel table's record, else one panel.
@@ -394,6 +409,7 @@ int make_plan(int64_t m, int64_t k, int64_t n, int depth, const bmm_options& o, 
   P.n = n;
   P.nw = words_of(n);
   int tuned_ds = -1, tuned_shift = 0;
+  const bool f4 = (o.leaf == BMM_LEAF_AUTO ? auto_leaf(k) : o.leaf) == BMM_LEAF_MFMA_F4;
   if (depth == -1) {
     std::lock_guard<std::mutex> lock(g_mu);
     auto it = g_depth.find({m, k, n});
@@ -401,13 +417,19 @@ int make_plan(int64_t m, int64_t k, int64_t n, int depth, const bmm_options& o, 
   }
   if (depth == -1) {
     // largest depth keeping every leaf dimension >= 2048 bits (at most 8 levels): the
-    // depth tuner's optimum at n = 2^18 on gfx950 has 2048-bit leaves
+    // depth tuner's optimum at n = 2^18 on gfx950 has 2048-bit leaves with the int8 leaf.
+    // A level takes an eighth off the matrix-core time and adds passes over the operands
+    // and the result, which the twice as fast fp4 leaf repays on larger leaves only:
+    // there the harmonic size mkn / (mk + nk + mn) stays >= 1250 (cubes: 3750 bits; at
+    // n = 16384 leaves of 4096 take 1.14 ms, of 2048 1.22 ms, at n = 65536 55.7 and 59 ms).
     depth = 0;
     while (depth < 8) {
       const int d = depth + 1;
       const int64_t u = (int64_t)1 << d;
       if (m % u || k % (64 * u) || n % (64 * u)) break;
       if (m / u < 2048 || k / u < 2048 || n / u < 2048) break;
+      const double harmonic = 1.0 / (1.0 / (m / u) + 1.0 / (k / u) + 1.0 / (n / u));
+      if (f4 && harmonic < 1250.0) break;
       depth = d;
     }
   }
@@ -421,7 +443,10 @@ int make_plan(int64_t m, int64_t k, int64_t n, int depth, const bmm_options& o, 
     ds = tuned_ds;
     dp = depth - ds;
   } else if (dp < 0 && ds < 0) {
-    dp = std::min(depth, 4);
+    // four breadth-first levels keep the int8 leaf's launches long; with the fp4 leaf two
+    // are better, whose operands and results stay near the caches from the expansion to
+    // the leaf and back (n = 32768: 7.9 against 8.4 ms with three)
+    dp = std::min(depth, f4 ? 2 : 4);
     ds = depth - dp;
   } else if (dp < 0) {
     ds = std::min(ds, depth);
@@ -1192,7 +1217,9 @@ int bmm_autotune_save(const char* path) {
        "# depth m k n depth depth_serial shift\n"
        "# batched count log2_ops leaf tile workgroups_per_cu\n"
        "# batched_class count log2_ops k_class leaf tile\n"
-       "# kpanel semiring m k n panel_bits\n";
+       "# kpanel semiring m k n panel_bits\n"
+       "# auto_leaf leaf\n";
+  if (g_auto_leaf > 0) f << "auto_leaf " << g_auto_leaf << '\n';
   for (auto& [key, val] : g_tune)
     f << "leaf " << key.semiring << ' ' << key.m << ' ' << key.k << ' ' << key.n << ' '
       << key.batch << ' ' << val.best_leaf << ' ' << val.tile[1] << ' ' << val.tile[2] << ' '
@@ -1221,7 +1248,13 @@ int bmm_autotune_load(const char* path) {
     if (line.empty() || line[0] == '#') continue;
     int sr, leaf, t1, t2, t3, d, ds;
     long long m, k, n, b;
-    if (sscanf(line.c_str(), "leaf %d %lld %lld %lld %lld %d %d %d %d", &sr, &m, &k, &n, &b,
+    if (sscanf(line.c_str(), "auto_leaf %d", &leaf) == 1) {
+      if (leaf < BMM_LEAF_VALU || leaf > BMM_LEAF_MFMA_F4)
+        return fail(BMM_E_INVAL, "bad auto_leaf line: %s", line.c_str());
+      std::lock_guard<std::mutex> lock(g_mu);
+      g_auto_leaf = leaf;
+      ++g_batched_gen;
+    } else if (sscanf(line.c_str(), "leaf %d %lld %lld %lld %lld %d %d %d %d", &sr, &m, &k, &n, &b,
                &leaf, &t1, &t2, &t3) == 9) {
       int cnt = 0;
       if ((sr != BMM_GF2 && sr != BMM_BOOLEAN) || m <= 0 || n <= 0 || k < 0 || b <= 0 ||
@@ -1306,6 +1339,7 @@ void bmm_finalize(void) {
   (void)hipSetDevice(cur);
   g_scratch.clear();
   g_tune.clear();
+  g_auto_leaf = 0;
   g_depth.clear();
   g_batched.clear();
   g_bclass.clear();

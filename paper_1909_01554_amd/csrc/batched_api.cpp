@@ -199,8 +199,8 @@ struct PlanSet {
 };
 
 // Choices per problem: opt's leaf and tile where given; else the autotuner's per-class
-// record for plans of this count and total work, else its plan-wide record, else int8
-// with the LDS-staged 128 x 64 item (tile 4).  force_* (>= 0) override everything.
+// record for plans of this count and total work, else its plan-wide record, else the
+// table's auto_leaf (int8 without one) with the LDS-staged 128 x 64 item (tile 4).  force_* (>= 0) override everything.
 int build_set(const bmm_problem* problems, int64_t count, const bmm_options* opt,
               int force_leaf, int force_tile, int force_wpc, PlanSet* out) {
   if (count < 0 || (count > 0 && !problems)) return bfail(BMM_E_INVAL, "bad problem list");
@@ -226,7 +226,7 @@ int build_set(const bmm_problem* problems, int64_t count, const bmm_options* opt
     const bmm_problem& p = problems[i];
     int leaf = oleaf, tile = otile, cl = 0, ct = 0;
     const bool class_rec = batched_class_tuned(count, ops, k_class(p.k), &cl, &ct);
-    if (leaf == BMM_LEAF_AUTO) leaf = class_rec ? cl : (plan_rec ? pl : BMM_LEAF_MFMA_I8);
+    if (leaf == BMM_LEAF_AUTO) leaf = class_rec ? cl : (plan_rec ? pl : auto_leaf(p.k));
     if (tile <= 0) tile = class_rec && cl == leaf ? ct : (plan_rec && pl == leaf ? pt : 4);
     if (force_leaf > 0) leaf = force_leaf;
     if (force_tile > 0) tile = force_tile;

@@ -257,6 +257,8 @@ namespace bmm {
 // Inverse of the result's basis change of a scheme (standard -> alternative basis).
 // Leaf kind and tile of a product (options, then the autotune table, then the
 // default rule), as every entry point chooses them.
+// Leaf kind of BMM_LEAF_AUTO for products of this k without a table entry.
+int auto_leaf(int64_t k);
 void choose_leaf(int semiring, int64_t m, int64_t k, int64_t n, int64_t batch,
                  const bmm_options& o, int* leaf, int* tile);
 // The cubic product behind bmm_gf2 / bmm_boolean.  B^T goes to the library's cached

@@ -351,7 +351,7 @@ extern "C" int bmm_ooc(int semiring, const uint64_t* A, int64_t lda, const uint6
                 bn = std::min(block, (n + 63) / 64 * 64);
   const int64_t bkw = (bk + 63) / 64, bnw = bn / 64;
 
-  int leaf = o.leaf == BMM_LEAF_AUTO ? BMM_LEAF_MFMA_I8 : o.leaf;
+  int leaf = o.leaf == BMM_LEAF_AUTO ? auto_leaf(std::min(bk, k)) : o.leaf;
   if (leaf < BMM_LEAF_VALU || leaf > BMM_LEAF_MFMA_F4) return ofail(BMM_E_INVAL, "unknown leaf");
   if (leaf == BMM_LEAF_MFMA_F4 && std::min(block, k) >= ((int64_t)1 << 24))
     return ofail(BMM_E_UNSUPPORTED, "the fp4 leaf counts exactly only for k < 2^24");
