@@ -1,88 +1,78 @@
 // Bit-matrix transpose in 64 x 64 bit blocks.
 //
-// Lane l holds word (row 64*rb + l, word column wc) of a block; six butterfly stages
-// (distance 32, 16, ..., 1) exchange the off-diagonal halves of ever smaller
-// sub-blocks through cross-lane shuffles, after which lane l holds column
-// 64*wc + l as a 64-bit word over the block's rows.  Bits of rows past the end
+// A workgroup of RB waves transposes a tile of 64 RB rows x CW words: wave i loads rows
+// 64 i .. + 63, a row per lane (16 bytes at a time where rows are 16-byte aligned), turns
+// each word's 64 x 64 block in registers (bit_transpose.h: 31 VALU instructions, no
+// cross-lane traffic through LDS), and leaves the 64-bit pieces of the transposed rows in
+// LDS, from where they go out RB words (8 RB bytes) at a time.  Bits of rows past the end
 // read as zero, so the padding of the transposed rows is zero.
-#include "bmm_internal.h"
+//
+// Bound by memory (large) and by latency (small).  8 x 8 blocks move whole 64-byte halves of
+// a line both ways, in bands of 8 tiles whose pieces of a row are neighbours (16384 x 16384
+// bits: 14.0 us, 4.8 TB/s; in row order 18.7 us; with shuffles through LDS, in row order,
+// 26.6 us; 65536 x 65536: 292, 385 and 402 us).  Matrices of fewer than 256 such tiles take
+// 4 x 2 blocks: 2048 x 2048 bits are 128 workgroups instead of 16, 3.5 us instead of 10.1.
+#include "bit_transpose.h"
 
 namespace bmm {
 namespace {
 
-__device__ __forceinline__ uint64_t swap_stage(uint64_t x, int lane, int j, uint64_t m) {
-  const uint64_t y = __shfl_xor(x, j);
-  if ((lane & j) == 0) {
-    // this lane is row k, the partner row k + j: take the partner's low part
-    const uint64_t t = ((x >> j) ^ y) & m;
-    return x ^ (t << j);
-  }
-  const uint64_t t = ((y >> j) ^ x) & m;
-  return x ^ t;
-}
-
-// A workgroup transposes a tile of 512 rows x 8 words (8 x 8 blocks of 64 x 64
-// bits) through LDS, so global reads and writes move 64 contiguous bytes per
-// eight threads; each wave transposes 16 of the blocks in registers.
-constexpr int TR_ROWS = 512, TR_WORDS = 8, TR_STR = 9;  // padded LDS row (in words)
-
-__global__ __launch_bounds__(256) void transpose_kernel(const uint64_t* __restrict__ src,
-                                                        int64_t lds, int64_t strideS,
-                                                        uint64_t* __restrict__ dst, int64_t ldd,
-                                                        int64_t strideD, int64_t rows,
-                                                        int64_t cols, int64_t n_rt,
-                                                        int64_t n_wt, int64_t batch) {
-  __shared__ uint64_t tile[TR_ROWS * TR_STR];
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int64_t per = n_rt * n_wt;
-  const int64_t b = (int64_t)blockIdx.x / per;
-  if (b >= batch) return;  // uniform per workgroup
-  const int64_t t = (int64_t)blockIdx.x - b * per;
-  const int64_t r0 = (t / n_wt) * TR_ROWS;
-  const int64_t w0 = (t % n_wt) * TR_WORDS;
-  const int64_t src_words = (cols + 63) >> 6;
-  const int64_t dst_words = (rows + 63) >> 6;
+template <int RB, int CW>
+__global__ __launch_bounds__(64 * RB) void transpose_kernel(
+    const uint64_t* __restrict__ src, int64_t lds, int64_t strideS, uint64_t* __restrict__ dst,
+    int64_t ldd, int64_t strideD, int64_t rows, int64_t cols, uint32_t n_rt, uint32_t n_wt,
+    int vec) {
+  constexpr int STR = RB + 1;  // padded LDS row (in words)
+  __shared__ uint64_t tile[64 * CW * STR];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const TileCoord c0 = xcd_tile(blockIdx.x, gridDim.x, n_rt, n_wt);
+  const int64_t b = c0.b, r0 = c0.tm * (64 * RB), w0 = c0.tn * CW;
+  const int64_t src_words = (cols + 63) >> 6, dst_words = (rows + 63) >> 6;
   const uint64_t* S = src + b * strideS;
   uint64_t* D = dst + b * strideD;
-  const int sub_r = tid >> 3, sub_w = tid & 7;
-#pragma unroll 4
-  for (int it = 0; it < TR_ROWS / 32; ++it) {
-    const int lr = it * 32 + sub_r;
-    const int64_t r = r0 + lr, w = w0 + sub_w;
-    tile[lr * TR_STR + sub_w] = (r < rows && w < src_words) ? S[r * lds + w] : 0ull;
-  }
-  __syncthreads();
-  uint64_t res[16];
+  const int64_t r = r0 + 64 * wave + lane;
+  uint64_t x[CW];
+  if (vec && w0 + CW <= src_words) {  // uniform
+    const ulonglong2* p = reinterpret_cast<const ulonglong2*>(S + (r < rows ? r : rows - 1) * lds + w0);
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int blk = wave * 16 + i;
-    const int rb = blk >> 3, wc = blk & 7;
-    uint64_t x = tile[(rb * 64 + lane) * TR_STR + wc];
-    x = swap_stage(x, lane, 32, 0x00000000FFFFFFFFull);
-    x = swap_stage(x, lane, 16, 0x0000FFFF0000FFFFull);
-    x = swap_stage(x, lane, 8, 0x00FF00FF00FF00FFull);
-    x = swap_stage(x, lane, 4, 0x0F0F0F0F0F0F0F0Full);
-    x = swap_stage(x, lane, 2, 0x3333333333333333ull);
-    x = swap_stage(x, lane, 1, 0x5555555555555555ull);
-    res[i] = x;
-  }
-  __syncthreads();
+    for (int i = 0; i < CW / 2; ++i) {
+      const ulonglong2 v = p[i];
+      x[2 * i] = r < rows ? v.x : 0ull;
+      x[2 * i + 1] = r < rows ? v.y : 0ull;
+    }
+  } else {
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int blk = wave * 16 + i;
-    const int rb = blk >> 3, wc = blk & 7;
-    // lane now holds output row (64 * (w0 + wc) + lane), word (r0 / 64 + rb)
-    tile[(wc * 64 + lane) * TR_STR + rb] = res[i];
+    for (int i = 0; i < CW; ++i)
+      x[i] = (r < rows && w0 + i < src_words) ? S[r * lds + w0 + i] : 0ull;
   }
+  const Transpose tr(lane);
+  // lane c then holds output row 64 (w0 + i) + c, word r0 / 64 + wave
+#pragma unroll
+  for (int i = 0; i < CW; ++i) tile[(64 * i + lane) * STR + wave] = transpose64(x[i], tr);
   __syncthreads();
-#pragma unroll 4
-  for (int it = 0; it < TR_ROWS / 32; ++it) {
-    const int orow = it * 32 + sub_r;
-    const int64_t c = w0 * 64 + orow, wd = r0 / 64 + sub_w;
-    if (c < cols && wd < dst_words) D[c * ldd + wd] = tile[orow * TR_STR + sub_w];
+  const int sub_r = tid / RB, sub_w = tid % RB;
+  const int64_t wd = r0 / 64 + sub_w;
+#pragma unroll
+  for (int i = 0; i < CW; ++i) {
+    const int orow = 64 * i + sub_r;
+    const int64_t c = w0 * 64 + orow;
+    if (c < cols && wd < dst_words) D[c * ldd + wd] = tile[orow * STR + sub_w];
   }
+}
+
+template <int RB, int CW>
+hipError_t launch(const uint64_t* src, int64_t lds, int64_t strideS, uint64_t* dst, int64_t ldd,
+                  int64_t strideD, int64_t rows, int64_t cols, int64_t batch, hipStream_t s) {
+  const int64_t n_rt = (rows + 64 * RB - 1) / (64 * RB);
+  const int64_t n_wt = ((cols + 63) / 64 + CW - 1) / CW;
+  const int64_t blocks = n_rt * n_wt * batch;
+  if (!grid_fits(blocks, 64 * RB)) return kGridTooLarge;
+  const int vec = (reinterpret_cast<uintptr_t>(src) & 15) == 0 && ((lds | strideS) & 1) == 0;
+  hipLaunchKernelGGL((transpose_kernel<RB, CW>), dim3((unsigned)blocks), dim3(64 * RB), 0, s, src,
+                     lds, strideS, dst, ldd, strideD, rows, cols, (uint32_t)n_rt, (uint32_t)n_wt,
+                     vec);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -91,13 +81,9 @@ hipError_t launch_transpose(const uint64_t* src, int64_t lds, int64_t strideS, u
                             int64_t ldd, int64_t strideD, int64_t rows, int64_t cols,
                             int64_t batch, hipStream_t s) {
   if (rows <= 0 || cols <= 0 || batch <= 0) return hipSuccess;
-  const int64_t n_rt = (rows + TR_ROWS - 1) / TR_ROWS;
-  const int64_t n_wt = ((cols + 63) / 64 + TR_WORDS - 1) / TR_WORDS;
-  const int64_t blocks = n_rt * n_wt * batch;
-  if (!grid_fits(blocks, 256)) return kGridTooLarge;
-  hipLaunchKernelGGL(transpose_kernel, dim3((unsigned)blocks), dim3(256), 0, s, src, lds,
-                     strideS, dst, ldd, strideD, rows, cols, n_rt, n_wt, batch);
-  return hipGetLastError();
+  const bool small = ((rows + 511) / 512) * ((cols + 511) / 512) * batch < 256;
+  return small ? launch<4, 2>(src, lds, strideS, dst, ldd, strideD, rows, cols, batch, s)
+               : launch<8, 8>(src, lds, strideS, dst, ldd, strideD, rows, cols, batch, s);
 }
 
 }  // namespace bmm
