@@ -83,9 +83,10 @@ __device__ __forceinline__ TileCoord xcd_tile(uint32_t g, uint32_t total, int64_
 }
 
 // MFMA leaf variants (rows x cols of C per wave, or per workgroup for the last and the
-// fifth).  64 x 64 and 64 x 32 are the register-fed tiles for small products, and int8 has
-// the unrolled register-fed 128 x 64 pipeline (k = 2048 and 4096) and the chunked 64 x 128
-// loop (k >= 2^24); every other choice is the panel leaf, which picks its shape itself.
+// fifth).  64 x 64 is the panel leaf's small form, 64 x 32 always the one with k split over
+// waves, and int8 has the unrolled register-fed 128 x 64 pipeline (k = 2048 and 4096) and,
+// from k = 2^24 on, the chunked 64 x 128 loop; every other choice is the panel leaf, which
+// picks its shape itself.
 enum MfmaTile { MFMA_128x64 = 0, MFMA_64x64 = 1, MFMA_64x128 = 2, MFMA_64x32 = 3,
                 MFMA_LDS_256x256 = 4, MFMA_DEEP_128x64 = 5, MFMA_CHUNK_64x128 = 6,
                 MFMA_LDS4_256x128 = 7, MFMA_NUM_TILES };
@@ -100,6 +101,11 @@ constexpr int64_t kNearPitch = (int64_t)1 << 20;
 // The LDS-staged leaf of panel_tile.h (fmt: mfma::MfmaFormat) on 2 x 2 wave tiles of 64 x 128
 // or 128 x 64, whichever the shape pads less; k < kPanelMaxK.
 hipError_t launch_leaf_panel(int semiring, int fmt, const LeafBatch& p, hipStream_t s);
+// The same on smaller tiles, for products that would leave CUs idle: 128 x 128 per workgroup,
+// or (split, and where even those are few) 64 x 64 with k split over a workgroup's waves.
+hipError_t launch_leaf_small(int semiring, int fmt, const LeafBatch& p, bool split, hipStream_t s);
+// Whether a batch of m x n results is small in this sense.
+bool leaf_small_tiles(int64_t m, int64_t n, int64_t batch);
 hipError_t launch_leaf_valu(int semiring, const LeafBatch& p, int tile, hipStream_t s);
 // The VALU leaf in outer-product form (tile 2): B row-major (k x n, pitch ldb words), one
 // product; k = 0 leaves C zero (or unchanged when accumulating).

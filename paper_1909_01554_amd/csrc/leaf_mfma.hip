@@ -51,35 +51,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void l
                                     p.accumulate);
 }
 
-// The register-fed leaf with the 2-deep loop (16-byte loads where the operands are aligned).
-// CHUNKED: aligned int8 leaves run the pipeline as a loop over fully unrolled chunks of 12
-// steps, which leaves the compiler's conservative wait for outstanding loads at the loop's
-// back edge once per chunk instead of once per step pair.
-template <int SEMI, int RA, int RB, int FMT, bool CHUNKED = false>
-hipError_t launch_t(const LeafBatch& p, hipStream_t s) {
-  constexpr int TM = 32 * RA, TN = 32 * RB;
-  const int64_t tiles_m = (p.m + TM - 1) / TM;
-  // cover whole 64-bit output words, so padding dwords are written (as zero)
-  const int64_t tiles_n = (((p.n + 63) / 64) * 64 + TN - 1) / TN;
+// int8 from k = 2^24 on, where the panel leaf's products of 2^7 would overflow int32 sums:
+// 64 x 128 wave tiles fed from registers, 0/1 operand bytes.  Aligned operands run the load
+// pipeline as a loop over fully unrolled chunks of 12 steps, which leaves the compiler's
+// conservative wait for outstanding loads at the loop's back edge once per chunk instead of
+// once per step pair.
+template <int SEMI>
+hipError_t launch_long(const LeafBatch& p, hipStream_t s) {
+  const int64_t tiles_m = (p.m + 63) / 64, tiles_n = (p.n + 127) / 128;
   const int64_t blocks = ((tiles_m + 1) / 2) * ((tiles_n + 1) / 2) * p.batch;
   if (blocks == 0) return hipSuccess;
   if (!grid_fits(blocks, 256)) return kGridTooLarge;
   const dim3 g((unsigned)blocks), b(256);
-  if constexpr (CHUNKED) {
-    if (aligned16(p)) {
-      hipLaunchKernelGGL((leaf_mfma_kernel<SEMI, RA, RB, 2, FMT, 2, -12>), g, b, 0, s, p,
-                         tiles_m, tiles_n);
-      return hipGetLastError();
-    }
-  }
-  // int8: the 64-bit expansion; fp4: the 32-bit form (the wide one spills)
-  constexpr bool kWideForm = FMT == mfma::FMT_I8;
-  constexpr bool kShort = RA > RB;
   if (aligned16(p))
-    hipLaunchKernelGGL((leaf_mfma_kernel<SEMI, RA, RB, 2, FMT, 2, 0, kWideForm, kShort>), g, b, 0,
-                       s, p, tiles_m, tiles_n);
+    hipLaunchKernelGGL((leaf_mfma_kernel<SEMI, 2, 4, 2, mfma::FMT_I8, 2, -12>), g, b, 0, s, p,
+                       tiles_m, tiles_n);
   else
-    hipLaunchKernelGGL((leaf_mfma_kernel<SEMI, RA, RB, 1, FMT, 2, 0, kWideForm, kShort>), g, b, 0,
+    hipLaunchKernelGGL((leaf_mfma_kernel<SEMI, 2, 4, 1, mfma::FMT_I8, 2, 0, true, false>), g, b, 0,
                        s, p, tiles_m, tiles_n);
   return hipGetLastError();
 }
@@ -101,16 +89,15 @@ hipError_t launch_deep(const LeafBatch& p, hipStream_t s) {
 
 template <int SEMI, int FMT>
 hipError_t launch_semi(const LeafBatch& p, int tile, hipStream_t s) {
-  if (tile == MFMA_64x64) return launch_t<SEMI, 2, 2, FMT>(p, s);
-  if (tile == MFMA_64x32) return launch_t<SEMI, 2, 1, FMT>(p, s);
   if constexpr (FMT == mfma::FMT_I8) {
-    // the panel leaf's products of 2^7 would overflow int32 sums from k = 2^24 on
-    if (p.k >= panel::kMaxK) return launch_t<SEMI, 2, 4, FMT, true>(p, s);
+    if (p.k >= panel::kMaxK) return launch_long<SEMI>(p, s);
     if (tile == MFMA_DEEP_128x64 && aligned16(p)) {
       if (p.k == 2048) return launch_deep<SEMI, 8>(p, s);
       if (p.k == 4096) return launch_deep<SEMI, 16>(p, s);
     }
   }
+  if (tile == MFMA_64x64 || tile == MFMA_64x32)
+    return launch_leaf_small(SEMI, FMT, p, tile == MFMA_64x32, s);
   return launch_leaf_panel(SEMI, FMT, p, s);
 }
 

@@ -1,6 +1,9 @@
 // Cubic leaf on the matrix cores with operand rows staged in LDS by direct loads (see
-// panel_tile.h for the tile and its operands): one workgroup per 128 x 256 or 256 x 128
-// tile of C, two workgroups per CU.
+// panel_tile.h for the tiles and their operands): one workgroup per 128 x 256 or 256 x 128
+// tile of C, two workgroups per CU; for smaller products one per 128 x 128 tile, or per 64 x
+// 64 tile with k split over its waves.
+#include <algorithm>
+
 #include "panel_tile.h"
 
 namespace bmm {
@@ -41,7 +44,54 @@ hipError_t launch_semi(const LeafBatch& p, hipStream_t s) {
               : launch_shape<SEMI, FMT, 4, 2, false>(p, s);
 }
 
+constexpr int kSplit = 4;  // waves that share a 64 x 64 tile
+
+template <int SEMI, int FMT>
+__global__ __launch_bounds__(64 * kSplit) __attribute__((amdgpu_waves_per_eu(2))) void
+leaf_split_kernel(LeafBatch p, int64_t grid_m, int64_t grid_n) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[kSplit * panel::kSplitBytes];
+  const TileCoord c = xcd_tile(blockIdx.x, gridDim.x, grid_m, grid_n);
+  panel::split_tile<SEMI, FMT, kSplit>(
+      p.A + c.b * p.strideA, p.lda, p.BT + c.b * p.strideB, p.ldbt, p.C + c.b * p.strideC, p.ldc,
+      p.m, p.k, p.n, c.tm, c.tn, p.accumulate,
+      __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), smem);
+}
+
+template <int SEMI, int FMT>
+hipError_t launch_small(const LeafBatch& p, bool split, hipStream_t s) {
+  const int64_t grid_m = (p.m + 63) / 64, grid_n = (p.n + 63) / 64;
+  const int64_t blocks = grid_m * grid_n * p.batch;
+  // up to 512 tiles of 64 x 64, two workgroups per CU, the split form is the faster one
+  // (512: 10.3 against 16.7 us; 1024, at n = 2048: 9.8 against 8.1 us)
+  if (!split && blocks > 512 && p.lda < kNearPitch && p.ldbt < kNearPitch)
+    return launch_shape<SEMI, FMT, 2, 2, false>(p, s);
+  if (!grid_fits(blocks, 64 * kSplit)) return kGridTooLarge;
+  hipLaunchKernelGGL((leaf_split_kernel<SEMI, FMT>), dim3((unsigned)blocks), dim3(64 * kSplit), 0,
+                     s, p, grid_m, grid_n);
+  return hipGetLastError();
+}
+
 }  // namespace
+
+bool leaf_small_tiles(int64_t m, int64_t n, int64_t batch) {
+  auto tiles = [&](int64_t r, int64_t c) { return ((m + r - 1) / r) * ((n + c - 1) / c) * batch; };
+  const int64_t large = std::min(tiles(128, 256), tiles(256, 128)), small = tiles(128, 128);
+  // whole rounds over 256 CUs; a small tile is half the work of a large one, and costs
+  // 4 to 13% more per unit (n = 4096, 4 rounds against 2: 25.5 and 24.0 us; n = 3072, 3
+  // against 2: 16.0 and 18.7 us; 5001 x 7003 x 3333, 5 against 3: 50.5 and 58.7 us)
+  return tiles(64, 64) <= 512 || 0.54 * ((small + 255) / 256) < (double)((large + 255) / 256);
+}
+
+hipError_t launch_leaf_small(int semiring, int fmt, const LeafBatch& p, bool split,
+                             hipStream_t s) {
+  if (p.m <= 0 || p.n <= 0 || p.batch <= 0) return hipSuccess;
+  if (p.k >= panel::kMaxK) return hipErrorInvalidValue;  // counts would not be exact
+  if (fmt == mfma::FMT_F4)
+    return semiring == GF2 ? launch_small<GF2, mfma::FMT_F4>(p, split, s)
+                           : launch_small<BOOLEAN, mfma::FMT_F4>(p, split, s);
+  return semiring == GF2 ? launch_small<GF2, mfma::FMT_I8>(p, split, s)
+                         : launch_small<BOOLEAN, mfma::FMT_I8>(p, split, s);
+}
 
 hipError_t launch_leaf_panel(int semiring, int fmt, const LeafBatch& p, hipStream_t s) {
   if (p.m <= 0 || p.n <= 0 || p.batch <= 0) return hipSuccess;

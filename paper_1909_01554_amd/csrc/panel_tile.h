@@ -34,6 +34,7 @@
 
 #include <type_traits>
 
+#include "bit_transpose.h"
 #include "mfma_tile.h"
 
 namespace bmm {
@@ -143,48 +144,55 @@ __device__ __forceinline__ typename mfma::Acc<FMT>::type step(
   }
 }
 
-// The lane index as a fresh value: what is derived from it (addresses, selectors) is not
-// computed earlier than here and kept in registers across a main loop or a persistent one.
-__device__ __forceinline__ int fresh_lane() {
-  int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-  asm volatile("" : "+v"(lane));
-  return lane;
+// The counts are computed where this is called.
+__device__ __forceinline__ void computed(const v16f& acc) { asm volatile("" ::"v"(acc)); }
+__device__ __forceinline__ void computed(const v16i& acc) { asm volatile("" ::"v"(acc)); }
+
+// One round: 128 bits per lane (256 per row) of RA rows of A and RB rows of B^T.
+template <int SEMI, int FMT, int RA, int RB, class AccV>
+__device__ __forceinline__ void mfma_round(u4 (&xa)[RA], u4 (&xb)[RB], AccV (&acc)[RA][RB]) {
+  constexpr bool SIGNED_OK = SEMI == GF2;
+  constexpr bool REV_A = RA < RB;  // int8: the side with fewer rows is reversed
+  if constexpr (FMT == FMT_I8) {
+#pragma unroll
+    for (int f = 0; f < RA; ++f)
+      if constexpr (REV_A) xa[f] = reverse_bytes(xa[f]);
+#pragma unroll
+    for (int g = 0; g < RB; ++g)
+      if constexpr (!REV_A) xb[g] = reverse_bytes(xb[g]);
+  }
+  auto one = [&](auto dc) {
+    constexpr int D = decltype(dc)::value;
+    if constexpr (D < Planes<FMT>::N) {
+      v4i eb[RB];
+#pragma unroll
+      for (int g = 0; g < RB; ++g) eb[g] = plane<FMT, D, !REV_A, SIGNED_OK>(xb[g]);
+#pragma unroll
+      for (int f = 0; f < RA; ++f) {
+        const v4i ea = plane<FMT, D, REV_A, SIGNED_OK>(xa[f]);
+#pragma unroll
+        for (int g = 0; g < RB; ++g) acc[f][g] = step<FMT, D>(ea, eb[g], acc[f][g]);
+      }
+    }
+  };
+  one(std::integral_constant<int, 0>{});
+  one(std::integral_constant<int, 1>{});
+  one(std::integral_constant<int, 2>{});
+  one(std::integral_constant<int, 3>{});
+  one(std::integral_constant<int, 4>{});
+  one(std::integral_constant<int, 5>{});
+  one(std::integral_constant<int, 6>{});
+  one(std::integral_constant<int, 7>{});
+  // the round ends here: the compiler would otherwise sink it below the next barrier, and
+  // the LDS reads issued before it would have nothing to hide behind
+#pragma unroll
+  for (int f = 0; f < RA; ++f)
+#pragma unroll
+    for (int g = 0; g < RB; ++g) computed(acc[f][g]);
+  __builtin_amdgcn_sched_barrier(0);
 }
 
 // ---- results ----
-
-// 32 x 32 bit transposes over the 32 lanes of each wave half, by five exchanges between
-// lanes 16, 8, 4, 2 and 1 apart (3 VALU instructions each, where a ballot and two selects
-// per count take 7 per count); the selectors depend on the lane only.
-struct Transpose {
-  uint32_t s16, s8, r4, m4, r2, m2, r1, m1;
-  __device__ __forceinline__ explicit Transpose(int lane) {
-    s16 = (lane & 16) ? 0x07060302u : 0x05040100u;
-    s8 = (lane & 8) ? 0x03070105u : 0x06020400u;
-    r4 = (lane & 4) ? 4 : 28;
-    m4 = (lane & 4) ? 0x0f0f0f0fu : 0xf0f0f0f0u;
-    r2 = (lane & 2) ? 2 : 30;
-    m2 = (lane & 2) ? 0x33333333u : 0xccccccccu;
-    r1 = (lane & 1) ? 1 : 31;
-    m1 = (lane & 1) ? 0x55555555u : 0xaaaaaaaau;
-  }
-  template <int CTRL>
-  static __device__ __forceinline__ uint32_t dpp(uint32_t x) {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, true);
-  }
-  static __device__ __forceinline__ uint32_t merge(uint32_t m, uint32_t y, uint32_t r, uint32_t x) {
-    return (m & __builtin_amdgcn_alignbit(y, y, r)) | (~m & x);
-  }
-  __device__ __forceinline__ uint32_t operator()(uint32_t x) const {
-    const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-    x = __builtin_amdgcn_perm(r[1], r[0], s16);
-    x = __builtin_amdgcn_perm(dpp<0x128>(x), x, s8);        // row_ror:8
-    x = merge(m4, dpp<0x1B>(dpp<0x141>(x)), r4, x);         // half mirror, then 3 - i
-    x = merge(m2, dpp<0x4E>(x), r2, x);                     // quad_perm [2,3,0,1]
-    x = merge(m1, dpp<0xB1>(x), r1, x);                     // quad_perm [1,0,3,2]
-    return x;
-  }
-};
 
 // The 16 result bits of a lane's column of one 32 x 32 block, bit v of the upper half of
 // the dword (E2M1 parity) or of the lower half (else): two instructions per count, one
@@ -281,7 +289,6 @@ __device__ __forceinline__ void tile(const uint64_t* __restrict__ A, int64_t lda
                                      unsigned char* smem) {
   constexpr int TM = 64 * RA, TN = 64 * RB, NL = (TM + TN) / 64;
   constexpr int STAGE = (TM + TN) * kRowBytes;
-  constexpr bool SIGNED_OK = SEMI == GF2;
   const int wy = w >> 1, wx = w & 1;
   const int64_t kw = (k + 63) >> 6;
   const int64_t stages = (kw + kWords - 1) / kWords;
@@ -369,47 +376,6 @@ __device__ __forceinline__ void tile(const uint64_t* __restrict__ A, int64_t lda
   };
   using AccV = typename mfma::Acc<FMT>::type;
   AccV acc[RA][RB];
-  auto round = [&](int s) {
-    constexpr bool REV_A = RA < RB;  // int8: the side with fewer rows is reversed
-    if constexpr (FMT == FMT_I8) {
-#pragma unroll
-      for (int f = 0; f < RA; ++f)
-        if (REV_A) xa[s][f] = reverse_bytes(xa[s][f]);
-#pragma unroll
-      for (int g = 0; g < RB; ++g)
-        if (!REV_A) xb[s][g] = reverse_bytes(xb[s][g]);
-    }
-    auto one = [&](auto dc) {
-      constexpr int D = decltype(dc)::value;
-      if constexpr (D < Planes<FMT>::N) {
-        v4i eb[RB];
-#pragma unroll
-        for (int g = 0; g < RB; ++g) eb[g] = plane<FMT, D, !REV_A, SIGNED_OK>(xb[s][g]);
-#pragma unroll
-        for (int f = 0; f < RA; ++f) {
-          const v4i ea = plane<FMT, D, REV_A, SIGNED_OK>(xa[s][f]);
-#pragma unroll
-          for (int g = 0; g < RB; ++g) acc[f][g] = step<FMT, D>(ea, eb[g], acc[f][g]);
-        }
-      }
-    };
-    one(std::integral_constant<int, 0>{});
-    one(std::integral_constant<int, 1>{});
-    one(std::integral_constant<int, 2>{});
-    one(std::integral_constant<int, 3>{});
-    one(std::integral_constant<int, 4>{});
-    one(std::integral_constant<int, 5>{});
-    one(std::integral_constant<int, 6>{});
-    one(std::integral_constant<int, 7>{});
-    // the round ends here: the compiler would otherwise sink it below the next barrier,
-    // and the LDS reads issued before it would have nothing to hide behind
-#pragma unroll
-    for (int f = 0; f < RA; ++f)
-#pragma unroll
-      for (int g = 0; g < RB; ++g) asm volatile("" ::"v"(acc[f][g]));
-    __builtin_amdgcn_sched_barrier(0);
-  };
-
 #pragma unroll
   for (int f = 0; f < RA; ++f)
 #pragma unroll
@@ -423,18 +389,137 @@ __device__ __forceinline__ void tile(const uint64_t* __restrict__ A, int64_t lda
   int cur = 0;
   for (int64_t st = 0; st < stages; ++st) {
     read(cur, 1);
-    round(0);
+    mfma_round<SEMI, FMT>(xa[0], xb[0], acc);
     if (st + 1 < stages) {
       stage_sync();
       if (st + 2 < stages) load(st + 2, cur);
       read(cur ^ 1, 0);
     }
-    if (st * kWords + 4 < kw) round(1);  // else only zero words are left
+    if (st * kWords + 4 < kw) mfma_round<SEMI, FMT>(xa[1], xb[1], acc);  // else only zero words are left
     cur ^= 1;
   }
   __builtin_amdgcn_s_setprio(0);
   store_tile<SEMI, FMT, RA, RB>(acc, C, ldc, m, n, row0 + wy * 32 * RA,
                                 (col0 >> 6) + wx * (RB / 2), accumulate, semiring);
+}
+
+// ---- small products: k split over a workgroup's waves ----
+
+// Rows [64 im, ...) x columns [64 in, ...) of C = A B by W waves that share the tile and
+// take the 512-bit stages of k in turn (w, w + W, ...), each staging its 128 operand rows in
+// 8 KB of LDS of its own (no barrier in the loop: a wave reads a stage into registers and
+// loads its next one into the same place; a second buffer per wave gained nothing).  At the end the waves' result bits, one word per
+// lane, are XORed or ORed through LDS.  For products whose larger tiles would leave CUs
+// idle: a wave's chain of loads is W times shorter, and there are 8 W waves where the panel
+// tile of 128 x 256 has 4.  Bound by the latency of those chains (fp4, 704 x 16704 x 2368:
+// 17.6 us, with 128 x 128 tiles 31.6 us; 256 x 8192 x 8192: 10.3 and 16.7 us; before, with
+// register-fed 64 x 64 wave tiles, 35.6 and 18.2 us).  0 < k < 2^24; smem: kSplitBytes W bytes.
+constexpr int kSplitBytes = 128 * kRowBytes;
+
+template <int SEMI, int FMT, int W>
+__device__ __forceinline__ void split_tile(const uint64_t* __restrict__ A, int64_t lda,
+                                           const uint64_t* __restrict__ BT, int64_t ldbt,
+                                           uint64_t* C, int64_t ldc, int64_t m, int64_t k,
+                                           int64_t n, int64_t im, int64_t in, int accumulate,
+                                           int w, unsigned char* smem) {
+  const int64_t kw = (k + 63) >> 6;
+  const int stages = (int)((kw + kWords - 1) / kWords);
+  const int64_t row0 = im * 64, col0 = in * 64;
+  const uint64_t* Ab = A + row0 * lda;
+  const uint64_t* Bb = BT + col0 * ldbt;
+  unsigned char* const mine = smem + w * kSplitBytes;
+  const int lane = fresh_lane(), half = lane >> 5, li = lane & 31;
+  const int chunk = (lane & 3) ^ ((lane >> 3) & 3);
+  // load i fills LDS rows 16 i .. + 15 (A's 64 rows, then B^T's)
+  const uint64_t* src[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const bool isA = i < 4;
+    const int64_t lim = isA ? m - 1 - row0 : n - 1 - col0;
+    int64_t r = 16 * (i & 3) + (lane >> 2);
+    r = r < lim ? r : lim;
+    src[i] = (isA ? Ab : Bb) + r * (isA ? lda : ldbt) + 2 * chunk;
+  }
+  typedef __attribute__((address_space(3))) unsigned char* lds_ptr;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr)mine;
+  auto load = [&](int st) {
+    const int64_t w0 = (int64_t)st * kWords;
+    if (w0 + kWords <= kw) {  // uniform
+#pragma unroll
+      for (int i = 0; i < 8; ++i) load_lds16(src[i] + w0, lds0 + i * 1024);
+      return;
+    }
+    const int left = (int)(kw - w0) - 2 * chunk;  // words of the lane's chunk and after
+    const int o0 = left > 0 ? 0 : left - 1, o1 = left > 1 ? 1 : left - 1;
+    uint64_t x[8][2];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      x[i][0] = ((mfma::gq_ptr)src[i])[w0 + o0];
+      x[i][1] = ((mfma::gq_ptr)src[i])[w0 + o1];
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      ulonglong2 v;
+      v.x = left > 0 ? x[i][0] : 0ull;
+      v.y = left > 1 ? x[i][1] : 0ull;
+      *reinterpret_cast<ulonglong2*>(mine + i * 1024 + lane * 16) = v;
+    }
+  };
+  using AccV = typename mfma::Acc<FMT>::type;
+  AccV acc[2][2];
+#pragma unroll
+  for (int f = 0; f < 2; ++f)
+#pragma unroll
+    for (int g = 0; g < 2; ++g) acc[f][g] = AccV{};
+  const int base = li * kRowBytes + (half ^ ((li >> 1) & 3)) * 16;
+  if (w < stages) load(w);
+  for (int st = w; st < stages; st += W) {
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    u4 xa[2][2], xb[2][2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int f = 0; f < 2; ++f) {
+        xa[s][f] = *reinterpret_cast<const u4*>(mine + (base ^ (32 * s)) + 2048 * f);
+        xb[s][f] = *reinterpret_cast<const u4*>(mine + 4096 + (base ^ (32 * s)) + 2048 * f);
+      }
+    if (st + W < stages) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // read: the next stage may land
+      load(st + W);
+    }
+    mfma_round<SEMI, FMT>(xa[0], xb[0], acc);
+    if ((int64_t)st * kWords + 4 < kw) mfma_round<SEMI, FMT>(xa[1], xb[1], acc);
+  }
+  // lane li of half h holds row r(li) of block h: one word of C per lane and wave
+  constexpr bool gf2 = SEMI == GF2;
+  uint64_t word = 0;
+  {
+    const Transpose tr(lane);
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      const auto s = __builtin_amdgcn_permlane32_swap(pack16<FMT>(acc[0][g], gf2),
+                                                      pack16<FMT>(acc[1][g], gf2), false, false);
+      const uint32_t x =
+          tr(__builtin_amdgcn_perm(s[1], s[0], packs_high<FMT>(gf2) ? 0x07060302u : 0x05040100u));
+      word |= (uint64_t)x << (32 * g);
+    }
+  }
+  uint64_t* const part = reinterpret_cast<uint64_t*>(smem);
+  __syncthreads();  // every wave is done with its stages
+  if (w > 0) part[w * 64 + lane] = word;
+  __syncthreads();
+  if (w > 0) return;
+#pragma unroll
+  for (int i = 1; i < W; ++i) word = gf2 ? word ^ part[i * 64 + lane] : word | part[i * 64 + lane];
+  const int r = ((li >> 2) & 3) * 8 + (li >> 4) * 4 + (li & 3);
+  const int64_t row = row0 + 32 * half + r;
+  if (row < m) {
+    const int64_t valid = n - col0;
+    if (valid < 64) word &= ((uint64_t)1 << valid) - 1;
+    const mfma::gw_ptr dst = (mfma::gw_ptr)C + row * ldc + in;
+    if (accumulate) word = gf2 ? (word ^ *dst) : (word | *dst);
+    *dst = word;
+  }
 }
 
 }  // namespace panel

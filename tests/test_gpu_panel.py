@@ -82,3 +82,47 @@ def test_longest_counts(bmm, fname, leaf, k):
         product(bmm, sr)(to_dev(A), to_dev(BT), Cd, m, k, n, b_transposed=True,
                          options=bmm.Options(leaf=leaf, tile=1))
         assert [int(x) for x in from_dev(Cd)[:, 0]] == [31 * b for b in bits]
+
+
+# products of the small tiles: 64 x 64 with k split over four waves (up to 512 such tiles)
+# and, from 513 of them, 128 x 128; k from one word to beyond the four waves' first stages
+SMALL = [(64, 64, 64), (65, 2048, 65), (63, 2049, 200), (200, 1536, 63), (33, 5000, 300),
+         (1, 1, 1), (1500, 577, 1500), (1537, 1024, 1473), (1600, 100, 1409)]
+
+
+@pytest.mark.parametrize("sname,sr", SEMIRINGS)
+@pytest.mark.parametrize("fname,leaf", FORMATS)
+@pytest.mark.parametrize("tile", [2, 4])
+def test_small_tiles(bmm, sname, sr, fname, leaf, tile):
+    for i, (m, k, n) in enumerate(SMALL):
+        p = bmmgen.Dist.half() if sr == oracle.GF2 else bmmgen.Dist.inv_sqrt(k)
+        A = bmmgen.fill_cpu(m, k, 91 + i, bmmgen.TAG_A, p)
+        B = bmmgen.fill_cpu(k, n, 91 + i, bmmgen.TAG_B, p)
+        C0 = bmmgen.fill_cpu(m, n, 91 + i, 0xC0, bmmgen.Dist.half())
+        ab = oracle.mul(A, B, k, n, sr)
+        for acc in (False, True):
+            announce("small", sname, fname, tile, (m, k, n), acc)
+            Cd = to_dev(C0, words(n) + i % 2) if acc else empty_dev(m, words(n) + i % 2, fill=-1)
+            product(bmm, sr)(to_dev(A, A.shape[1] + i % 2), to_dev(B), Cd, m, k, n,
+                             options=bmm.Options(leaf=leaf, tile=tile), accumulate=acc)
+            want = ab if not acc else (ab ^ C0 if sr == oracle.GF2 else ab | C0)
+            assert np.array_equal(from_dev(Cd, words(n)), want), (m, k, n, acc)
+
+
+def test_transpose_edges(bmm):
+    """Both tile sizes of the transpose (fewer than 256 tiles of 512 x 512 bits, or not), odd
+    pitches, and edges within and past a 64-bit block; padding bits come out zero."""
+    for i, (r, c) in enumerate([(1, 1), (64, 64), (65, 63), (257, 129), (511, 1025), (8200, 8129),
+                                (16400, 4161)]):
+        X = bmmgen.fill_cpu(r, c, 17 + i, bmmgen.TAG_A, bmmgen.Dist.half())
+        for pad in (0, 1):
+            announce("transpose", (r, c), pad)
+            D = empty_dev(c, words(r) + pad, fill=-1)
+            bmm.bmm_transpose(to_dev(X, X.shape[1] + pad), D, r, c)
+            got = from_dev(D)
+            bits = np.unpackbits(X.view(np.uint8), axis=1, bitorder="little")[:, :c]
+            want = np.zeros((c, words(r) * 64), dtype=np.uint8)
+            want[:, :r] = bits.T
+            want = np.packbits(want, axis=1, bitorder="little").view(np.uint64)
+            assert np.array_equal(got[:, :words(r)], want), (r, c, pad)
+            assert pad == 0 or (got[:, -1] == np.uint64(2**64 - 1)).all()
