@@ -418,16 +418,25 @@ int make_plan(int64_t m, int64_t k, int64_t n, int depth, const bmm_options& o, 
     // A level takes an eighth off the matrix-core time and adds passes over the operands
     // and the result, which the twice as fast fp4 leaf repays on larger leaves only:
     // there the harmonic size mkn / (mk + nk + mn) stays >= 1250 (cubes: 3750 bits; at
-    // n = 16384 leaves of 4096 take 1.14 ms, of 2048 1.22 ms, at n = 65536 55.7 and 59 ms).
-    depth = 0;
-    while (depth < 8) {
-      const int d = depth + 1;
+    // n = 32768 leaves of 4096 take 7.6 ms, of 2048 8.1 ms, at n = 65536 54.5 and 58 ms).
+    auto admits = [&](int d) {
       const int64_t u = (int64_t)1 << d;
-      if (m % u || k % (64 * u) || n % (64 * u)) break;
-      if (m / u < 2048 || k / u < 2048 || n / u < 2048) break;
-      const double harmonic = 1.0 / (1.0 / (m / u) + 1.0 / (k / u) + 1.0 / (n / u));
-      if (f4 && harmonic < 1250.0) break;
-      depth = d;
+      return m % u == 0 && k % (64 * u) == 0 && n % (64 * u) == 0 && m / u >= 2048 &&
+             k / u >= 2048 && n / u >= 2048;
+    };
+    depth = 0;
+    while (depth < 8 && admits(depth + 1)) {
+      const double u = (double)((int64_t)2 << depth);
+      if (f4 && 1.0 / (u / m + u / k + u / n) < 1250.0) break;
+      ++depth;
+    }
+    // a second level is merged into the first one's passes, so it still pays on half that
+    // leaf (n = 8192: 185 us with two levels, 196 with one, 212 without; n = 12288: 480, 509,
+    // 546); a single level does not where k is short, which is when the result's passes
+    // weigh most (22528 x 4608 x 18432: 617 us with it, 568 without)
+    if (f4 && depth <= 1) {
+      if (admits(2)) depth = 2;
+      else if (k < 6000) depth = 0;
     }
   }
   const int64_t u = (int64_t)1 << depth;
@@ -522,6 +531,7 @@ struct StrassenRun {
   char* ws;
   int leaf, tile;
   hipStream_t s;
+  int basis;  // 1: standard-basis operands and result, changed level by level on the way
 
   uint64_t* at(size_t off) const { return reinterpret_cast<uint64_t*>(ws + off); }
 
@@ -538,17 +548,9 @@ struct StrassenRun {
       const int step = p.psteps[i];
       const int64_t M = p.m >> lvl, KW = p.kw >> lvl, N = p.n >> lvl;
       const Level& L = p.par[i];
-      if (step == 2) {
-        HIP_TRY(launch_expand2(0, curT, pitchT, strideT, at(L.T), M, KW, inst, s, p.scheme),
-                "expand2 T");
-        HIP_TRY(launch_expand2(1, curS, pitchS, strideS, at(L.S), N, KW, inst, s, p.scheme),
-                "expand2 S");
-      } else {
-        HIP_TRY(launch_expand(0, curT, pitchT, strideT, at(L.T), M, KW, inst, s, p.scheme),
-                "expand T");
-        HIP_TRY(launch_expand(1, curS, pitchS, strideS, at(L.S), N, KW, inst, s, p.scheme),
-                "expand S");
-      }
+      HIP_TRY(launch_expand_pair(step, curT, pitchT, strideT, at(L.T), M, curS, pitchS, strideS,
+                                 at(L.S), N, KW, inst, basis, s, p.scheme),
+              "expand");
       lvl += step;
       inst *= step == 2 ? 49 : 7;
       curT = at(L.T);
@@ -594,12 +596,8 @@ struct StrassenRun {
       }
       const int64_t M2 = p.m >> lvl, NW2 = p.nw >> lvl;
       const int a = i == 0 ? acc : 0;
-      if (step == 2)
-        HIP_TRY(launch_compress2(src, dst, ldd, strideD, M2, NW2, inst, s, a, p.scheme),
-                "compress2");
-      else
-        HIP_TRY(launch_compress(src, dst, ldd, strideD, M2, NW2, inst, s, a, p.scheme),
-                "compress");
+      HIP_TRY(launch_compress(step, src, dst, ldd, strideD, M2, NW2, inst, s, a, basis, p.scheme),
+              "compress");
     }
     return BMM_OK;
   }
@@ -621,13 +619,15 @@ struct StrassenRun {
       }
       return BMM_OK;
     }
-    HIP_TRY(launch_expand(0, T, ldT, 0, at(L.T), M, KW, 1, s, p.scheme), "serial expand T");
-    HIP_TRY(launch_expand(1, S, ldS, 0, at(L.S), N, KW, 1, s, p.scheme), "serial expand S");
+    HIP_TRY(launch_expand_pair(1, T, ldT, 0, at(L.T), M, S, ldS, 0, at(L.S), N, KW, 1, basis, s,
+                               p.scheme),
+            "serial expand");
     const int64_t cT = (M / 2) * (KW / 2), cS = (N / 2) * (KW / 2), cQ = (M / 2) * (NW / 2);
     for (int h = 0; h < 7; ++h)
       BMM_TRY(solve(level + 1, at(L.T) + h * cT, KW / 2, at(L.S) + h * cS, KW / 2,
                     at(L.Q) + h * cQ, NW / 2, 0));
-    HIP_TRY(launch_compress(at(L.Q), Q, ldQ, 0, M, NW, 1, s, acc, p.scheme), "serial compress");
+    HIP_TRY(launch_compress(1, at(L.Q), Q, ldQ, 0, M, NW, 1, s, acc, basis, p.scheme),
+            "serial compress");
     return BMM_OK;
   }
 };
@@ -706,11 +706,16 @@ int bmm_gf2_strassen(const uint64_t* A, int64_t lda, const uint64_t* B, int64_t 
       overlaps(ew, b_t ? extent(B, n, ldb, P.kw) : extent(B, k, ldb, P.nw)))
     return fail(BMM_E_INVAL, "workspace overlaps an operand");
   char* ws = static_cast<char*>(workspace);
+  // The basis changes happen inside the expansions and compressions, which then read A (and
+  // B^T, if given) where it lies; the lean levels and the shifted leaf take operands that
+  // are in the alternative basis already.
+  const bool fused = !alt && !P.lean && !P.shift;
+  const bool stage_b = fused ? !b_t : st.b, stage_a = !fused && st.a;
   // B^T: staged in the workspace (transposed, or copied when it will be changed), or
   // read where it lies (alternative-basis input, or changed in place)
   uint64_t* BT = const_cast<uint64_t*>(B);
   int64_t ldbt = ldb;
-  if (st.b) {
+  if (stage_b) {
     BT = reinterpret_cast<uint64_t*>(ws + P.bhat);
     ldbt = P.kw;
     if (b_t)
@@ -720,32 +725,31 @@ int bmm_gf2_strassen(const uint64_t* A, int64_t lda, const uint64_t* B, int64_t 
   }
   uint64_t* Ah = const_cast<uint64_t*>(A);
   int64_t ldah = lda;
-  if (st.a) {
+  if (stage_a) {
     Ah = reinterpret_cast<uint64_t*>(ws + P.ahat);
     ldah = P.kw;
     HIP_TRY(launch_copy(A, lda, Ah, P.kw, m, P.kw, s), "copy A");
   }
-  if (!alt) {
+  const bool change = !alt && !fused;
+  if (change) {
     // forward changes (eq. mb-fwdbasisrecurrence / ab-fwdbasisrecurrence), in the
     // workspace copies or in the caller's A and B^T (BMM_FLAG_INPLACE_BASIS)
     HIP_TRY(launch_basis(Ah, ldah, 0, m, P.kw, 1, P.depth, 0, s, P.scheme, 0), "basis A");
     HIP_TRY(launch_basis(BT, ldbt, 0, n, P.kw, 1, P.depth, 0, s, P.scheme, 1), "basis B");
   }
-  const uint64_t* T0 = Ah;
-  const int64_t ldT0 = ldah;
   int leaf, tile;
   const int64_t u = (int64_t)1 << P.depth;
   int64_t leaves = 1;
   for (int i = 0; i < P.dp; ++i) leaves *= 7;
   pick_leaf(BMM_GF2, m / u, k / u, n / u, leaves, o, &leaf, &tile);
-  StrassenRun run{&P, ws, leaf, tile, s};
-  // C ^= chi(core) is computed as chi(chi^-1(C) ^ core): C is taken to the
-  // alternative basis and back (chi^-1 is chi itself for the self-inverse design
-  // and the forward change for the chaining one).
-  if (!alt && acc) HIP_TRY(to_alt_basis(C, ldc, m, P.nw, P.depth, P.scheme, s), "basis C");
-  BMM_TRY(run.solve(0, T0, ldT0, BT, ldbt, C, ldc, acc));
-  if (!alt) HIP_TRY(launch_basis(C, ldc, 0, m, P.nw, 1, P.depth, 1, s, P.scheme), "basis C");
-  if (inplace) {
+  StrassenRun run{&P, ws, leaf, tile, s, fused ? 1 : 0};
+  // C ^= chi(core) is computed as chi(chi^-1(C) ^ core) where chi is a pass of its own: C is
+  // taken to the alternative basis and back (chi^-1 is chi itself for the self-inverse
+  // design and the forward change for the chaining one).
+  if (change && acc) HIP_TRY(to_alt_basis(C, ldc, m, P.nw, P.depth, P.scheme, s), "basis C");
+  BMM_TRY(run.solve(0, Ah, ldah, BT, ldbt, C, ldc, acc));
+  if (change) HIP_TRY(launch_basis(C, ldc, 0, m, P.nw, 1, P.depth, 1, s, P.scheme), "basis C");
+  if (change && inplace) {
     // restore the caller's operands: the self-inverse change is an involution (its
     // forward change again), the chaining change is undone by its inverse (section 2.3)
     const int undo = P.scheme == BMM_SCHEME_CHAINING ? 1 : 0;
@@ -836,7 +840,7 @@ int strassen_alt(const uint64_t* Ahat, int64_t lda, const uint64_t* BThat, int64
   int64_t leaves = 1;
   for (int i = 0; i < P.dp; ++i) leaves *= 7;
   pick_leaf(BMM_GF2, m / u, k / u, n / u, leaves, o, &leaf, &tile);
-  StrassenRun run{&P, static_cast<char*>(ws), leaf, tile, s};
+  StrassenRun run{&P, static_cast<char*>(ws), leaf, tile, s, 0};
   return run.solve(0, Ahat, lda, BThat, ldbt, C, ldc, accumulate);
 }
 
@@ -886,10 +890,8 @@ int bmm_expand(int side, int levels, int scheme, const uint64_t* src, int64_t ld
   if (rows % u || words % u) return fail(BMM_E_UNSUPPORTED, "sizes must be divisible by %ld", (long)u);
   if (!src || !dst || ldp < words) return fail(BMM_E_INVAL, "null pointer or pitch too small");
   hipStream_t s = (hipStream_t)hip_stream;
-  return check_hip(levels == 2 ? launch_expand2(side, src, ldp, strideP, dst, rows, words,
-                                                parents, s, scheme)
-                               : launch_expand(side, src, ldp, strideP, dst, rows, words,
-                                               parents, s, scheme),
+  return check_hip(launch_expand(side, levels, src, ldp, strideP, dst, rows, words, parents, s,
+                                 scheme),
                    "expand");
 }
 
@@ -905,10 +907,8 @@ int bmm_compress(int levels, int scheme, const uint64_t* src, uint64_t* dst, int
   if (rows % u || words % u) return fail(BMM_E_UNSUPPORTED, "sizes must be divisible by %ld", (long)u);
   if (!src || !dst || ldp < words) return fail(BMM_E_INVAL, "null pointer or pitch too small");
   hipStream_t s = (hipStream_t)hip_stream;
-  return check_hip(levels == 2 ? launch_compress2(src, dst, ldp, strideP, rows, words, parents,
-                                                  s, 0, scheme)
-                               : launch_compress(src, dst, ldp, strideP, rows, words, parents,
-                                                 s, 0, scheme),
+  return check_hip(launch_compress(levels, src, dst, ldp, strideP, rows, words, parents, s, 0, 0,
+                                   scheme),
                    "compress");
 }
 

@@ -158,22 +158,24 @@ hipError_t launch_basis(uint64_t* X, int64_t ld, int64_t stride, int64_t rows,
 // matrix 7p + h of `dst`, each (rows/2) x (words/2) with pitch words/2.
 // side 0: left operand (alpha), 1: right operand stored transposed (beta with
 // the 01 and 10 quadrants swapped).
-hipError_t launch_expand(int side, const uint64_t* src, int64_t ldp, int64_t strideP,
+// levels = 2: two recursion levels at once (49 grandchildren per parent, index
+// 49p + 7h1 + h2).
+hipError_t launch_expand(int side, int levels, const uint64_t* src, int64_t ldp, int64_t strideP,
                          uint64_t* dst, int64_t rows, int64_t words, int64_t parents,
                          hipStream_t s, int scheme = 0);
-// Two recursion levels at once (49 grandchildren per parent, index 49p + 7h1 + h2).
-hipError_t launch_expand2(int side, const uint64_t* src, int64_t ldp, int64_t strideP,
-                          uint64_t* dst, int64_t rows, int64_t words, int64_t parents,
-                          hipStream_t s, int scheme = 0);
+// Both operands in one launch.  basis = 1: they are in the standard basis, and each level's
+// forward change is applied before it expands.
+hipError_t launch_expand_pair(int levels, const uint64_t* T, int64_t ldT, int64_t strideT,
+                              uint64_t* dstT, int64_t rowsT, const uint64_t* S, int64_t ldS,
+                              int64_t strideS, uint64_t* dstS, int64_t rowsS, int64_t words,
+                              int64_t parents, int basis, hipStream_t s, int scheme);
 // Inverse of the above for the products: 7 children (compact, (rows/2) x
 // (words/2)) of parent p combine by gamma into the parent's 4 quadrants
-// (accumulate = 1: XORed into the parent instead of overwriting it).
-hipError_t launch_compress(const uint64_t* src, uint64_t* dst, int64_t ldp, int64_t strideP,
-                           int64_t rows, int64_t words, int64_t parents, hipStream_t s,
-                           int accumulate = 0, int scheme = 0);
-hipError_t launch_compress2(const uint64_t* src, uint64_t* dst, int64_t ldp,
-                            int64_t strideP, int64_t rows, int64_t words, int64_t parents,
-                            hipStream_t s, int accumulate = 0, int scheme = 0);
+// (accumulate = 1: XORed into the parent instead of overwriting it; basis = 1: after each
+// level's inverse change).
+hipError_t launch_compress(int levels, const uint64_t* src, uint64_t* dst, int64_t ldp,
+                           int64_t strideP, int64_t rows, int64_t words, int64_t parents,
+                           hipStream_t s, int accumulate = 0, int basis = 0, int scheme = 0);
 
 // One child at a time (the lean depth-first levels): child h of a parent (rows x words,
 // pitch ldp) of side 0 (left) or 1 (right, stored transposed) into dst (pitch ldd); and

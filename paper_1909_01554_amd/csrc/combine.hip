@@ -12,8 +12,12 @@
 // moves it through registers: one level reads 4 words and writes 7 (expand)
 // or reads 7 and writes 4 (compress); the merged two-level kernels read 16 and
 // write 49, or read 49 and write 16, so the intermediate level never goes to
-// HBM (section 3.15, merging levels).  Children of parent p are matrices
+// HBM (section 3.15, merging levels).  With operands in the standard basis the levels'
+// basis changes are applied in the same registers, which saves their own passes over A, B
+// and C, and the copy of A they would change.  Children of parent p are matrices
 // 7p + h, grandchildren 49p + 7h1 + h2, stored compactly one after another.
+#include <type_traits>
+
 #include "bmm_internal.h"
 #include "scheme.h"
 
@@ -23,48 +27,56 @@ namespace {
 using scheme::compress_one;
 using scheme::expand_one;
 
-template <int SCH, int SIDE>
-__global__ __launch_bounds__(256) void expand_kernel(const uint64_t* __restrict__ src,
-                                                     int64_t ldp, int64_t strideP,
-                                                     uint64_t* __restrict__ dst, int64_t rows,
-                                                     int64_t words, int64_t parents) {
-  const int64_t hr = rows >> 1, hw = words >> 1;
-  const int64_t csize = hr * hw;
-  const int64_t total = csize * parents;
-  const int64_t gstride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gstride) {
-    const int64_t p = e / csize;
-    const int64_t q = e - p * csize;
-    const int64_t r = q / hw;
-    const int64_t w = q - r * hw;
-    const uint64_t* P = src + p * strideP;
-    const uint64_t q00 = P[r * ldp + w];
-    const uint64_t q01 = P[r * ldp + hw + w];
-    const uint64_t q10 = P[(r + hr) * ldp + w];
-    const uint64_t q11 = P[(r + hr) * ldp + hw + w];
+// Index of a word: 32 bits where every index of the launch fits (a 64-bit division is about
+// 100 instructions, as many as the rest of a thread's work).
+inline bool fits32(int64_t total) { return total < ((int64_t)1 << 31); }
+
+// One operand of an expansion: parents of rows x words at base + p * stride, pitch ld.
+struct Operand {
+  const uint64_t* src;
+  int64_t ld, stride;
+  uint64_t* dst;
+  int64_t rows;
+};
+
+// BASIS: the operand is in the standard basis, and each level's forward change is applied
+// to the quadrants before they expand (phi then alpha or beta, level by level, is the same
+// map as all levels of phi first: both are Kronecker products over the levels).
+template <int SCH, int SIDE, int BASIS>
+__device__ __forceinline__ void expand_level(uint64_t q00, uint64_t q01, uint64_t q10,
+                                             uint64_t q11, uint64_t (&o)[7]) {
+  if constexpr (BASIS) {
+    if constexpr (SIDE == 0) scheme::fwd<SCH>(q00, q01, q10, q11);
+    else scheme::fwd<SCH>(q00, q10, q01, q11);  // stored transposed
+  }
+  expand_one<SCH, SIDE>(q00, q01, q10, q11, o);
+}
+
+template <int SCH, int SIDE, int BASIS, class I>
+__device__ __forceinline__ void expand1(const Operand& a, int64_t words, int64_t parents) {
+  const I hr = (I)(a.rows >> 1), hw = (I)(words >> 1);
+  const I csize = hr * hw, total = csize * (I)parents;
+  const I gstride = (I)gridDim.x * blockDim.x;
+  for (I e = (I)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gstride) {
+    const I p = e / csize, q = e - p * csize, r = q / hw, w = q - r * hw;
+    const uint64_t* P = a.src + (int64_t)p * a.stride + (int64_t)r * a.ld + w;
+    const int64_t down = (int64_t)hr * a.ld;
     uint64_t o[7];
-    expand_one<SCH, SIDE>(q00, q01, q10, q11, o);
-    uint64_t* D = dst + 7 * p * csize + q;
+    expand_level<SCH, SIDE, BASIS>(P[0], P[hw], P[down], P[down + hw], o);
+    uint64_t* D = a.dst + 7 * (int64_t)p * csize + q;
 #pragma unroll
-    for (int h = 0; h < 7; ++h) D[h * csize] = o[h];
+    for (int h = 0; h < 7; ++h) D[h * (int64_t)csize] = o[h];
   }
 }
 
-template <int SCH, int SIDE>
-__global__ __launch_bounds__(256) void expand2_kernel(const uint64_t* __restrict__ src,
-                                                      int64_t ldp, int64_t strideP,
-                                                      uint64_t* __restrict__ dst, int64_t rows,
-                                                      int64_t words, int64_t parents) {
-  const int64_t qr = rows >> 2, qw = words >> 2;
-  const int64_t gsize = qr * qw;
-  const int64_t total = gsize * parents;
-  const int64_t gstride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gstride) {
-    const int64_t p = e / gsize;
-    const int64_t q = e - p * gsize;
-    const int64_t r = q / qw;
-    const int64_t w = q - r * qw;
-    const uint64_t* P = src + p * strideP + r * ldp + w;
+template <int SCH, int SIDE, int BASIS, class I>
+__device__ __forceinline__ void expand2(const Operand& a, int64_t words, int64_t parents) {
+  const I qr = (I)(a.rows >> 2), qw = (I)(words >> 2);
+  const I gsize = qr * qw, total = gsize * (I)parents;
+  const I gstride = (I)gridDim.x * blockDim.x;
+  for (I e = (I)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gstride) {
+    const I p = e / gsize, q = e - p * gsize, r = q / qw, w = q - r * qw;
+    const uint64_t* P = a.src + (int64_t)p * a.stride + (int64_t)r * a.ld + w;
     // x[i1][j1][i2][j2] at row i1*2qr + i2*qr + r, word j1*2qw + j2*qw + w
     uint64_t x[2][2][2][2];
 #pragma unroll
@@ -75,7 +87,7 @@ __global__ __launch_bounds__(256) void expand2_kernel(const uint64_t* __restrict
         for (int i2 = 0; i2 < 2; ++i2)
 #pragma unroll
           for (int j2 = 0; j2 < 2; ++j2)
-            x[i1][j1][i2][j2] = P[(i1 * 2 * qr + i2 * qr) * ldp + j1 * 2 * qw + j2 * qw];
+            x[i1][j1][i2][j2] = P[(2 * i1 + i2) * (int64_t)qr * a.ld + (2 * j1 + j2) * (int64_t)qw];
     // first level: for each inner quadrant (i2, j2), expand over (i1, j1)
     uint64_t t[7][2][2];
 #pragma unroll
@@ -83,18 +95,33 @@ __global__ __launch_bounds__(256) void expand2_kernel(const uint64_t* __restrict
 #pragma unroll
       for (int j2 = 0; j2 < 2; ++j2) {
         uint64_t o[7];
-        expand_one<SCH, SIDE>(x[0][0][i2][j2], x[0][1][i2][j2], x[1][0][i2][j2], x[1][1][i2][j2], o);
+        expand_level<SCH, SIDE, BASIS>(x[0][0][i2][j2], x[0][1][i2][j2], x[1][0][i2][j2],
+                                       x[1][1][i2][j2], o);
 #pragma unroll
         for (int h = 0; h < 7; ++h) t[h][i2][j2] = o[h];
       }
-    uint64_t* D = dst + 49 * p * gsize + q;
+    uint64_t* D = a.dst + 49 * (int64_t)p * gsize + q;
 #pragma unroll
     for (int h1 = 0; h1 < 7; ++h1) {
       uint64_t o[7];
-      expand_one<SCH, SIDE>(t[h1][0][0], t[h1][0][1], t[h1][1][0], t[h1][1][1], o);
+      expand_level<SCH, SIDE, BASIS>(t[h1][0][0], t[h1][0][1], t[h1][1][0], t[h1][1][1], o);
 #pragma unroll
-      for (int h2 = 0; h2 < 7; ++h2) D[(7 * h1 + h2) * gsize] = o[h2];
+      for (int h2 = 0; h2 < 7; ++h2) D[(7 * h1 + h2) * (int64_t)gsize] = o[h2];
     }
+  }
+}
+
+// Both operands in one launch: the left one in grid row 0, the right one in row 1 (a null
+// operand has no rows).
+template <int SCH, int LEVELS, int BASIS, class I>
+__global__ __launch_bounds__(256) void expand_kernel(Operand left, Operand right, int64_t words,
+                                                     int64_t parents) {
+  if (blockIdx.y == 0) {
+    if constexpr (LEVELS == 2) expand2<SCH, 0, BASIS, I>(left, words, parents);
+    else expand1<SCH, 0, BASIS, I>(left, words, parents);
+  } else {
+    if constexpr (LEVELS == 2) expand2<SCH, 1, BASIS, I>(right, words, parents);
+    else expand1<SCH, 1, BASIS, I>(right, words, parents);
   }
 }
 
@@ -106,60 +133,61 @@ __device__ __forceinline__ void put(uint64_t& d, uint64_t v) {
     d = v;
 }
 
+// Seven products into four quadrants; BASIS: and this level's inverse change after it.
+template <int SCH, int BASIS>
+__device__ __forceinline__ void compress_level(const uint64_t (&v)[7], uint64_t& c00, uint64_t& c01,
+                                               uint64_t& c10, uint64_t& c11) {
+  compress_one<SCH>(v, c00, c01, c10, c11);
+  if constexpr (BASIS) scheme::inv<SCH>(c00, c01, c10, c11);
+}
+
 // ACC = 1: the parent quadrants are XORed into dst instead of overwriting it.
-template <int SCH, int ACC>
+template <int SCH, int ACC, int BASIS, class I>
 __global__ __launch_bounds__(256) void compress_kernel(const uint64_t* __restrict__ src,
                                                        uint64_t* __restrict__ dst, int64_t ldp,
                                                        int64_t strideP, int64_t rows,
                                                        int64_t words, int64_t parents) {
-  const int64_t hr = rows >> 1, hw = words >> 1;
-  const int64_t csize = hr * hw;
-  const int64_t total = csize * parents;
-  const int64_t gstride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gstride) {
-    const int64_t p = e / csize;
-    const int64_t q = e - p * csize;
-    const int64_t r = q / hw;
-    const int64_t w = q - r * hw;
-    const uint64_t* S = src + 7 * p * csize + q;
+  const I hr = (I)(rows >> 1), hw = (I)(words >> 1);
+  const I csize = hr * hw, total = csize * (I)parents;
+  const I gstride = (I)gridDim.x * blockDim.x;
+  for (I e = (I)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gstride) {
+    const I p = e / csize, q = e - p * csize, r = q / hw, w = q - r * hw;
+    const uint64_t* S = src + 7 * (int64_t)p * csize + q;
     uint64_t v[7];
 #pragma unroll
-    for (int h = 0; h < 7; ++h) v[h] = S[h * csize];
+    for (int h = 0; h < 7; ++h) v[h] = S[h * (int64_t)csize];
     uint64_t c00, c01, c10, c11;
-    compress_one<SCH>(v, c00, c01, c10, c11);
-    uint64_t* P = dst + p * strideP;
-    put<ACC>(P[r * ldp + w], c00);
-    put<ACC>(P[r * ldp + hw + w], c01);
-    put<ACC>(P[(r + hr) * ldp + w], c10);
-    put<ACC>(P[(r + hr) * ldp + hw + w], c11);
+    compress_level<SCH, BASIS>(v, c00, c01, c10, c11);
+    uint64_t* P = dst + (int64_t)p * strideP + (int64_t)r * ldp + w;
+    const int64_t down = (int64_t)hr * ldp;
+    put<ACC>(P[0], c00);
+    put<ACC>(P[hw], c01);
+    put<ACC>(P[down], c10);
+    put<ACC>(P[down + hw], c11);
   }
 }
 
-template <int SCH, int ACC>
+template <int SCH, int ACC, int BASIS, class I>
 __global__ __launch_bounds__(256) void compress2_kernel(const uint64_t* __restrict__ src,
                                                         uint64_t* __restrict__ dst, int64_t ldp,
                                                         int64_t strideP, int64_t rows,
                                                         int64_t words, int64_t parents) {
-  const int64_t qr = rows >> 2, qw = words >> 2;
-  const int64_t gsize = qr * qw;
-  const int64_t total = gsize * parents;
-  const int64_t gstride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gstride) {
-    const int64_t p = e / gsize;
-    const int64_t q = e - p * gsize;
-    const int64_t r = q / qw;
-    const int64_t w = q - r * qw;
-    const uint64_t* S = src + 49 * p * gsize + q;
+  const I qr = (I)(rows >> 2), qw = (I)(words >> 2);
+  const I gsize = qr * qw, total = gsize * (I)parents;
+  const I gstride = (I)gridDim.x * blockDim.x;
+  for (I e = (I)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gstride) {
+    const I p = e / gsize, q = e - p * gsize, r = q / qw, w = q - r * qw;
+    const uint64_t* S = src + 49 * (int64_t)p * gsize + q;
     // inner level: for each h1, combine the seven h2 products into quadrants (i2, k2)
     uint64_t c[7][2][2];
 #pragma unroll
     for (int h1 = 0; h1 < 7; ++h1) {
       uint64_t v[7];
 #pragma unroll
-      for (int h2 = 0; h2 < 7; ++h2) v[h2] = S[(7 * h1 + h2) * gsize];
-      compress_one<SCH>(v, c[h1][0][0], c[h1][0][1], c[h1][1][0], c[h1][1][1]);
+      for (int h2 = 0; h2 < 7; ++h2) v[h2] = S[(7 * h1 + h2) * (int64_t)gsize];
+      compress_level<SCH, BASIS>(v, c[h1][0][0], c[h1][0][1], c[h1][1][0], c[h1][1][1]);
     }
-    uint64_t* P = dst + p * strideP + r * ldp + w;
+    uint64_t* P = dst + (int64_t)p * strideP + (int64_t)r * ldp + w;
 #pragma unroll
     for (int i2 = 0; i2 < 2; ++i2)
 #pragma unroll
@@ -168,12 +196,12 @@ __global__ __launch_bounds__(256) void compress2_kernel(const uint64_t* __restri
 #pragma unroll
         for (int h1 = 0; h1 < 7; ++h1) v[h1] = c[h1][i2][k2];
         uint64_t c00, c01, c10, c11;
-        compress_one<SCH>(v, c00, c01, c10, c11);
-        const int64_t off = i2 * qr * ldp + k2 * qw;
+        compress_level<SCH, BASIS>(v, c00, c01, c10, c11);
+        const int64_t off = i2 * (int64_t)qr * ldp + k2 * (int64_t)qw;
         put<ACC>(P[off], c00);
-        put<ACC>(P[off + 2 * qw], c01);
-        put<ACC>(P[off + 2 * qr * ldp], c10);
-        put<ACC>(P[off + 2 * qr * ldp + 2 * qw], c11);
+        put<ACC>(P[off + 2 * (int64_t)qw], c01);
+        put<ACC>(P[off + 2 * (int64_t)qr * ldp], c10);
+        put<ACC>(P[off + 2 * (int64_t)qr * ldp + 2 * (int64_t)qw], c11);
       }
   }
 }
@@ -279,87 +307,100 @@ inline unsigned grid_for(int64_t total) {
   return (unsigned)blocks;
 }
 
+template <int SCH, int BASIS, class I>
+void launch_expand_t(int levels, const Operand& l, const Operand& r, int64_t words,
+                     int64_t parents, dim3 g, hipStream_t s) {
+  if (levels == 2)
+    hipLaunchKernelGGL((expand_kernel<SCH, 2, BASIS, I>), g, dim3(256), 0, s, l, r, words, parents);
+  else
+    hipLaunchKernelGGL((expand_kernel<SCH, 1, BASIS, I>), g, dim3(256), 0, s, l, r, words, parents);
+}
+
 template <int SCH>
-hipError_t expand_sch(int side, int levels, const uint64_t* src, int64_t ldp, int64_t strideP,
-                      uint64_t* dst, int64_t rows, int64_t words, int64_t parents,
-                      hipStream_t s) {
+hipError_t expand_sch(int levels, const Operand& l, const Operand& r, int64_t words,
+                      int64_t parents, int basis, hipStream_t s) {
   const int sh = levels == 2 ? 2 : 1;
+  const int64_t rows = l.rows > r.rows ? l.rows : r.rows;
   const int64_t total = (rows >> sh) * (words >> sh) * parents;
   if (total <= 0) return hipSuccess;
-  const dim3 g(grid_for(total)), b(256);
-  if (levels == 2) {
-    if (side == 0)
-      hipLaunchKernelGGL((expand2_kernel<SCH, 0>), g, b, 0, s, src, ldp, strideP, dst, rows,
-                         words, parents);
-    else
-      hipLaunchKernelGGL((expand2_kernel<SCH, 1>), g, b, 0, s, src, ldp, strideP, dst, rows,
-                         words, parents);
-  } else {
-    if (side == 0)
-      hipLaunchKernelGGL((expand_kernel<SCH, 0>), g, b, 0, s, src, ldp, strideP, dst, rows,
-                         words, parents);
-    else
-      hipLaunchKernelGGL((expand_kernel<SCH, 1>), g, b, 0, s, src, ldp, strideP, dst, rows,
-                         words, parents);
-  }
+  const dim3 g(grid_for(total), r.rows > 0 ? 2 : 1);
+  const bool narrow = fits32(total);
+  if (basis) narrow ? launch_expand_t<SCH, 1, uint32_t>(levels, l, r, words, parents, g, s)
+                    : launch_expand_t<SCH, 1, int64_t>(levels, l, r, words, parents, g, s);
+  else narrow ? launch_expand_t<SCH, 0, uint32_t>(levels, l, r, words, parents, g, s)
+              : launch_expand_t<SCH, 0, int64_t>(levels, l, r, words, parents, g, s);
   return hipGetLastError();
+}
+
+template <int SCH, int ACC, int BASIS, class I>
+void launch_compress_t(int levels, const uint64_t* src, uint64_t* dst, int64_t ldp,
+                       int64_t strideP, int64_t rows, int64_t words, int64_t parents, dim3 g,
+                       hipStream_t s) {
+  if (levels == 2)
+    hipLaunchKernelGGL((compress2_kernel<SCH, ACC, BASIS, I>), g, dim3(256), 0, s, src, dst, ldp,
+                       strideP, rows, words, parents);
+  else
+    hipLaunchKernelGGL((compress_kernel<SCH, ACC, BASIS, I>), g, dim3(256), 0, s, src, dst, ldp,
+                       strideP, rows, words, parents);
+}
+
+template <int SCH, int ACC, int BASIS>
+void launch_compress_i(int levels, const uint64_t* src, uint64_t* dst, int64_t ldp,
+                       int64_t strideP, int64_t rows, int64_t words, int64_t parents, dim3 g,
+                       bool narrow, hipStream_t s) {
+  if (narrow)
+    launch_compress_t<SCH, ACC, BASIS, uint32_t>(levels, src, dst, ldp, strideP, rows, words,
+                                                 parents, g, s);
+  else
+    launch_compress_t<SCH, ACC, BASIS, int64_t>(levels, src, dst, ldp, strideP, rows, words,
+                                                parents, g, s);
 }
 
 template <int SCH>
 hipError_t compress_sch(int levels, const uint64_t* src, uint64_t* dst, int64_t ldp,
                         int64_t strideP, int64_t rows, int64_t words, int64_t parents,
-                        hipStream_t s, int accumulate) {
+                        hipStream_t s, int accumulate, int basis) {
   const int sh = levels == 2 ? 2 : 1;
   const int64_t total = (rows >> sh) * (words >> sh) * parents;
   if (total <= 0) return hipSuccess;
-  const dim3 g(grid_for(total)), b(256);
-  if (levels == 2) {
-    if (accumulate)
-      hipLaunchKernelGGL((compress2_kernel<SCH, 1>), g, b, 0, s, src, dst, ldp, strideP, rows,
-                         words, parents);
-    else
-      hipLaunchKernelGGL((compress2_kernel<SCH, 0>), g, b, 0, s, src, dst, ldp, strideP, rows,
-                         words, parents);
-  } else {
-    if (accumulate)
-      hipLaunchKernelGGL((compress_kernel<SCH, 1>), g, b, 0, s, src, dst, ldp, strideP, rows,
-                         words, parents);
-    else
-      hipLaunchKernelGGL((compress_kernel<SCH, 0>), g, b, 0, s, src, dst, ldp, strideP, rows,
-                         words, parents);
-  }
+  const dim3 g(grid_for(total));
+  const bool narrow = fits32(total);
+  auto go = [&](auto acc, auto bas) {
+    launch_compress_i<SCH, decltype(acc)::value, decltype(bas)::value>(
+        levels, src, dst, ldp, strideP, rows, words, parents, g, narrow, s);
+  };
+  const std::integral_constant<int, 0> no;
+  const std::integral_constant<int, 1> yes;
+  if (accumulate) basis ? go(yes, yes) : go(yes, no);
+  else basis ? go(no, yes) : go(no, no);
   return hipGetLastError();
 }
 
-hipError_t expand_any(int scheme, int side, int levels, const uint64_t* src, int64_t ldp,
-                      int64_t strideP, uint64_t* dst, int64_t rows, int64_t words,
-                      int64_t parents, hipStream_t s) {
+hipError_t expand_any(int scheme, int levels, const Operand& l, const Operand& r, int64_t words,
+                      int64_t parents, int basis, hipStream_t s) {
   switch (scheme) {
     case BMM_SCHEME_CHAINING:
-      return expand_sch<BMM_SCHEME_CHAINING>(side, levels, src, ldp, strideP, dst, rows, words,
-                                             parents, s);
-    case BMM_SCHEME_WINOGRAD:
-      return expand_sch<BMM_SCHEME_WINOGRAD>(side, levels, src, ldp, strideP, dst, rows, words,
-                                             parents, s);
+      return expand_sch<BMM_SCHEME_CHAINING>(levels, l, r, words, parents, basis, s);
+    case BMM_SCHEME_WINOGRAD:  // no basis change
+      return expand_sch<BMM_SCHEME_WINOGRAD>(levels, l, r, words, parents, 0, s);
     default:
-      return expand_sch<BMM_SCHEME_SELF_INVERSE>(side, levels, src, ldp, strideP, dst, rows,
-                                                 words, parents, s);
+      return expand_sch<BMM_SCHEME_SELF_INVERSE>(levels, l, r, words, parents, basis, s);
   }
 }
 
 hipError_t compress_any(int scheme, int levels, const uint64_t* src, uint64_t* dst, int64_t ldp,
                         int64_t strideP, int64_t rows, int64_t words, int64_t parents,
-                        hipStream_t s, int accumulate) {
+                        hipStream_t s, int accumulate, int basis) {
   switch (scheme) {
     case BMM_SCHEME_CHAINING:
       return compress_sch<BMM_SCHEME_CHAINING>(levels, src, dst, ldp, strideP, rows, words,
-                                               parents, s, accumulate);
+                                               parents, s, accumulate, basis);
     case BMM_SCHEME_WINOGRAD:
       return compress_sch<BMM_SCHEME_WINOGRAD>(levels, src, dst, ldp, strideP, rows, words,
-                                               parents, s, accumulate);
+                                               parents, s, accumulate, 0);
     default:
       return compress_sch<BMM_SCHEME_SELF_INVERSE>(levels, src, dst, ldp, strideP, rows, words,
-                                                   parents, s, accumulate);
+                                                   parents, s, accumulate, basis);
   }
 }
 
@@ -423,28 +464,27 @@ hipError_t launch_gamma(int scheme, int h, const uint64_t* src, int64_t lds, uin
   return hipGetLastError();
 }
 
-hipError_t launch_expand(int side, const uint64_t* src, int64_t ldp, int64_t strideP,
+hipError_t launch_expand(int side, int levels, const uint64_t* src, int64_t ldp, int64_t strideP,
                          uint64_t* dst, int64_t rows, int64_t words, int64_t parents,
                          hipStream_t s, int scheme) {
-  return expand_any(scheme, side, 1, src, ldp, strideP, dst, rows, words, parents, s);
+  const Operand x{src, ldp, strideP, dst, rows}, none{nullptr, 0, 0, nullptr, 0};
+  return side == 0 ? expand_any(scheme, levels, x, none, words, parents, 0, s)
+                   : expand_any(scheme, levels, none, x, words, parents, 0, s);
 }
 
-hipError_t launch_expand2(int side, const uint64_t* src, int64_t ldp, int64_t strideP,
-                          uint64_t* dst, int64_t rows, int64_t words, int64_t parents,
-                          hipStream_t s, int scheme) {
-  return expand_any(scheme, side, 2, src, ldp, strideP, dst, rows, words, parents, s);
+hipError_t launch_expand_pair(int levels, const uint64_t* T, int64_t ldT, int64_t strideT,
+                              uint64_t* dstT, int64_t rowsT, const uint64_t* S, int64_t ldS,
+                              int64_t strideS, uint64_t* dstS, int64_t rowsS, int64_t words,
+                              int64_t parents, int basis, hipStream_t s, int scheme) {
+  return expand_any(scheme, levels, Operand{T, ldT, strideT, dstT, rowsT},
+                    Operand{S, ldS, strideS, dstS, rowsS}, words, parents, basis, s);
 }
 
-hipError_t launch_compress(const uint64_t* src, uint64_t* dst, int64_t ldp, int64_t strideP,
-                           int64_t rows, int64_t words, int64_t parents, hipStream_t s,
-                           int accumulate, int scheme) {
-  return compress_any(scheme, 1, src, dst, ldp, strideP, rows, words, parents, s, accumulate);
-}
-
-hipError_t launch_compress2(const uint64_t* src, uint64_t* dst, int64_t ldp, int64_t strideP,
-                            int64_t rows, int64_t words, int64_t parents, hipStream_t s,
-                            int accumulate, int scheme) {
-  return compress_any(scheme, 2, src, dst, ldp, strideP, rows, words, parents, s, accumulate);
+hipError_t launch_compress(int levels, const uint64_t* src, uint64_t* dst, int64_t ldp,
+                           int64_t strideP, int64_t rows, int64_t words, int64_t parents,
+                           hipStream_t s, int accumulate, int basis, int scheme) {
+  return compress_any(scheme, levels, src, dst, ldp, strideP, rows, words, parents, s, accumulate,
+                      basis);
 }
 
 hipError_t launch_copy(const uint64_t* src, int64_t lds, uint64_t* dst, int64_t ldd,
