@@ -829,9 +829,12 @@ int strassen_alt_plan(int64_t m, int64_t k, int64_t n, int depth, const bmm_opti
 
 int strassen_alt(const uint64_t* Ahat, int64_t lda, const uint64_t* BThat, int64_t ldbt,
                  uint64_t* C, int64_t ldc, int64_t m, int64_t k, int64_t n, int depth,
-                 void* ws, size_t bytes, const bmm_options& o, int accumulate, hipStream_t s) {
+                 void* ws, size_t bytes, const bmm_options& o, int accumulate, hipStream_t s,
+                 int standard) {
   StrassenPlan P;
   BMM_TRY(make_plan(m, k, n, depth, o, false, &P, false));
+  if (standard && (P.lean || P.shift))
+    return fail(BMM_E_INVAL, "lean levels and the shifted leaf take the alternative basis");
   if (bytes < P.bytes) return fail(BMM_E_WORKSPACE, "workspace of %zu bytes needed", P.bytes);
   if (m == 0 || n == 0 || (k == 0 && accumulate)) return BMM_OK;
   if (k == 0) return check_hip(launch_zero(C, ldc, m, P.nw, s), "zero");
@@ -840,7 +843,7 @@ int strassen_alt(const uint64_t* Ahat, int64_t lda, const uint64_t* BThat, int64
   int64_t leaves = 1;
   for (int i = 0; i < P.dp; ++i) leaves *= 7;
   pick_leaf(BMM_GF2, m / u, k / u, n / u, leaves, o, &leaf, &tile);
-  StrassenRun run{&P, static_cast<char*>(ws), leaf, tile, s, 0};
+  StrassenRun run{&P, static_cast<char*>(ws), leaf, tile, s, standard};
   return run.solve(0, Ahat, lda, BThat, ldbt, C, ldc, accumulate);
 }
 

@@ -287,11 +287,14 @@ hipError_t to_alt_basis(uint64_t* C, int64_t ldc, int64_t rows, int64_t words, i
 // given transposed), for callers that stage their own operands (the
 // out-of-core pipeline).  depth = -1 picks it as the public product does;
 // strassen_alt_plan reports the workspace and the depth chosen.  accumulate = 1
-// XORs the (alternative-basis) result into C.  Both return a bmm status.
+// XORs the (alternative-basis) result into C.  standard = 1: operands and result are in the
+// standard basis instead (not with lean levels or the shifted leaf).  Both return a bmm
+// status.
 int strassen_alt_plan(int64_t m, int64_t k, int64_t n, int depth, const bmm_options& o,
                       size_t* bytes, int* depth_out);
 int strassen_alt(const uint64_t* Ahat, int64_t lda, const uint64_t* BThat, int64_t ldbt,
                  uint64_t* C, int64_t ldc, int64_t m, int64_t k, int64_t n, int depth,
-                 void* ws, size_t bytes, const bmm_options& o, int accumulate, hipStream_t s);
+                 void* ws, size_t bytes, const bmm_options& o, int accumulate, hipStream_t s,
+                 int standard = 0);
 
 }  // namespace bmm

@@ -5,10 +5,9 @@
 // recursion (sections 3.7 and 3.12, Algorithm 3): for each of the 7^dh
 // sub-instances the GPU forms its two operands from uploaded standard-basis
 // blocks (the weights of alpha.phi and beta.phi, e.g. 14 blocks of A per level
-// for the self-inverse design), changes them to the device levels' basis,
-// runs the recursion's core, and XORs the product into its gamma targets in an
-// HBM copy of C-hat; one inverse basis change over all dh + d levels finishes
-// C before a single download.  This does (7/8)^dh of the block-order work.
+// for the self-inverse design), runs the recursion's core, and XORs the product into the blocks of C that chi.gamma
+// sends it to; a block goes down once its last product is in.  This does (7/8)^dh of the
+// block-order work.
 // Other shapes, and GF(2) with BMM_FLAG_OOC_BLOCK_ORDER, use the block order:
 //
 // A, B and C live in page-locked host memory.  C is cut into b x b blocks;
@@ -135,7 +134,8 @@ struct Resources {
 // Coefficient masks of one host level of a scheme: a[h] and b[h] over the
 // standard quadrants (bit q, order 00 01 10 11) of A and B for operand h, and
 // g[q] over the seven products for result quadrant q, from the scheme's own
-// programs run on masks.
+// programs run on masks; gamma with the level's inverse basis change after it, so a result
+// block is final once its last product is in.
 struct LevelMasks {
   uint32_t a[7], b[7], g[4];
 };
@@ -156,6 +156,7 @@ LevelMasks level_masks() {
   for (int h = 0; h < 7; ++h) q[h] = 1ull << h;
   uint64_t c[4];
   scheme::compress_one<SCH>(q, c[0], c[1], c[2], c[3]);
+  scheme::inv<SCH>(c[0], c[1], c[2], c[3]);
   for (int i = 0; i < 4; ++i) L.g[i] = (uint32_t)c[i];
   return L;
 }
@@ -179,15 +180,25 @@ inline int digit_at(int64_t h, int dh, int l) {
 }
 
 struct HostRes {
-  hipStream_t copy = nullptr, comb = nullptr, comp = nullptr;
+  hipStream_t copy = nullptr, comb = nullptr, comp = nullptr, down = nullptr;
   hipEvent_t loaded[2] = {}, freed[2] = {}, ready[2] = {}, done[2] = {};
+  std::vector<hipEvent_t> events;  // of resident blocks and finished result blocks
   uint64_t *stage[2] = {}, *T[2] = {}, *ST[2] = {}, *btmp = nullptr, *Q = nullptr,
-           *Chat = nullptr;
+           *Cres = nullptr, *Ares = nullptr, *Bres = nullptr;
   void* ws = nullptr;
 
+  int event(hipEvent_t* e) {
+    *e = nullptr;
+    if (hipEventCreateWithFlags(e, hipEventDisableTiming) != hipSuccess)
+      return ofail(BMM_E_DEVICE, "event: %s", hipGetErrorString(hipGetLastError()));
+    events.push_back(*e);
+    return BMM_OK;
+  }
+
   ~HostRes() {
-    for (hipStream_t st : {copy, comb, comp})
+    for (hipStream_t st : {copy, comb, comp, down})
       if (st) (void)hipStreamSynchronize(st);
+    for (hipEvent_t e : events) (void)hipEventDestroy(e);
     for (int i = 0; i < 2; ++i) {
       for (hipEvent_t e : {loaded[i], freed[i], ready[i], done[i]})
         if (e) (void)hipEventDestroy(e);
@@ -197,15 +208,31 @@ struct HostRes {
     }
     (void)hipFree(btmp);
     (void)hipFree(Q);
-    (void)hipFree(Chat);
+    (void)hipFree(Cres);
+    (void)hipFree(Ares);
+    (void)hipFree(Bres);
     (void)hipFree(ws);
-    for (hipStream_t st : {copy, comb, comp})
+    for (hipStream_t st : {copy, comb, comp, down})
       if (st) (void)hipStreamDestroy(st);
   }
 };
 
+// Order of the seven products of a level: the first ones take few blocks (products start
+// while the rest is uploaded) and the last ones finish a result block each, which then goes
+// down while the next product runs.
+const int* product_order(int scheme) {
+  static const int self_inverse[7] = {0, 1, 2, 3, 6, 5, 4}, plain[7] = {0, 1, 2, 3, 4, 5, 6};
+  return scheme == BMM_SCHEME_SELF_INVERSE ? self_inverse : plain;
+}
+
 // The host-level recursion; returns 1 (nothing done) when the shape or the free
 // HBM does not admit it, else a bmm status.
+//
+// Where A and B fit in HBM beside the rest, each of their blocks is uploaded once, in the
+// order in which the products need them, and stays (PCIe carries 2 n^2 / 8 bytes up instead
+// of 28 blocks per four): at n = 32768 with 16384-bit blocks 25.2 -> 13.8 ms, of which the
+// copies take 4.9 ms up and 2.5 ms down.  Otherwise every product's blocks come through two
+// staging slots.
 int ooc_host_levels(const uint64_t* A, int64_t lda, const uint64_t* B, int64_t ldb,
                     uint64_t* C, int64_t ldc, int64_t n, int64_t b, const bmm_options& o,
                     int leaf, CopyLog& log) {
@@ -217,12 +244,13 @@ int ooc_host_levels(const uint64_t* A, int64_t lda, const uint64_t* B, int64_t l
   po.depth_serial = po.depth_parallel = -1;
   po.leaf = leaf;
   po.flags = 0;
+  po.shift = 0;  // the shifted leaf takes operands already in the alternative basis
   size_t ws_bytes = 0;
   int d = 0;
   if (strassen_alt_plan(b, b, b, -1, po, &ws_bytes, &d) != BMM_OK) return 1;
   const int64_t bw = b / 64, nw = n / 64;
-  const size_t blk = (size_t)b * bw * 8;
-  const size_t need = 8 * blk + (size_t)n * nw * 8 + ws_bytes;
+  const size_t blk = (size_t)b * bw * 8, full = (size_t)n * nw * 8;
+  const size_t need = 8 * blk + full + ws_bytes;
   size_t free_b = 0, total_b = 0;
   if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
     (void)hipGetLastError();
@@ -244,85 +272,152 @@ int ooc_host_levels(const uint64_t* A, int64_t lda, const uint64_t* B, int64_t l
       if (!((L.g[quad_at(r, c, dh, l)] >> digit_at(h, dh, l)) & 1)) return false;
     return true;
   };
+  std::vector<int64_t> order(H), last(g * g, -1);
+  for (int64_t i = 0; i < H; ++i) {
+    int64_t h = 0;
+    for (int l = 0; l < dh; ++l) h = 7 * h + product_order(o.scheme)[digit_at(i, dh, l)];
+    order[i] = h;
+    for (int64_t q = 0; q < g * g; ++q)
+      if (coef_c(h, q / g, q % g)) last[q] = i;
+  }
 
   HostRes R;
-  for (hipStream_t* st : {&R.copy, &R.comb, &R.comp})
-    OOC_TRY(hip_ok(hipStreamCreateWithFlags(st, hipStreamNonBlocking), "stream"));
+  bool resident = need + 2 * full + ((size_t)1 << 30) <= free_b;
+  if (resident && (bmm::dev_malloc((void**)&R.Ares, full) != hipSuccess ||
+                   bmm::dev_malloc((void**)&R.Bres, full) != hipSuccess)) {
+    (void)hipGetLastError();
+    (void)hipFree(R.Ares);
+    R.Ares = nullptr;
+    resident = false;
+  }
+  // With resident blocks an operand is a few XORs, which go on the product's own stream: of
+  // more than four streams in the process (the caller's among them) two would share a
+  // hardware queue, and uploads waited there behind a download that waited for its product.
+  for (hipStream_t* st : {&R.copy, &R.comp, &R.down, &R.comb})
+    if (!resident || st != &R.comb)
+      OOC_TRY(hip_ok(hipStreamCreateWithFlags(st, hipStreamNonBlocking), "stream"));
+  const hipStream_t comb = resident ? R.comp : R.comb;
+  const int sets = resident ? 1 : 2;
   for (int i = 0; i < 2; ++i) {
     for (hipEvent_t* e : {&R.loaded[i], &R.freed[i], &R.ready[i], &R.done[i]})
       OOC_TRY(hip_ok(hipEventCreateWithFlags(e, hipEventDisableTiming), "event"));
-    if (bmm::dev_malloc((void**)&R.stage[i], blk) != hipSuccess ||
-        bmm::dev_malloc((void**)&R.T[i], blk) != hipSuccess ||
-        bmm::dev_malloc((void**)&R.ST[i], blk) != hipSuccess) {
+    if (i < sets && (bmm::dev_malloc((void**)&R.stage[i], blk) != hipSuccess ||
+                     bmm::dev_malloc((void**)&R.T[i], blk) != hipSuccess ||
+                     bmm::dev_malloc((void**)&R.ST[i], blk) != hipSuccess)) {
       (void)hipGetLastError();
       return ofail(BMM_E_NOMEM, "out-of-core host-level buffers");
     }
   }
-  if (bmm::dev_malloc((void**)&R.btmp, blk) != hipSuccess || bmm::dev_malloc((void**)&R.Q, blk) != hipSuccess ||
-      bmm::dev_malloc((void**)&R.Chat, (size_t)n * nw * 8) != hipSuccess ||
+  if ((!resident && bmm::dev_malloc((void**)&R.btmp, blk) != hipSuccess) ||
+      bmm::dev_malloc((void**)&R.Q, blk) != hipSuccess ||
+      bmm::dev_malloc((void**)&R.Cres, full) != hipSuccess ||
       (ws_bytes && bmm::dev_malloc(&R.ws, ws_bytes) != hipSuccess)) {
     (void)hipGetLastError();
     return ofail(BMM_E_NOMEM, "out-of-core host-level buffers");
   }
-  OOC_TRY(hip_ok(launch_zero(R.Chat, nw, n, nw, R.comp), "zero C"));
 
-  int64_t up = 0;  // blocks uploaded so far (staging slot up % 2)
-  for (int64_t h = 0; h < H; ++h) {
-    const int t = (int)(h & 1);
-    if (h >= 2) OOC_TRY(hip_ok(hipStreamWaitEvent(R.comb, R.done[t], 0), "wait"));
+  auto upload = [&](uint64_t* dst, int side, int64_t r, int64_t c) {
+    const uint64_t* src = side == 0 ? A + r * b * lda + c * bw : B + r * b * ldb + c * bw;
+    OOC_TRY(log.begin(R.copy));
+    OOC_TRY(hip_ok(hipMemcpy2DAsync(dst, bw * 8, src, (side == 0 ? lda : ldb) * 8, bw * 8, b,
+                                    hipMemcpyHostToDevice, R.copy),
+                   "H2D block"));
+    return log.end(R.copy, (double)blk, 0);
+  };
+  // Resident block q of a side (B's transposed), uploaded on first use; the product waits.
+  std::vector<hipEvent_t> up_event[2] = {std::vector<hipEvent_t>(g * g, nullptr),
+                                         std::vector<hipEvent_t>(g * g, nullptr)};
+  auto block = [&](int side, int64_t q) { return (side == 0 ? R.Ares : R.Bres) + q * b * bw; };
+  auto resident_block = [&](int side, int64_t q) {
+    if (!up_event[side][q]) {
+      OOC_TRY(R.event(&up_event[side][q]));
+      if (side == 0) {
+        OOC_TRY(upload(block(0, q), 0, q / g, q % g));
+      } else {  // (the copy stream transposes it, so the one staging slot is free again)
+        OOC_TRY(upload(R.stage[0], 1, q / g, q % g));
+        OOC_TRY(hip_ok(launch_transpose(R.stage[0], bw, 0, block(1, q), bw, 0, b, b, 1, R.copy),
+                       "transpose"));
+      }
+      OOC_TRY(hip_ok(hipEventRecord(up_event[side][q], R.copy), "record"));
+    }
+    return hip_ok(hipStreamWaitEvent(comb, up_event[side][q], 0), "wait");
+  };
+
+  int64_t up = 0;  // blocks staged so far (slot up % 2)
+  std::vector<char> begun(g * g, 0);
+  for (int64_t i = 0; i < H; ++i) {
+    const int64_t h = order[i];
+    const int t = resident ? 0 : (int)(i & 1);
+    if (i >= 2 && !resident)
+      OOC_TRY(hip_ok(hipStreamWaitEvent(comb, R.done[t], 0), "wait"));
+    const uint64_t* operand[2];
     for (int side = 0; side < 2; ++side) {
-      bool first = true;
-      for (int64_t r = 0; r < g; ++r)
-        for (int64_t c = 0; c < g; ++c) {
-          if (!coef(side == 0 ? L.a : L.b, h, r, c)) continue;
-          const int s = (int)(up & 1);
+      uint64_t* const acc = side == 0 ? R.T[t] : R.ST[t];
+      std::vector<int64_t> blocks;
+      for (int64_t q = 0; q < g * g; ++q)
+        if (coef(side == 0 ? L.a : L.b, h, q / g, q % g)) blocks.push_back(q);
+      operand[side] = acc;
+      if (blocks.empty()) OOC_TRY(hip_ok(launch_zero(acc, bw, b, bw, comb), "zero"));
+      for (size_t j = 0; j < blocks.size(); ++j) {
+        const int64_t q = blocks[j];
+        const uint64_t* add;
+        const int s = (int)(up & 1);
+        if (resident) {
+          OOC_TRY(resident_block(side, q));
+          add = block(side, q);
+          if (blocks.size() == 1) {  // the product reads it where it lies
+            operand[side] = add;
+            break;
+          }
+        } else {
           if (up >= 2) OOC_TRY(hip_ok(hipStreamWaitEvent(R.copy, R.freed[s], 0), "wait"));
-          const uint64_t* src = side == 0 ? A + r * b * lda + c * bw : B + r * b * ldb + c * bw;
-          const int64_t ld = side == 0 ? lda : ldb;
-          OOC_TRY(log.begin(R.copy));
-          OOC_TRY(hip_ok(hipMemcpy2DAsync(R.stage[s], bw * 8, src, ld * 8, bw * 8, b,
-                                          hipMemcpyHostToDevice, R.copy),
-                         "H2D block"));
-          OOC_TRY(log.end(R.copy, (double)blk, 0));
+          OOC_TRY(upload(R.stage[s], side, q / g, q % g));
           OOC_TRY(hip_ok(hipEventRecord(R.loaded[s], R.copy), "record"));
-          OOC_TRY(hip_ok(hipStreamWaitEvent(R.comb, R.loaded[s], 0), "wait"));
-          const uint64_t* add = R.stage[s];
-          uint64_t* acc = side == 0 ? R.T[t] : R.ST[t];
-          if (side == 1) {  // B block (J, K) -> its transpose, stored as block (K, J) of B^T
-            OOC_TRY(hip_ok(launch_transpose(R.stage[s], bw, 0, R.btmp, bw, 0, b, b, 1, R.comb),
+          OOC_TRY(hip_ok(hipStreamWaitEvent(comb, R.loaded[s], 0), "wait"));
+          add = R.stage[s];
+          if (side == 1) {
+            OOC_TRY(hip_ok(launch_transpose(R.stage[s], bw, 0, R.btmp, bw, 0, b, b, 1, comb),
                            "transpose"));
             add = R.btmp;
           }
-          OOC_TRY(hip_ok(first ? launch_copy(add, bw, acc, bw, b, bw, R.comb)
-                               : launch_xor(add, bw, acc, bw, b, bw, R.comb),
-                         "combine"));
-          OOC_TRY(hip_ok(hipEventRecord(R.freed[s], R.comb), "record"));
-          first = false;
+        }
+        OOC_TRY(hip_ok(j == 0 ? launch_copy(add, bw, acc, bw, b, bw, comb)
+                              : launch_xor(add, bw, acc, bw, b, bw, comb),
+                       "combine"));
+        if (!resident) {
+          OOC_TRY(hip_ok(hipEventRecord(R.freed[s], comb), "record"));
           ++up;
         }
-      if (first) OOC_TRY(hip_ok(launch_zero(side == 0 ? R.T[t] : R.ST[t], bw, b, bw, R.comb),
-                                "zero"));
+      }
     }
-    OOC_TRY(hip_ok(launch_basis(R.T[t], bw, 0, b, bw, 1, d, 0, R.comb, o.scheme, 0), "basis"));
-    OOC_TRY(hip_ok(launch_basis(R.ST[t], bw, 0, b, bw, 1, d, 0, R.comb, o.scheme, 1), "basis"));
-    OOC_TRY(hip_ok(hipEventRecord(R.ready[t], R.comb), "record"));
-    OOC_TRY(hip_ok(hipStreamWaitEvent(R.comp, R.ready[t], 0), "wait"));
-    OOC_TRY(strassen_alt(R.T[t], bw, R.ST[t], bw, R.Q, bw, b, b, b, d, R.ws, ws_bytes, po, 0,
-                         R.comp));
+    if (!resident) {
+      OOC_TRY(hip_ok(hipEventRecord(R.ready[t], comb), "record"));
+      OOC_TRY(hip_ok(hipStreamWaitEvent(R.comp, R.ready[t], 0), "wait"));
+    }
+    OOC_TRY(strassen_alt(operand[0], bw, operand[1], bw, R.Q, bw, b, b, b, d, R.ws, ws_bytes, po, 0,
+                         R.comp, 1));
     OOC_TRY(hip_ok(hipEventRecord(R.done[t], R.comp), "record"));
-    for (int64_t r = 0; r < g; ++r)
-      for (int64_t c = 0; c < g; ++c)
-        if (coef_c(h, r, c))
-          OOC_TRY(hip_ok(launch_xor(R.Q, bw, R.Chat + r * b * nw + c * bw, nw, b, bw, R.comp),
-                         "accumulate"));
+    for (int64_t q = 0; q < g * g; ++q) {
+      uint64_t* const dst = R.Cres + q * b * bw;
+      if (coef_c(h, q / g, q % g)) {
+        OOC_TRY(hip_ok(begun[q] ? launch_xor(R.Q, bw, dst, bw, b, bw, R.comp)
+                                : launch_copy(R.Q, bw, dst, bw, b, bw, R.comp),
+                       "accumulate"));
+        begun[q] = 1;
+      }
+      if (last[q] != i) continue;
+      hipEvent_t fin;
+      OOC_TRY(R.event(&fin));
+      OOC_TRY(hip_ok(hipEventRecord(fin, R.comp), "record"));
+      OOC_TRY(hip_ok(hipStreamWaitEvent(R.down, fin, 0), "wait"));
+      OOC_TRY(log.begin(R.down));
+      OOC_TRY(hip_ok(hipMemcpy2DAsync(C + (q / g) * b * ldc + (q % g) * bw, ldc * 8, dst, bw * 8,
+                                      bw * 8, b, hipMemcpyDeviceToHost, R.down),
+                     "D2H C"));
+      OOC_TRY(log.end(R.down, (double)blk, 1));
+    }
   }
-  OOC_TRY(hip_ok(launch_basis(R.Chat, nw, 0, n, nw, 1, dh + d, 1, R.comp, o.scheme, 0),
-                 "basis C"));
-  OOC_TRY(log.begin(R.comp));
-  OOC_TRY(hip_ok(hipMemcpy2DAsync(C, ldc * 8, R.Chat, nw * 8, nw * 8, n, hipMemcpyDeviceToHost,
-                                  R.comp),
-                 "D2H C"));
-  OOC_TRY(log.end(R.comp, (double)n * nw * 8, 1));
+  OOC_TRY(hip_ok(hipStreamSynchronize(R.down), "sync"));
   OOC_TRY(hip_ok(hipStreamSynchronize(R.comp), "sync"));
   OOC_TRY(hip_ok(hipStreamSynchronize(R.copy), "sync"));
   return BMM_OK;
