@@ -162,27 +162,46 @@ def _ptr(t):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
 
+# torch once it has been needed (the package itself imports without it)
+_torch = None
+
+
 def _stream(t, stream):
     if stream is not None:
         return ctypes.c_void_p(int(stream))
-    import torch
     if not t.is_cuda:  # host operands: the current device's current stream
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
-    return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+        return ctypes.c_void_p(_torch_module().cuda.current_stream().cuda_stream)
+    return _current_stream(t.get_device())
+
+
+def _current_stream(index):
+    """Handle of the device's current stream, without the Stream object around it where
+    torch gives the bare handle."""
+    t = _torch_module()
+    raw = getattr(t._C, "_cuda_getCurrentRawStream", None)
+    return raw(index) if raw is not None else t.cuda.current_stream(index).cuda_stream
+
+
+def _torch_module():
+    global _torch
+    if _torch is None:
+        import torch
+        _torch = torch
+    return _torch
 
 
 def _ld(t):
-    if t.dim() != 2 or t.stride(1) != 1:
+    st = t.stride()
+    if len(st) != 2 or st[1] != 1:
         raise ValueError("matrices must be 2-D with contiguous rows")
-    return t.stride(0)
+    return st[0]
 
 
 def _is_tensor(t):
     try:
-        import torch
+        return isinstance(t, _torch_module().Tensor)
     except ImportError:
         return False
-    return isinstance(t, torch.Tensor)
 
 
 def _span(t):
@@ -198,23 +217,32 @@ def _mat(t, name, rows, cols_bits, device=True):
     sizes claim would otherwise be read or written out of bounds."""
     if not _is_tensor(t):
         raise TypeError(f"{name} must be a torch tensor")
-    if t.element_size() != 8 or t.is_floating_point() or t.is_complex():
+    if t.dtype is not _torch.int64 and (t.element_size() != 8 or t.is_floating_point()
+                                        or t.is_complex()):
         raise ValueError(f"{name} must hold 64-bit words (torch.int64 or torch.uint64), "
                          f"not {t.dtype}")
-    if t.dim() != 2 or t.stride(1) != 1:
+    st = t.stride()
+    if len(st) != 2 or st[1] != 1:
         raise ValueError(f"{name} must be 2-D with contiguous rows")
     if rows > 0 and cols_bits > 0:
-        if t.shape[0] < rows or t.shape[1] < words(cols_bits):
-            raise ValueError(f"{name} has shape {tuple(t.shape)}; the sizes need at least "
+        shape = t.shape
+        if shape[0] < rows or shape[1] < words(cols_bits):
+            raise ValueError(f"{name} has shape {tuple(shape)}; the sizes need at least "
                              f"{rows} x {words(cols_bits)} words")
+    _place(t, name, device)
+    return t
+
+
+def _place(t, name, device):
     if device is True and not t.is_cuda:
         raise ValueError(f"{name} must be a GPU tensor")
     if device is False and t.is_cuda:
         raise ValueError(f"{name} must be in (page-locked) host memory")
-    return t
 
 
 def _sizes(m, k, n):
+    if m >= 0 and k >= 0 and n >= 0:
+        return
     for v, nm in ((m, "m"), (k, "k"), (n, "n")):
         if int(v) < 0:
             raise ValueError(f"{nm} = {v} is negative")
@@ -229,15 +257,21 @@ def _operands(A, B, C, m, k, n, b_transposed, device=True):
                 (B, "B", k, n)] + mats
     for t, name, r, c in mats:
         _mat(t, name, r, c, device=None)
-    for t, name, r, c in mats:
-        _mat(t, name, r, c, device=device)
+    for t, name, _, _ in mats:
+        _place(t, name, device)
 
 
 def _opts(options, flags):
-    o = Options()
-    if options is not None:
-        for name, _ in Options._fields_:
-            setattr(o, name, getattr(options, name))
+    if type(options) is Options:
+        if options.flags | flags == options.flags:
+            return options  # the library only reads it
+        o = Options()
+        ctypes.memmove(ctypes.byref(o), ctypes.byref(options), ctypes.sizeof(Options))
+    else:
+        o = Options()
+        if options is not None:
+            for name, _ in Options._fields_:
+                setattr(o, name, getattr(options, name))
     o.flags |= flags
     return o
 
@@ -246,8 +280,8 @@ def _product(fn, A, B, C, m, k, n, options, flags, stream):
     o = _opts(options, flags)
     _operands(A, B, C, m, k, n, bool(o.flags & FLAG_B_TRANSPOSED),
               device=not (o.flags & FLAG_HOST_OPERANDS))
-    _check(fn(_ptr(A), _ld(A), _ptr(B), _ld(B), _ptr(C), _ld(C), m, k, n, ctypes.byref(o),
-              _stream(C, stream)))
+    _check(fn(A.data_ptr(), _ld(A), B.data_ptr(), _ld(B), C.data_ptr(), _ld(C), m, k, n,
+              ctypes.byref(o), _stream(C, stream)))
     return C
 
 
@@ -355,8 +389,7 @@ class BatchedPlan:
 
     def launch(self, stream=None):
         if stream is None:
-            import torch
-            stream = torch.cuda.current_stream().cuda_stream
+            stream = _torch_module().cuda.current_stream().cuda_stream
         _check(_c_plan_launch(self._h, ctypes.c_void_p(int(stream))))
 
     def destroy(self):
