@@ -287,6 +287,14 @@ int cubic_product(int semiring, const uint64_t* A, int64_t lda, const uint64_t* 
                 "%zu: pass B in the form the leaf reads (B^T for the MFMA leaves and VALU tile "
                 "1, B for VALU tile 2) or call bmm_gf2 / bmm_boolean",
                 stage_bytes, caller_bt->bytes);
+  const int64_t panel = k_panel_bits(semiring, m, k, n, o);
+  // a small product reads B row-major: no transposed copy, one launch
+  if (stage && (leaf == BMM_LEAF_MFMA_I8 || leaf == BMM_LEAF_MFMA_F4) && (tile == 2 || tile == 4) &&
+      panel >= k && leaf_rows_fits(m, k, n)) {
+    LeafBatch p{A, lda, 0, B, ldb, 0, C, ldc, 0, m, k, n, 1, acc ? 1 : 0};
+    return check_hip(launch_leaf_rows(semiring, leaf == BMM_LEAF_MFMA_F4 ? 1 : 0, p, s),
+                     "leaf launch");
+  }
   const uint64_t* Bl = B;  // B^T, or B for the outer-product form
   int64_t ldl = ldb;
   if (stage) {
@@ -302,7 +310,6 @@ int cubic_product(int semiring, const uint64_t* A, int64_t lda, const uint64_t* 
   }
   // k in panels: C = sum over panels of A[:, panel] B[panel, :], each panel's product
   // added into C (XOR or OR) after the first; the leaf and tile are the full shape's
-  const int64_t panel = k_panel_bits(semiring, m, k, n, o);
   for (int64_t p0 = 0; p0 < k; p0 += panel) {
     const int64_t kp = std::min(panel, k - p0);
     const int pacc = (acc || p0 > 0) ? 1 : 0;

@@ -104,6 +104,10 @@ hipError_t launch_leaf_panel(int semiring, int fmt, const LeafBatch& p, hipStrea
 // The same on smaller tiles, for products that would leave CUs idle: 128 x 128 per workgroup,
 // or (split, and where even those are few) 64 x 64 with k split over a workgroup's waves.
 hipError_t launch_leaf_small(int semiring, int fmt, const LeafBatch& p, bool split, hipStream_t s);
+// The k-split form on B given row-major (p.BT points at B, k x n, pitch p.ldbt), so that a
+// small product is one launch; leaf_rows_fits: where this is the faster way.
+hipError_t launch_leaf_rows(int semiring, int fmt, const LeafBatch& p, hipStream_t s);
+bool leaf_rows_fits(int64_t m, int64_t k, int64_t n);
 // Whether a batch of m x n results is small in this sense.
 bool leaf_small_tiles(int64_t m, int64_t n, int64_t batch);
 hipError_t launch_leaf_valu(int semiring, const LeafBatch& p, int tile, hipStream_t s);

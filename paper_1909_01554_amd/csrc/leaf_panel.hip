@@ -46,12 +46,12 @@ hipError_t launch_semi(const LeafBatch& p, hipStream_t s) {
 
 constexpr int kSplit = 4;  // waves that share a 64 x 64 tile
 
-template <int SEMI, int FMT>
+template <int SEMI, int FMT, bool BT>
 __global__ __launch_bounds__(64 * kSplit) __attribute__((amdgpu_waves_per_eu(2))) void
 leaf_split_kernel(LeafBatch p, int64_t grid_m, int64_t grid_n) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[kSplit * panel::kSplitBytes];
   const TileCoord c = xcd_tile(blockIdx.x, gridDim.x, grid_m, grid_n);
-  panel::split_tile<SEMI, FMT, kSplit>(
+  panel::split_tile<SEMI, FMT, kSplit, BT>(
       p.A + c.b * p.strideA, p.lda, p.BT + c.b * p.strideB, p.ldbt, p.C + c.b * p.strideC, p.ldc,
       p.m, p.k, p.n, c.tm, c.tn, p.accumulate,
       __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), smem);
@@ -66,8 +66,18 @@ hipError_t launch_small(const LeafBatch& p, bool split, hipStream_t s) {
   if (!split && blocks > 512 && p.lda < kNearPitch && p.ldbt < kNearPitch)
     return launch_shape<SEMI, FMT, 2, 2, false>(p, s);
   if (!grid_fits(blocks, 64 * kSplit)) return kGridTooLarge;
-  hipLaunchKernelGGL((leaf_split_kernel<SEMI, FMT>), dim3((unsigned)blocks), dim3(64 * kSplit), 0,
-                     s, p, grid_m, grid_n);
+  hipLaunchKernelGGL((leaf_split_kernel<SEMI, FMT, true>), dim3((unsigned)blocks),
+                     dim3(64 * kSplit), 0, s, p, grid_m, grid_n);
+  return hipGetLastError();
+}
+
+template <int SEMI, int FMT>
+hipError_t launch_rows(const LeafBatch& p, hipStream_t s) {
+  const int64_t grid_m = (p.m + 63) / 64, grid_n = (p.n + 63) / 64;
+  const int64_t blocks = grid_m * grid_n * p.batch;
+  if (!grid_fits(blocks, 64 * kSplit)) return kGridTooLarge;
+  hipLaunchKernelGGL((leaf_split_kernel<SEMI, FMT, false>), dim3((unsigned)blocks),
+                     dim3(64 * kSplit), 0, s, p, grid_m, grid_n);
   return hipGetLastError();
 }
 
@@ -91,6 +101,25 @@ hipError_t launch_leaf_small(int semiring, int fmt, const LeafBatch& p, bool spl
                            : launch_small<BOOLEAN, mfma::FMT_F4>(p, split, s);
   return semiring == GF2 ? launch_small<GF2, mfma::FMT_I8>(p, split, s)
                          : launch_small<BOOLEAN, mfma::FMT_I8>(p, split, s);
+}
+
+bool leaf_rows_fits(int64_t m, int64_t k, int64_t n) {
+  // Every row of tiles turns B again, 8 bytes of a line at a time, which a saved launch (and
+  // the scratch copy) repays while the product is small: 1024^3 6.2 us against 7.2 us with a
+  // transpose of its own, 3000 x 500 x 500 6.3 and 7.3 us, 256 x 4096 x 256 7.4 and 7.7 us,
+  // but 256 x 4096 x 4096 10.5 and 9.1 us, 200 x 20000 x 200 21.8 and 14.3 us.
+  return k <= 4096 && ((m + 63) / 64) * ((n + 63) / 64) <= 512 &&
+         (double)m * (double)k * (double)n <= (double)(1 << 30);
+}
+
+hipError_t launch_leaf_rows(int semiring, int fmt, const LeafBatch& p, hipStream_t s) {
+  if (p.m <= 0 || p.n <= 0 || p.batch <= 0) return hipSuccess;
+  if (p.k >= panel::kMaxK) return hipErrorInvalidValue;  // counts would not be exact
+  if (fmt == mfma::FMT_F4)
+    return semiring == GF2 ? launch_rows<GF2, mfma::FMT_F4>(p, s)
+                           : launch_rows<BOOLEAN, mfma::FMT_F4>(p, s);
+  return semiring == GF2 ? launch_rows<GF2, mfma::FMT_I8>(p, s)
+                         : launch_rows<BOOLEAN, mfma::FMT_I8>(p, s);
 }
 
 hipError_t launch_leaf_panel(int semiring, int fmt, const LeafBatch& p, hipStream_t s) {

@@ -416,49 +416,66 @@ __device__ __forceinline__ void tile(const uint64_t* __restrict__ A, int64_t lda
 // register-fed 64 x 64 wave tiles, 35.6 and 18.2 us).  0 < k < 2^24; smem: kSplitBytes W bytes.
 constexpr int kSplitBytes = 128 * kRowBytes;
 
-template <int SEMI, int FMT, int W>
+//
+// BT = false: B is given row-major.  A wave then loads its stage's 512 rows of the tile's
+// one column word, a row per lane, and turns the 64 x 64 blocks in registers (31 VALU
+// instructions each); lane c holds column c's stage, and a swap of the wave's halves gives
+// the operands' layout, so B never goes through LDS.
+template <int SEMI, int FMT, int W, bool BT>
 __device__ __forceinline__ void split_tile(const uint64_t* __restrict__ A, int64_t lda,
-                                           const uint64_t* __restrict__ BT, int64_t ldbt,
+                                           const uint64_t* __restrict__ B, int64_t ldb,
                                            uint64_t* C, int64_t ldc, int64_t m, int64_t k,
                                            int64_t n, int64_t im, int64_t in, int accumulate,
                                            int w, unsigned char* smem) {
   const int64_t kw = (k + 63) >> 6;
   const int stages = (int)((kw + kWords - 1) / kWords);
   const int64_t row0 = im * 64, col0 = in * 64;
-  const uint64_t* Ab = A + row0 * lda;
-  const uint64_t* Bb = BT + col0 * ldbt;
   unsigned char* const mine = smem + w * kSplitBytes;
   const int lane = fresh_lane(), half = lane >> 5, li = lane & 31;
   const int chunk = (lane & 3) ^ ((lane >> 3) & 3);
+  constexpr int NL = BT ? 8 : 4;
   // load i fills LDS rows 16 i .. + 15 (A's 64 rows, then B^T's)
-  const uint64_t* src[8];
+  const uint64_t* src[NL];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < NL; ++i) {
     const bool isA = i < 4;
     const int64_t lim = isA ? m - 1 - row0 : n - 1 - col0;
     int64_t r = 16 * (i & 3) + (lane >> 2);
     r = r < lim ? r : lim;
-    src[i] = (isA ? Ab : Bb) + r * (isA ? lda : ldbt) + 2 * chunk;
+    src[i] = (isA ? A + row0 * lda : B + col0 * ldb) + r * (isA ? lda : ldb) + 2 * chunk;
   }
   typedef __attribute__((address_space(3))) unsigned char* lds_ptr;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr)mine;
+  uint64_t brow[8];  // BT = false: rows 64 j + lane of the stage, the tile's column word
   auto load = [&](int st) {
     const int64_t w0 = (int64_t)st * kWords;
-    if (w0 + kWords <= kw) {  // uniform
+    const bool whole = (w0 + kWords) * 64 <= k;  // uniform
+    if constexpr (!BT) {
+      const mfma::gq_ptr p = (mfma::gq_ptr)B + (w0 * 64 + lane) * ldb + in;
+      if (whole) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) load_lds16(src[i] + w0, lds0 + i * 1024);
+        for (int j = 0; j < 8; ++j) brow[j] = p[64 * j * ldb];
+      } else {
+        const int64_t rows = k - w0 * 64 - lane;  // row 64 j + lane lies in B if 64 j < rows
+#pragma unroll
+        for (int j = 0; j < 8; ++j) brow[j] = 64 * j < rows ? p[64 * j * ldb] : 0ull;
+      }
+    }
+    if (whole || w0 + kWords <= kw) {
+#pragma unroll
+      for (int i = 0; i < NL; ++i) load_lds16(src[i] + w0, lds0 + i * 1024);
       return;
     }
     const int left = (int)(kw - w0) - 2 * chunk;  // words of the lane's chunk and after
     const int o0 = left > 0 ? 0 : left - 1, o1 = left > 1 ? 1 : left - 1;
-    uint64_t x[8][2];
+    uint64_t x[NL][2];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < NL; ++i) {
       x[i][0] = ((mfma::gq_ptr)src[i])[w0 + o0];
       x[i][1] = ((mfma::gq_ptr)src[i])[w0 + o1];
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < NL; ++i) {
       ulonglong2 v;
       v.x = left > 0 ? x[i][0] : 0ull;
       v.y = left > 1 ? x[i][1] : 0ull;
@@ -472,16 +489,34 @@ __device__ __forceinline__ void split_tile(const uint64_t* __restrict__ A, int64
 #pragma unroll
     for (int g = 0; g < 2; ++g) acc[f][g] = AccV{};
   const int base = li * kRowBytes + (half ^ ((li >> 1) & 3)) * 16;
+  const Transpose tr(lane);
   if (w < stages) load(w);
   for (int st = w; st < stages; st += W) {
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     u4 xa[2][2], xb[2][2];
+    if constexpr (!BT) {
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {  // word v of chunks 2 s and 2 s + 1
+          const uint64_t c0 = transpose64(brow[4 * s + v], tr);
+          const uint64_t c1 = transpose64(brow[4 * s + 2 + v], tr);
+          const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)c0, (uint32_t)c1, false, false);
+          const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(c0 >> 32),
+                                                           (uint32_t)(c1 >> 32), false, false);
+          xb[s][0][2 * v] = lo[0];
+          xb[s][1][2 * v] = lo[1];
+          xb[s][0][2 * v + 1] = hi[0];
+          xb[s][1][2 * v + 1] = hi[1];
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
 #pragma unroll
     for (int s = 0; s < 2; ++s)
 #pragma unroll
       for (int f = 0; f < 2; ++f) {
         xa[s][f] = *reinterpret_cast<const u4*>(mine + (base ^ (32 * s)) + 2048 * f);
-        xb[s][f] = *reinterpret_cast<const u4*>(mine + 4096 + (base ^ (32 * s)) + 2048 * f);
+        if constexpr (BT)
+          xb[s][f] = *reinterpret_cast<const u4*>(mine + 4096 + (base ^ (32 * s)) + 2048 * f);
       }
     if (st + W < stages) {
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // read: the next stage may land
@@ -493,16 +528,13 @@ __device__ __forceinline__ void split_tile(const uint64_t* __restrict__ A, int64
   // lane li of half h holds row r(li) of block h: one word of C per lane and wave
   constexpr bool gf2 = SEMI == GF2;
   uint64_t word = 0;
-  {
-    const Transpose tr(lane);
 #pragma unroll
-    for (int g = 0; g < 2; ++g) {
-      const auto s = __builtin_amdgcn_permlane32_swap(pack16<FMT>(acc[0][g], gf2),
-                                                      pack16<FMT>(acc[1][g], gf2), false, false);
-      const uint32_t x =
-          tr(__builtin_amdgcn_perm(s[1], s[0], packs_high<FMT>(gf2) ? 0x07060302u : 0x05040100u));
-      word |= (uint64_t)x << (32 * g);
-    }
+  for (int g = 0; g < 2; ++g) {
+    const auto s = __builtin_amdgcn_permlane32_swap(pack16<FMT>(acc[0][g], gf2),
+                                                    pack16<FMT>(acc[1][g], gf2), false, false);
+    const uint32_t x =
+        tr(__builtin_amdgcn_perm(s[1], s[0], packs_high<FMT>(gf2) ? 0x07060302u : 0x05040100u));
+    word |= (uint64_t)x << (32 * g);
   }
   uint64_t* const part = reinterpret_cast<uint64_t*>(smem);
   __syncthreads();  // every wave is done with its stages

@@ -109,6 +109,31 @@ def test_small_tiles(bmm, sname, sr, fname, leaf, tile):
             assert np.array_equal(from_dev(Cd, words(n)), want), (m, k, n, acc)
 
 
+# products that read B row-major in one launch (m k n up to 2^30, k up to 4096), and ones just
+# past that; B's last rows short of a 64-row block, a stage and a wave's turn
+ROWS = [(1, 1, 1), (64, 64, 64), (65, 63, 129), (130, 513, 70), (40, 2047, 200), (300, 4096, 257),
+        (64, 4097, 64), (1024, 1024, 1024), (1025, 1024, 1024)]
+
+
+@pytest.mark.parametrize("sname,sr", SEMIRINGS)
+@pytest.mark.parametrize("fname,leaf", FORMATS)
+@pytest.mark.parametrize("tile", [0, 2, 4])
+def test_row_major_b_in_one_launch(bmm, sname, sr, fname, leaf, tile):
+    for i, (m, k, n) in enumerate(ROWS):
+        p = bmmgen.Dist.half() if sr == oracle.GF2 else bmmgen.Dist.inv_sqrt(k)
+        A = bmmgen.fill_cpu(m, k, 111 + i, bmmgen.TAG_A, p)
+        B = bmmgen.fill_cpu(k, n, 111 + i, bmmgen.TAG_B, p)
+        C0 = bmmgen.fill_cpu(m, n, 111 + i, 0xC0, bmmgen.Dist.half())
+        ab = oracle.mul(A, B, k, n, sr)
+        for acc in (False, True):
+            announce("rows", sname, fname, tile, (m, k, n), acc)
+            Cd = to_dev(C0) if acc else empty_dev(m, words(n), fill=-1)
+            product(bmm, sr)(to_dev(A, A.shape[1] + i % 2), to_dev(B, B.shape[1] + i % 3), Cd, m, k,
+                             n, options=bmm.Options(leaf=leaf, tile=tile), accumulate=acc)
+            want = ab if not acc else (ab ^ C0 if sr == oracle.GF2 else ab | C0)
+            assert np.array_equal(from_dev(Cd, words(n)), want), (m, k, n, acc)
+
+
 def test_transpose_edges(bmm):
     """Both tile sizes of the transpose (fewer than 256 tiles of 512 x 512 bits, or not), odd
     pitches, and edges within and past a 64-bit block; padding bits come out zero."""
