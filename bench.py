@@ -615,8 +615,11 @@ def main():
         return [torch.cuda.Event(enable_timing=True) for _ in range(4)]
 
     def opts(leaf):
-        # --tile applies to the timed leaf kind only; side steps take their tuned tiles
-        return bmm.Options(leaf=leaf, tile=args.tile if leaf == LEAF[args.leaf] else 0,
+        # --tile applies to the timed leaf kind only; side steps take their tuned tiles, but
+        # for the VALU leaf, whose dot-product form (tile 1) is what its issue-rate roofline
+        # counts (the table form of tile 2 looks sums up instead of folding)
+        tile = args.tile if leaf == LEAF[args.leaf] else 0
+        return bmm.Options(leaf=leaf, tile=tile or (1 if leaf == bmm.LEAF_VALU else 0),
                            depth_serial=args.depth_serial,
                            depth_parallel=-1 if args.depth_serial < 0 else
                            args.depth - args.depth_serial, shift=args.shift)

@@ -174,8 +174,9 @@ int auto_leaf_locked(int64_t k) {
   return leaf == BMM_LEAF_MFMA_F4 && k >= kPanelMaxK ? BMM_LEAF_MFMA_I8 : leaf;
 }
 
+// row_major: the product may read B row-major (the VALU leaf's tile 2).
 void pick_leaf(int semiring, int64_t m, int64_t k, int64_t n, int64_t batch,
-               const bmm_options& o, int* leaf, int* tile) {
+               const bmm_options& o, int* leaf, int* tile, bool row_major = false) {
   *leaf = o.leaf;
   *tile = o.tile;
   if (*leaf == BMM_LEAF_AUTO || *tile <= 0) {
@@ -188,9 +189,11 @@ void pick_leaf(int semiring, int64_t m, int64_t k, int64_t n, int64_t batch,
     if (*leaf == BMM_LEAF_AUTO) *leaf = auto_leaf_locked(k);
   }
   if (*tile <= 0) {
-    // default MFMA tile for shapes the table lacks: small tiles where large ones would leave
+    // default tile for shapes the table lacks.  VALU: tables of B's rows for large cubic
+    // products, else the dot-product form; MFMA: small tiles where large ones would leave
     // CUs idle, else the panel leaf (under the numbers of the long-k tiles for long k)
-    if (*leaf != BMM_LEAF_VALU && leaf_small_tiles(m, n, batch)) *tile = 2;
+    if (*leaf == BMM_LEAF_VALU) *tile = row_major && leaf_valu_table_fits(m, n) ? 2 : 1;
+    else if (leaf_small_tiles(m, n, batch)) *tile = 2;
     else if (*leaf == BMM_LEAF_MFMA_I8 && k >= 8192) *tile = 7;
     else if (*leaf == BMM_LEAF_MFMA_F4 && k >= 4096) *tile = 5;
     else *tile = 1;
@@ -274,7 +277,7 @@ int cubic_product(int semiring, const uint64_t* A, int64_t lda, const uint64_t* 
     return BMM_OK;
   }
   int leaf, tile;
-  pick_leaf(semiring, m, k, n, 1, o, &leaf, &tile);
+  pick_leaf(semiring, m, k, n, 1, o, &leaf, &tile, caller_bt == nullptr);
   // The VALU leaf's outer-product form (tile 2) reads B row-major; every other leaf reads
   // B^T. Whichever form the leaf needs and the caller did not pass is staged in scratch.
   const bool outer = leaf == BMM_LEAF_VALU && tile == 2;
@@ -314,8 +317,9 @@ int cubic_product(int semiring, const uint64_t* A, int64_t lda, const uint64_t* 
     const int64_t kp = std::min(panel, k - p0);
     const int pacc = (acc || p0 > 0) ? 1 : 0;
     if (outer) {
-      HIP_TRY(launch_leaf_valu_outer(semiring, A + p0 / 64, lda, Bl + p0 * ldl, ldl, C, ldc, m,
-                                     kp, n, pacc, s),
+      const auto launch =
+          leaf_valu_table_fits(m, n) ? launch_leaf_valu_table : launch_leaf_valu_outer;
+      HIP_TRY(launch(semiring, A + p0 / 64, lda, Bl + p0 * ldl, ldl, C, ldc, m, kp, n, pacc, s),
               "leaf launch");
     } else {
       LeafBatch p{A + p0 / 64, lda, 0, Bl + p0 / 64, ldl, 0, C, ldc, 0, m, kp, n, 1, pacc};
@@ -935,7 +939,7 @@ int bmm_leaf_choice(int semiring, int64_t m, int64_t k, int64_t n, int64_t batch
   if (semiring != BMM_GF2 && semiring != BMM_BOOLEAN) return fail(BMM_E_INVAL, "bad semiring");
   if (m < 0 || k < 0 || n < 0 || batch <= 0) return fail(BMM_E_INVAL, "bad shape");
   if (!leaf_out || !tile_out) return fail(BMM_E_INVAL, "null output");
-  pick_leaf(semiring, m, k, n, batch, opt ? *opt : defaults(), leaf_out, tile_out);
+  pick_leaf(semiring, m, k, n, batch, opt ? *opt : defaults(), leaf_out, tile_out, batch == 1);
   return BMM_OK;
 }
 

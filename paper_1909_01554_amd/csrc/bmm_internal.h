@@ -117,6 +117,11 @@ hipError_t launch_leaf_valu_outer(int semiring, const uint64_t* A, int64_t lda,
                                   const uint64_t* B, int64_t ldb, uint64_t* C, int64_t ldc,
                                   int64_t m, int64_t k, int64_t n, int accumulate,
                                   hipStream_t s);
+// The same product by tables of sums of 8 rows of B in LDS (leaf_valu_table.hip).
+hipError_t launch_leaf_valu_table(int semiring, const uint64_t* A, int64_t lda, const uint64_t* B,
+                                  int64_t ldb, uint64_t* C, int64_t ldc, int64_t m, int64_t k,
+                                  int64_t n, int accumulate, hipStream_t s);
+bool leaf_valu_table_fits(int64_t m, int64_t n);  // where it is the faster form
 // The last recursion level shifted into the int8 leaf (leaf_shift.hip): for every
 // parent p, the seven child products of its quadrants (alpha, beta of `scheme`) are
 // formed, multiplied and combined by gamma into the parent's result quadrants.

@@ -35,6 +35,7 @@
 #include <type_traits>
 
 #include "bit_transpose.h"
+#include "lds_load.h"
 #include "mfma_tile.h"
 
 namespace bmm {
@@ -55,21 +56,6 @@ constexpr int kRowBytes = 8 * kWords;   // LDS row
 constexpr int64_t kMaxK = kPanelMaxK;
 
 constexpr int lds_bytes(int RA, int RB) { return 2 * 64 * (RA + RB) * kRowBytes; }
-
-// 16 bytes per lane from base + voff to LDS at lds + 16 * lane (base and lds uniform).
-// The caller waits with stage_sync() before anyone reads them.  Global addresses need
-// 8-byte alignment only, which rows of odd pitch have.
-__device__ __forceinline__ void load_lds16(const void* base, uint32_t voff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds),
-               "v"(voff), "s"(base)
-               : "memory");
-}
-
-__device__ __forceinline__ void load_lds16(const void* addr, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds),
-               "v"(addr)
-               : "memory");
-}
 
 // This wave's LDS reads, LDS writes and direct loads are done, then everyone's.
 __device__ __forceinline__ void stage_sync() {
