@@ -29,7 +29,7 @@ namespace {
 // counters, for problems that share a matrix-core leaf kind and tile.
 struct Plan {
   BatchedDesc* descs = nullptr;  // device
-  BatchedSeg* segs = nullptr;    // device: every queue's segments, queue after queue
+  BatchedItem* list = nullptr;   // device: every queue's items, queue after queue
   unsigned int* counters = nullptr;
   BatchedQueues queues{};
   int64_t count = 0;
@@ -48,10 +48,10 @@ bool capturing(hipStream_t s) {
 // Free a group's device memory; the caller has made sure no launch of it still runs.
 void plan_free(Plan* P) {
   (void)hipFree(P->descs);
-  (void)hipFree(P->segs);
+  (void)hipFree(P->list);
   (void)hipFree(P->counters);
   P->descs = nullptr;
-  P->segs = nullptr;
+  P->list = nullptr;
   P->counters = nullptr;
 }
 
@@ -148,35 +148,45 @@ int build_plan(const bmm_problem* problems, const std::vector<int64_t>& idx, int
   P.tile = tile;
   P.count = (int64_t)host.size();
   std::vector<BatchedSeg> segs;
+  uint64_t total = 0;
   for (int x = 0; x < kXcds; ++x) {
     if (qitems[x] >= ((uint64_t)1 << 32) - ((uint64_t)1 << 20))
       return bfail(BMM_E_UNSUPPORTED, "batched plans hold fewer than 2^32 items per queue");
     P.queues.seg_off[x] = (uint32_t)segs.size();
     P.queues.seg_count[x] = (uint32_t)qsegs[x].size();
     P.queues.items[x] = (uint32_t)qitems[x];
+    P.queues.first[x] = total;
+    total += qitems[x];
     segs.insert(segs.end(), qsegs[x].begin(), qsegs[x].end());
   }
   if (hipGetDevice(&P.device) != hipSuccess) return bfail(BMM_E_DEVICE, "hipGetDevice");
   int cus = 256;
   (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, P.device);
-  P.grid = std::max(kXcds, cus * wg_per_cu);
+  // (two workgroups of tile 4 fit on a CU: more would only start to find the queues empty)
+  P.grid = std::max(kXcds, cus * (tile == 4 ? std::min(wg_per_cu, 2) : wg_per_cu));
   if (P.count > 0) {
-    const size_t cbytes = sizeof(unsigned int) * kXcds * kBatchedCounterStride;
+    // one counter per queue, and of the workgroups that have left
+    std::vector<unsigned int> counters((kXcds + 1) * kBatchedCounterStride, 0u);
+    for (int x = 0; x < kXcds; ++x)
+      counters[x * kBatchedCounterStride] = batched_first_take((unsigned)P.grid, (unsigned)x);
+    const size_t cbytes = sizeof(unsigned int) * counters.size();
+    // the list, then the segments it is expanded from
     if (bmm::dev_malloc((void**)&P.descs, sizeof(BatchedDesc) * host.size()) != hipSuccess ||
-        bmm::dev_malloc((void**)&P.segs, sizeof(BatchedSeg) * segs.size()) != hipSuccess ||
+        bmm::dev_malloc((void**)&P.list, sizeof(BatchedItem) * total +
+                                             sizeof(BatchedSeg) * segs.size()) != hipSuccess ||
         bmm::dev_malloc((void**)&P.counters, cbytes) != hipSuccess) {
-      (void)hipGetLastError();
-      (void)hipFree(P.descs);
-      (void)hipFree(P.segs);
-      return bfail(BMM_E_NOMEM, "plan allocation");
+      plan_free(&P);
+      return bfail(BMM_E_NOMEM, "plan allocation: %s", hipGetErrorString(hipGetLastError()));
     }
+    BatchedSeg* dsegs = reinterpret_cast<BatchedSeg*>(P.list + total);
     if (hipMemcpy(P.descs, host.data(), sizeof(BatchedDesc) * host.size(),
                   hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(P.segs, segs.data(), sizeof(BatchedSeg) * segs.size(),
-                  hipMemcpyHostToDevice) != hipSuccess) {
-      (void)hipFree(P.descs);
-      (void)hipFree(P.segs);
-      (void)hipFree(P.counters);
+        hipMemcpy(dsegs, segs.data(), sizeof(BatchedSeg) * segs.size(),
+                  hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(P.counters, counters.data(), cbytes, hipMemcpyHostToDevice) != hipSuccess ||
+        launch_batched_list(P.descs, dsegs, P.queues, P.list, nullptr) != hipSuccess ||
+        hipStreamSynchronize(nullptr) != hipSuccess) {
+      plan_free(&P);
       return bfail(BMM_E_DEVICE, "plan upload: %s", hipGetErrorString(hipGetLastError()));
     }
   }
@@ -270,7 +280,7 @@ int set_kernels(const PlanSet* S, hipStream_t s) {
   }
   for (const Plan& P : S->groups) {
     if (P.count == 0) continue;
-    hipError_t e = launch_batched_persistent(P.descs, P.segs, P.queues, P.counters, P.grid,
+    hipError_t e = launch_batched_persistent(P.descs, P.list, P.queues, P.counters, P.grid,
                                              P.tile, P.leaf == BMM_LEAF_MFMA_F4 ? 1 : 0, s);
     if (e != hipSuccess) return bfail(BMM_E_DEVICE, "batched launch: %s", hipGetErrorString(e));
   }

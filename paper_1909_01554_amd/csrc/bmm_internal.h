@@ -218,8 +218,8 @@ hipError_t launch_valu_rate(uint32_t seed, int64_t rounds, int blocks, uint32_t*
 // Persistent batched leaf over a device-resident problem table.  A work item is
 // one workgroup's 2 x 2 wave tiles of one problem; a problem's items, in banded
 // order, are split into contiguous ranges over kXcds queues (one per XCD), and
-// a queue's items are listed as segments (problem, first item) at increasing
-// queue positions.
+// a queue's items are listed one after another (expanded on the device from segments
+// (problem, first item) at increasing queue positions).
 struct BatchedDesc {
   const uint64_t* A;
   const uint64_t* BT;
@@ -237,16 +237,29 @@ struct BatchedSeg {
   uint32_t item_lo;  // the problem's item at that position
   uint32_t pad;
 };
+struct BatchedItem {
+  uint32_t problem, im, in, pad;  // 16 bytes per at least 2 KB of result
+};
 struct BatchedQueues {
+  uint64_t first[kXcds];  // of the queue's items in the list
   uint32_t seg_off[kXcds], seg_count[kXcds], items[kXcds];
 };
 constexpr int kBatchedCounterStride = 64;  // uint32s between queue counters (256 bytes)
 // tile 1: 128 x 64 per wave, 2: 64 x 64, 3: 64 x 128, 4: the panel leaf's 128 x 64
 // (k < kPanelMaxK, pitches below kNearPitch); fmt: mfma::MfmaFormat (0 int8, 1 E2M1).
-// counters: kXcds * kBatchedCounterStride uint32s, zeroed by the launch itself.
-hipError_t launch_batched_persistent(const BatchedDesc* descs, const BatchedSeg* segs,
+// counters: (kXcds + 1) * kBatchedCounterStride uint32s, set up with the plan and set back by
+// every launch.
+// Workgroup w of the grid starts with item w / kXcds of queue w % kXcds: the first
+// position of queue q that is taken by counting.
+__host__ __device__ inline unsigned batched_first_take(unsigned grid, unsigned q) {
+  return (grid + kXcds - 1 - q) / kXcds;
+}
+hipError_t launch_batched_persistent(const BatchedDesc* descs, const BatchedItem* list,
                                      const BatchedQueues& queues, unsigned int* counters,
                                      int grid, int tile, int fmt, hipStream_t s);
+// list[queues.first[q] + i]: item i of queue q, from the queues' segments.
+hipError_t launch_batched_list(const BatchedDesc* descs, const BatchedSeg* segs,
+                               const BatchedQueues& queues, BatchedItem* list, hipStream_t s);
 // Generation of the batched tuning records (changes whenever one is set or loaded).
 uint64_t batched_tune_generation();
 // Release bmm_batched's library-owned plans, graphs and staging buffers.

@@ -267,12 +267,19 @@ __device__ __forceinline__ void store_tile(const typename mfma::Acc<FMT>::type (
 // (Workgroups that took several tiles in turn, the next one's first stage loaded during
 // the last stage of this one, were 7 to 10% slower than one workgroup per tile, which the
 // hardware hands out as CUs come free: 62.8 against 57.8 ms for the n = 65536 recursion.)
-template <int SEMI, int FMT, int RA, int RB, bool FAR>
+// hook.loaded() runs on every wave once the first stage has arrived (and with it whatever the
+// wave had asked of memory before), hook.summed() before the results are stored: for a
+// persistent caller that looks ahead.
+struct NoHook {
+  __device__ void loaded() const {}
+  __device__ void summed() const {}
+};
+template <int SEMI, int FMT, int RA, int RB, bool FAR, class Hook = NoHook>
 __device__ __forceinline__ void tile(const uint64_t* __restrict__ A, int64_t lda,
                                      const uint64_t* __restrict__ BT, int64_t ldbt, uint64_t* C,
                                      int64_t ldc, int64_t m, int64_t k, int64_t n, int64_t im,
                                      int64_t in, int accumulate, int semiring, int w,
-                                     unsigned char* smem) {
+                                     unsigned char* smem, Hook&& hook = Hook()) {
   constexpr int TM = 64 * RA, TN = 64 * RB, NL = (TM + TN) / 64;
   constexpr int STAGE = (TM + TN) * kRowBytes;
   const int wy = w >> 1, wx = w & 1;
@@ -368,6 +375,7 @@ __device__ __forceinline__ void tile(const uint64_t* __restrict__ A, int64_t lda
     for (int g = 0; g < RB; ++g) acc[f][g] = AccV{};
   load(0, 0);
   stage_sync();
+  hook.loaded();
   if (stages > 1) load(1, 1);
   read(0, 0);
   // waves in their main loop go before the other workgroup's first loads and epilogue
@@ -385,6 +393,7 @@ __device__ __forceinline__ void tile(const uint64_t* __restrict__ A, int64_t lda
     cur ^= 1;
   }
   __builtin_amdgcn_s_setprio(0);
+  hook.summed();
   store_tile<SEMI, FMT, RA, RB>(acc, C, ldc, m, n, row0 + wy * 32 * RA,
                                 (col0 >> 6) + wx * (RB / 2), accumulate, semiring);
 }
