@@ -14,8 +14,8 @@
 // the item before is computed.  The last workgroup to leave sets the queue counters
 // back, so a launch is one kernel and can be captured into a HIP graph and replayed.
 // Together these took 256 problems of 256 to 1024 from 58 to 50 us, 300 of 256 to 2048 from
-// 136 to 122 us, and one of 256 from 18.6 to 12.8 us; with k in the thousands the matrix
-// cores bound an item, and 256 problems of 256 to 8192 stay at 1.03 ms.
+// 136 to 122 us, and one of 256 from 18.6 to 12.8 us.  With k in the thousands the matrix
+// cores bound an item.
 #include <stddef.h>
 
 #include "panel_tile.h"
@@ -146,7 +146,9 @@ __global__ void list_kernel(const BatchedDesc* __restrict__ descs,
 // before it starts: while item i is computed, wave 0 has on their way the descriptor of
 // item i + 1's problem, the record of item i + 2 and the position of item i + 3, each asked
 // for when what it depends on has come with the operands of some first stage, so
-// nothing waits for them.  Descriptor and record are handed to the other waves in LDS.
+// nothing waits for them.  The first stage of the next item is loaded while the results of this one are
+// packed and stored (256 problems of 256 to 8192: 963 us, without it 1019; 256 of 256 to 1024:
+// 46.6 and 50.0 us).
 // All of it goes to LDS directly.
 struct alignas(16) Ahead {
   uint32_t desc[2][32];    // of the items at hand and next (0..23: a BatchedDesc)
@@ -190,14 +192,18 @@ struct LookAhead {
   static __device__ __forceinline__ void arrive() {
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
   }
-  __device__ __forceinline__ void loaded() {
+  __device__ __forceinline__ void operator()() {
     if (w != 0) return;
     record(it + 2);
     descriptor(it + 1);
   }
-  __device__ __forceinline__ void summed() {
-    if (w == 0) arrive();
-  }
+};
+
+// What of an item is needed after its sums.
+struct Result {
+  uint64_t* C;
+  int64_t ldc, m, n, row0, col0;
+  int semiring;
 };
 
 template <int FMT>
@@ -222,21 +228,44 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void b
     LookAhead::arrive();
   }
   __syncthreads();
-  for (;; ++ahead.it) {
+  using Op = panel::Operands<4, 2, false>;
+  // the operands of the item at hand, their first stage on its way
+  auto begin = [&](Result& r) {
     const uint32_t* rec = lds.record[ahead.it & 3];
     const uint32_t mine = lds.desc[ahead.it & 1][lane & 31];
     auto word = [&](int i) { return (uint32_t)__builtin_amdgcn_readlane((int)mine, i); };
     auto quad = [&](int i) { return (uint64_t)word(i) | ((uint64_t)word(i + 1) << 32); };
-    if (__builtin_amdgcn_readfirstlane(rec[0]) == kNoItem) break;  // the same for every wave
     constexpr int M = offsetof(BatchedDesc, m) / 4, LD = offsetof(BatchedDesc, lda) / 4;
-    panel::tile<mfma::SEMI_ANY, FMT, 4, 2, false>(
-        (const uint64_t*)quad(0), (int64_t)quad(LD), (const uint64_t*)quad(2), (int64_t)quad(LD + 2),
-        (uint64_t*)quad(4), (int64_t)quad(LD + 4), (int64_t)quad(M), (int64_t)quad(M + 2),
-        (int64_t)quad(M + 4), (uint32_t)__builtin_amdgcn_readfirstlane(rec[1]),
-        (uint32_t)__builtin_amdgcn_readfirstlane(rec[2]), 0,
-        (int)word(offsetof(BatchedDesc, semiring) / 4), w, smem, ahead);
-    // (also what frees the item's LDS for the next one)
-    __syncthreads();
+    const uint32_t im = __builtin_amdgcn_readfirstlane(rec[1]);
+    const uint32_t in = __builtin_amdgcn_readfirstlane(rec[2]);
+    r = Result{(uint64_t*)quad(4), (int64_t)quad(LD + 4), (int64_t)quad(M), (int64_t)quad(M + 4),
+               (int64_t)im * Op::TM + (w >> 1) * 128, (int64_t)in * (Op::TN / 64) + (w & 1),
+               (int)word(offsetof(BatchedDesc, semiring) / 4)};
+    Op op((const uint64_t*)quad(0), (int64_t)quad(LD), (const uint64_t*)quad(2),
+          (int64_t)quad(LD + 2), r.m, (int64_t)quad(M + 2), r.n, im, in, w, smem);
+    op.load(0, 0);
+    return op;
+  };
+  auto none = [&]() {  // the same for every wave
+    return __builtin_amdgcn_readfirstlane(lds.record[ahead.it & 3][0]) == kNoItem;
+  };
+  if (!none()) {
+    Result now, next;
+    Op op = begin(next);
+    bool more = true;
+    while (more) {
+      now = next;
+      panel::AccV<FMT> acc[4][2];
+      panel::sums<mfma::SEMI_ANY, FMT, 4, 2, false>(op, 0, acc, ahead);
+      // all waves are done with the operands, and the next item is in LDS
+      if (w == 0) LookAhead::arrive();
+      __syncthreads();
+      ++ahead.it;
+      more = !none();
+      if (more) op = begin(next);
+      panel::store_tile<mfma::SEMI_ANY, FMT, 4, 2>(acc, now.C, now.ldc, now.m, now.n, now.row0,
+                                                   now.col0, 0, now.semiring);
+    }
   }
   if (w == 0) leave(counters, lane);
 }

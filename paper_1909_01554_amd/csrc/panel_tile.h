@@ -260,45 +260,34 @@ __device__ __forceinline__ void store_tile(const typename mfma::Acc<FMT>::type (
 
 // ---- one workgroup tile ----
 
-// Rows [64 RA im, ...) x columns [64 RB in, ...) of C = A B, by the four waves w = 0..3 of
-// a workgroup (all of them call it; every one takes part in loads and barriers).  Needs
-// k < 2^24 and lds_bytes(RA, RB) of LDS, which nobody reads any more when it is called.
-// FAR: pitches of kNearPitch words and more (64-bit row addresses).
-// (Workgroups that took several tiles in turn, the next one's first stage loaded during
-// the last stage of this one, were 7 to 10% slower than one workgroup per tile, which the
-// hardware hands out as CUs come free: 62.8 against 57.8 ms for the n = 65536 recursion.)
-// hook.loaded() runs on every wave once the first stage has arrived (and with it whatever the
-// wave had asked of memory before), hook.summed() before the results are stored: for a
-// persistent caller that looks ahead.
-struct NoHook {
-  __device__ void loaded() const {}
-  __device__ void summed() const {}
-};
-template <int SEMI, int FMT, int RA, int RB, bool FAR, class Hook = NoHook>
-__device__ __forceinline__ void tile(const uint64_t* __restrict__ A, int64_t lda,
-                                     const uint64_t* __restrict__ BT, int64_t ldbt, uint64_t* C,
-                                     int64_t ldc, int64_t m, int64_t k, int64_t n, int64_t im,
-                                     int64_t in, int accumulate, int semiring, int w,
-                                     unsigned char* smem, Hook&& hook = Hook()) {
-  constexpr int TM = 64 * RA, TN = 64 * RB, NL = (TM + TN) / 64;
-  constexpr int STAGE = (TM + TN) * kRowBytes;
-  const int wy = w >> 1, wx = w & 1;
-  const int64_t kw = (k + 63) >> 6;
-  const int64_t stages = (kw + kWords - 1) / kWords;
-  const int64_t row0 = im * TM, col0 = in * TN;
-  const uint64_t* Ab = A + row0 * lda;
-  const uint64_t* Bb = BT + col0 * ldbt;
+// The operands of one workgroup tile and the loads of their stages, made and called by all
+// its waves.
+template <int RA, int RB, bool FAR>
+struct Operands {
+  static constexpr int TM = 64 * RA, TN = 64 * RB, NL = (TM + TN) / 64;
+  static constexpr int STAGE = (TM + TN) * kRowBytes;
+  const uint64_t *Ab, *Bb;
+  int64_t lda, ldbt, kw;
+  int w;
+  unsigned char* smem;
+  uint32_t voff[NL];  // byte offset of the lane's chunk, or (FAR) its row
 
   // Load i of wave w fills LDS rows 16 (4 i + w) .. + 15, 4 lanes per row; rows past the
   // end of an operand repeat its last one (their results are not stored).
-  auto chunk_of = [](int ln) { return (ln & 3) ^ ((ln >> 3) & 3); };  // of a lane's slot
-  uint32_t voff[NL];  // byte offset of the lane's chunk, or (FAR) its row
-  {
+  static __device__ __forceinline__ int chunk_of(int ln) {  // of a lane's slot
+    return (ln & 3) ^ ((ln >> 3) & 3);
+  }
+  __device__ __forceinline__ Operands(const uint64_t* __restrict__ A, int64_t lda_,
+                                      const uint64_t* __restrict__ BT, int64_t ldbt_, int64_t m,
+                                      int64_t k, int64_t n, int64_t im, int64_t in, int w_,
+                                      unsigned char* smem_)
+      : Ab(A + im * TM * lda_), Bb(BT + in * TN * ldbt_), lda(lda_), ldbt(ldbt_),
+        kw((k + 63) >> 6), w(w_), smem(smem_) {
     const int lane = fresh_lane();
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
       const bool isA = 64 * i < TM;
-      const int64_t lim = isA ? m - 1 - row0 : n - 1 - col0;
+      const int64_t lim = isA ? m - 1 - im * TM : n - 1 - in * TN;
       int r = 16 * (4 * i + w) + (lane >> 2) - (isA ? 0 : TM);
       r = r < lim ? r : (int)lim;
       voff[i] = FAR ? (uint32_t)r
@@ -306,15 +295,16 @@ __device__ __forceinline__ void tile(const uint64_t* __restrict__ A, int64_t lda
     }
   }
   // the lane's chunk of load i in the stage at word w0
-  auto source = [&](int i, int64_t w0) -> const uint64_t* {
+  __device__ __forceinline__ const uint64_t* source(int i, int64_t w0) const {
     const bool isA = 64 * i < TM;
     const uint64_t* base = (isA ? Ab : Bb) + w0;
     if (FAR) return base + (int64_t)voff[i] * (isA ? lda : ldbt) + 2 * chunk_of(fresh_lane());
     return (const uint64_t*)((const char*)base + voff[i]);
-  };
-  typedef __attribute__((address_space(3))) unsigned char* lds_ptr;
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr)smem + w * 1024;
-  auto load = [&](int64_t st, int buf) {
+  }
+  // Stage st into LDS buffer buf.
+  __device__ __forceinline__ void load(int64_t st, int buf) const {
+    typedef __attribute__((address_space(3))) unsigned char* lds_ptr;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr)smem + w * 1024;
     const int64_t w0 = st * kWords;
     if (w0 + kWords <= kw) {  // uniform
 #pragma unroll
@@ -351,8 +341,25 @@ __device__ __forceinline__ void tile(const uint64_t* __restrict__ A, int64_t lda
         *reinterpret_cast<ulonglong2*>(smem + w * 1024 + buf * STAGE + (i + j) * 4096 + lane * 16) = v;
       }
     }
-  };
+  }
+};
 
+// The sums of one wave of the tile whose first stage is on its way to LDS buffer buf.
+// loaded() runs on every wave once it has arrived (and with it whatever the wave had asked
+// of memory before).  At the end other waves may still be reading their last stage.
+struct NoHook {
+  __device__ void operator()() const {}
+};
+template <int FMT>
+using AccV = typename mfma::Acc<FMT>::type;
+template <int SEMI, int FMT, int RA, int RB, bool FAR, class Hook = NoHook>
+__device__ __forceinline__ void sums(const Operands<RA, RB, FAR>& op, int buf,
+                                     AccV<FMT> (&acc)[RA][RB], Hook&& loaded = Hook()) {
+  constexpr int TM = 64 * RA, STAGE = Operands<RA, RB, FAR>::STAGE;
+  const int wy = op.w >> 1, wx = op.w & 1;
+  const int64_t kw = op.kw;
+  const int64_t stages = (kw + kWords - 1) / kWords;
+  unsigned char* smem = op.smem;
   // raw words of two rounds: lane half h takes chunk 2 s + h of round s
   const int lane = fresh_lane(), half = lane >> 5, li = lane & 31;
   const int slot = (half ^ ((li >> 1) & 3)) * 16;
@@ -367,35 +374,50 @@ __device__ __forceinline__ void tile(const uint64_t* __restrict__ A, int64_t lda
     for (int g = 0; g < RB; ++g)
       xb[s][g] = *reinterpret_cast<const u4*>(smem + buf * STAGE + (bbase ^ (32 * s)) + 2048 * g);
   };
-  using AccV = typename mfma::Acc<FMT>::type;
-  AccV acc[RA][RB];
 #pragma unroll
   for (int f = 0; f < RA; ++f)
 #pragma unroll
-    for (int g = 0; g < RB; ++g) acc[f][g] = AccV{};
-  load(0, 0);
+    for (int g = 0; g < RB; ++g) acc[f][g] = AccV<FMT>{};
   stage_sync();
-  hook.loaded();
-  if (stages > 1) load(1, 1);
-  read(0, 0);
+  loaded();
+  if (stages > 1) op.load(1, buf ^ 1);
+  read(buf, 0);
   // waves in their main loop go before the other workgroup's first loads and epilogue
   __builtin_amdgcn_s_setprio(1);
-  int cur = 0;
+  int cur = buf;
   for (int64_t st = 0; st < stages; ++st) {
     read(cur, 1);
     mfma_round<SEMI, FMT>(xa[0], xb[0], acc);
     if (st + 1 < stages) {
       stage_sync();
-      if (st + 2 < stages) load(st + 2, cur);
+      if (st + 2 < stages) op.load(st + 2, cur);
       read(cur ^ 1, 0);
     }
     if (st * kWords + 4 < kw) mfma_round<SEMI, FMT>(xa[1], xb[1], acc);  // else only zero words are left
     cur ^= 1;
   }
   __builtin_amdgcn_s_setprio(0);
-  hook.summed();
-  store_tile<SEMI, FMT, RA, RB>(acc, C, ldc, m, n, row0 + wy * 32 * RA,
-                                (col0 >> 6) + wx * (RB / 2), accumulate, semiring);
+}
+
+// Rows [64 RA im, ...) x columns [64 RB in, ...) of C = A B, by the four waves w = 0..3 of
+// a workgroup (all of them call it; every one takes part in loads and barriers).  Needs
+// k < 2^24 and lds_bytes(RA, RB) of LDS, which nobody reads any more when it is called.
+// FAR: pitches of kNearPitch words and more (64-bit row addresses).
+// (Workgroups that took several tiles in turn, the next one's first stage loaded during
+// the last stage of this one, were 7 to 10% slower than one workgroup per tile, which the
+// hardware hands out as CUs come free: 62.8 against 57.8 ms for the n = 65536 recursion.)
+template <int SEMI, int FMT, int RA, int RB, bool FAR>
+__device__ __forceinline__ void tile(const uint64_t* __restrict__ A, int64_t lda,
+                                     const uint64_t* __restrict__ BT, int64_t ldbt, uint64_t* C,
+                                     int64_t ldc, int64_t m, int64_t k, int64_t n, int64_t im,
+                                     int64_t in, int accumulate, int semiring, int w,
+                                     unsigned char* smem) {
+  Operands<RA, RB, FAR> op(A, lda, BT, ldbt, m, k, n, im, in, w, smem);
+  AccV<FMT> acc[RA][RB];
+  op.load(0, 0);
+  sums<SEMI, FMT, RA, RB, FAR>(op, 0, acc);
+  store_tile<SEMI, FMT, RA, RB>(acc, C, ldc, m, n, im * op.TM + (w >> 1) * 32 * RA,
+                                (in * op.TN >> 6) + (w & 1) * (RB / 2), accumulate, semiring);
 }
 
 // ---- small products: k split over a workgroup's waves ----
