@@ -81,6 +81,36 @@ hipError_t launch_rows(const LeafBatch& p, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int SEMI, int FMT, int WX>
+__global__ __launch_bounds__(128 * WX) __attribute__((amdgpu_waves_per_eu(2))) void
+leaf_turn_kernel(LeafBatch p, int64_t grid_m, int64_t grid_n) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[panel::rows_bytes(WX)];
+  const TileCoord c = xcd_tile(blockIdx.x, gridDim.x, grid_m, grid_n);
+  panel::rows_tile<SEMI, FMT, WX>(
+      p.A + c.b * p.strideA, p.lda, p.BT + c.b * p.strideB, p.ldbt, p.C + c.b * p.strideC, p.ldc,
+      p.m, p.k, p.n, c.tm, c.tn, p.accumulate,
+      __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), smem);
+}
+
+template <int SEMI, int FMT, int WX>
+hipError_t launch_turn(const LeafBatch& p, hipStream_t s) {
+  const int64_t grid_m = (p.m + 255) / 256, grid_n = (p.n + 64 * WX - 1) / (64 * WX);
+  const int64_t blocks = grid_m * grid_n * p.batch;
+  if (!grid_fits(blocks, 128 * WX)) return kGridTooLarge;
+  hipLaunchKernelGGL((leaf_turn_kernel<SEMI, FMT, WX>), dim3((unsigned)blocks), dim3(128 * WX), 0,
+                     s, p, grid_m, grid_n);
+  return hipGetLastError();
+}
+
+// E2M1: tiles of 256 columns, a workgroup of eight waves per CU, where there are more than one
+// of 128 columns per CU (k = 32768, n = 65536: 206 against 224 us, n = 32768: 193 and 130); int8
+// always takes 128 (n = 65536: 318 and 297 us).
+template <int SEMI>
+hipError_t launch_turn_f4(const LeafBatch& p, hipStream_t s) {
+  return (p.n + 127) / 128 > 256 ? launch_turn<SEMI, mfma::FMT_F4, 4>(p, s)
+                                 : launch_turn<SEMI, mfma::FMT_F4, 2>(p, s);
+}
+
 }  // namespace
 
 bool leaf_small_tiles(int64_t m, int64_t n, int64_t batch) {
@@ -120,6 +150,28 @@ hipError_t launch_leaf_rows(int semiring, int fmt, const LeafBatch& p, hipStream
                            : launch_rows<BOOLEAN, mfma::FMT_F4>(p, s);
   return semiring == GF2 ? launch_rows<GF2, mfma::FMT_I8>(p, s)
                          : launch_rows<BOOLEAN, mfma::FMT_I8>(p, s);
+}
+
+bool leaf_turn_fits(int64_t m, int64_t k, int64_t n, int64_t lda, int64_t ldb) {
+  // One row of tiles (with two B is turned twice: 512 x 32768 x 65536 gains 9%, 1024 rows
+  // lose) of more than half a tile's rows (m = 130: 59.5 against 68 us with a transpose and
+  // the other leaves, m = 128: 58 against 50, k = 8192, n = 65536); and tiles of 128 columns
+  // that fill the CUs, one or two on each, in every round (k = 8192: n = 57344, 7/8 of a
+  // round, 56 against 64 us; 49152 equal; 81920 110 against 86; k = 32768: 32768, half a
+  // round, 129 against 149 us, 16384 152 against 84).
+  const int64_t tiles = (n + 127) / 128;
+  const int64_t round = tiles <= 256 ? 256 : 512;
+  return m > 128 && m <= 256 && k < panel::kMaxK && lda < kNearPitch && ldb < kNearPitch &&
+         8 * tiles >= 7 * round * ((tiles + round - 1) / round);
+}
+
+hipError_t launch_leaf_turn(int semiring, int fmt, const LeafBatch& p, hipStream_t s) {
+  if (p.m <= 0 || p.n <= 0 || p.batch <= 0) return hipSuccess;
+  if (p.k <= 0 || !leaf_turn_fits(p.m, p.k, p.n, p.lda, p.ldbt)) return hipErrorInvalidValue;
+  if (fmt == mfma::FMT_F4)
+    return semiring == GF2 ? launch_turn_f4<GF2>(p, s) : launch_turn_f4<BOOLEAN>(p, s);
+  return semiring == GF2 ? launch_turn<GF2, mfma::FMT_I8, 2>(p, s)
+                         : launch_turn<BOOLEAN, mfma::FMT_I8, 2>(p, s);
 }
 
 hipError_t launch_leaf_panel(int semiring, int fmt, const LeafBatch& p, hipStream_t s) {

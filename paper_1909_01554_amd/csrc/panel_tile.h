@@ -420,6 +420,169 @@ __device__ __forceinline__ void tile(const uint64_t* __restrict__ A, int64_t lda
                                 (in * op.TN >> 6) + (w & 1) * (RB / 2), accumulate, semiring);
 }
 
+// ---- few rows: B row-major, turned on its way through LDS ----
+
+// Rows [256 im, ...) x columns [64 WX in, ...) of C = A B, B given row-major, by a workgroup of
+// 2 x WX waves of 128 x 64.  A's rows are staged as above, B's as they lie (the 512 rows of a
+// stage, WX words each), loaded four stages before the products they are for; two stages
+// before, every wave turns four of the 64 x 64 blocks in registers (31 VALU instructions
+// each) into the columns' rows.  So B is read once where one row of tiles covers C, and is
+// never copied.  Bound by the VALU work of the turns, which the matrix cores hide in part:
+// the two waves of a SIMD turn at different times, one before its round and one after (m =
+// 256, k = 32768, n = 65536, fp4: 206 us, all at once 211, rows loaded a stage later 221;
+// a transpose of B and the panel leaf 309).
+// 0 < k < 2^24, pitches below kNearPitch, n of at least WX words; smem: rows_bytes(WX).
+constexpr int rows_bytes(int WX) { return (2 * 256 + 5 * 64 * WX) * kRowBytes; }
+
+__device__ __forceinline__ void rows_sync() {  // all but the wave's last two loads
+  asm volatile("s_waitcnt vmcnt(2) lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+template <int SEMI, int FMT, int WX>
+__device__ __forceinline__ void rows_tile(const uint64_t* __restrict__ A, int64_t lda,
+                                          const uint64_t* __restrict__ B, int64_t ldb, uint64_t* C,
+                                          int64_t ldc, int64_t m, int64_t k, int64_t n, int64_t im,
+                                          int64_t in, int accumulate, int w, unsigned char* smem) {
+  constexpr int NW = 2 * WX, NL = 16 / NW, RA = 4, RB = 2;
+  constexpr int kA = 256 * kRowBytes, kB = 64 * WX * kRowBytes;  // bytes of a stage
+  constexpr int kRaw = 2 * kA, kTurned = kRaw + 3 * kB;          // where they start
+  const int wy = w / WX, wx = w % WX;
+  const int kw = (int)((k + 63) >> 6), stages = (kw + kWords - 1) / kWords;
+  const int64_t row0 = im * 256, nw = (n + 63) >> 6;
+  const int64_t word0 = in * WX < nw - WX ? in * WX : nw - WX;  // of the words read
+  const int shift = (int)(in * WX - word0);
+  const uint64_t* Ab = A + row0 * lda;
+  const uint64_t* Bb = B + word0;
+  typedef __attribute__((address_space(3))) unsigned char* lds_ptr;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr)smem;
+
+  auto chunk_of = [](int ln) { return (ln & 3) ^ ((ln >> 3) & 3); };
+  uint32_t voff[NL];
+  {
+    const int lane = fresh_lane();
+    const int64_t lim = m - 1 - row0;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      int r = 16 * (NW * i + w) + (lane >> 2);
+      r = r < lim ? r : (int)lim;
+      voff[i] = (uint32_t)r * ((uint32_t)lda * 8) + 16 * chunk_of(lane);
+    }
+  }
+  auto load_a = [&](int st, int buf) {
+    const int w0 = st * kWords;
+    if (w0 + kWords <= kw) {
+#pragma unroll
+      for (int i = 0; i < NL; ++i)
+        load_lds16(Ab + w0, voff[i], lds0 + buf * kA + (NW * i + w) * 1024);
+      return;
+    }
+    // the last, shorter stage: words past the end of k read as zero
+    const int lane = fresh_lane();
+    const int left = kw - w0 - 2 * chunk_of(lane);
+    const int o0 = left > 0 ? 0 : left - 1, o1 = left > 1 ? 1 : left - 1;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const mfma::gq_ptr src = (mfma::gq_ptr)((const char*)(Ab + w0) + voff[i]);
+      const uint64_t x0 = src[o0], x1 = src[o1];
+      ulonglong2 v;
+      v.x = left > 0 ? x0 : 0ull;
+      v.y = left > 1 ? x1 : 0ull;
+      *reinterpret_cast<ulonglong2*>(smem + buf * kA + (NW * i + w) * 1024 + lane * 16) = v;
+    }
+  };
+  // the stage's rows of B: 1 KB of them per load, two loads per wave (rows past the end
+  // of k repeat the last one)
+  auto load_b = [&](int st, int buf) {
+    constexpr int kLanes = WX / 2, kRows = 64 / kLanes;  // lanes per row, rows per load
+    const int lane = fresh_lane();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int64_t r0 = (int64_t)st * 512 + (2 * w + i) * kRows;
+      const int64_t first = r0 < k ? r0 : k - 1;
+      const int64_t lim = k - 1 - first;
+      int r = lane / kLanes;
+      r = r < lim ? r : (int)lim;
+      load_lds16(Bb + first * ldb, (uint32_t)r * ((uint32_t)ldb * 8) + 16 * (lane % kLanes),
+                 lds0 + kRaw + buf * kB + (2 * w + i) * 1024);
+    }
+  };
+  // four blocks of stage st: word wx, rows 64 (4 wy + j)
+  auto turn = [&](int st, int from, int buf) {
+    const int c = fresh_lane();
+    const Transpose tr(c);
+    const int word = wx + shift < WX ? wx + shift : WX - 1;
+    const unsigned char* raw = smem + kRaw + from * kB + (256 * wy + c) * (8 * WX) + 8 * word;
+    unsigned char* out = smem + kTurned + buf * kB + (64 * wx + c) * kRowBytes;
+    const int64_t left = k - ((int64_t)st * 512 + 256 * wy + c);  // rows from lane's first on
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      ulonglong2 v;
+      uint64_t x = *reinterpret_cast<const uint64_t*>(raw + (2 * q) * 64 * 8 * WX);
+      v.x = transpose64(left > 128 * q ? x : 0ull, tr);
+      x = *reinterpret_cast<const uint64_t*>(raw + (2 * q + 1) * 64 * 8 * WX);
+      v.y = transpose64(left > 128 * q + 64 ? x : 0ull, tr);
+      *reinterpret_cast<ulonglong2*>(out + (((2 * wy + q) ^ ((c >> 1) & 3)) * 16)) = v;
+    }
+  };
+
+  const int lane = fresh_lane(), half = lane >> 5, li = lane & 31;
+  const int slot = (half ^ ((li >> 1) & 3)) * 16;
+  const int abase = (wy * 32 * RA + li) * kRowBytes + slot;
+  const int bbase = (wx * 32 * RB + li) * kRowBytes + slot;
+  u4 xa[2][RA], xb[2][RB];
+  auto read = [&](int buf, int s) {
+#pragma unroll
+    for (int f = 0; f < RA; ++f)
+      xa[s][f] = *reinterpret_cast<const u4*>(smem + buf * kA + (abase ^ (32 * s)) + 2048 * f);
+#pragma unroll
+    for (int g = 0; g < RB; ++g)
+      xb[s][g] = *reinterpret_cast<const u4*>(smem + kTurned + buf * kB + (bbase ^ (32 * s)) +
+                                              2048 * g);
+  };
+  AccV<FMT> acc[RA][RB];
+#pragma unroll
+  for (int f = 0; f < RA; ++f)
+#pragma unroll
+    for (int g = 0; g < RB; ++g) acc[f][g] = AccV<FMT>{};
+  load_b(0, 0);
+  load_a(0, 0);
+  if (stages > 1) load_b(1, 1);
+  stage_sync();
+  if (stages > 2) load_b(2, 2);
+  turn(0, 0, 0);
+  rows_sync();
+  if (stages > 1) load_a(1, 1);
+  if (stages > 3) load_b(3, 0);
+  read(0, 0);
+  if (stages > 1) turn(1, 1, 1);
+  __builtin_amdgcn_s_setprio(1);
+  int cur = 0, third = 2;  // the buffers of stage st, and of st + 2's rows of B
+  for (int st = 0; st < stages; ++st) {
+    read(cur, 1);
+    mfma_round<SEMI, FMT>(xa[0], xb[0], acc);
+    if (st + 1 < stages) {
+      // stage st's operands are in registers, st + 1's and st + 2's rows of B have come
+      // (st + 3's, if there are any, are this wave's last two loads and on their way)
+      if (st + 3 < stages) rows_sync();
+      else stage_sync();
+      const int fourth = third == 0 ? 2 : third - 1;  // of stage st + 1 and st + 4
+      if (st + 2 < stages) load_a(st + 2, cur);
+      if (st + 4 < stages) load_b(st + 4, fourth);
+      read(cur ^ 1, 0);
+      if (st + 2 < stages && wy == 0) turn(st + 2, third, cur);
+    }
+    if (st * kWords + 4 < kw) mfma_round<SEMI, FMT>(xa[1], xb[1], acc);
+    if (st + 2 < stages && wy != 0) turn(st + 2, third, cur);
+    third = third == 2 ? 0 : third + 1;
+    cur ^= 1;
+  }
+  __builtin_amdgcn_s_setprio(0);
+  store_tile<SEMI, FMT, RA, RB>(acc, C, ldc, m, n, row0 + wy * 32 * RA, in * WX + wx, accumulate,
+                                SEMI);
+}
+
 // ---- small products: k split over a workgroup's waves ----
 
 // Rows [64 im, ...) x columns [64 in, ...) of C = A B by W waves that share the tile and
