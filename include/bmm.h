@@ -328,7 +328,9 @@ int bmm_compress(int levels, int scheme, const uint64_t* src, uint64_t* dst, int
  * the VALU leaf, per wave for the matrix-core leaves).  The VALU leaf's tile 1 is the
  * dot-product form against B^T (128 x 128); tile 2 is the outer-product form (512 x
  * 1024): each bit of A selects a row of B, whose words the waves read from LDS at one
- * address per wave, and the accumulators are the result bits.  Tile 2 reads B row-major, so it
+ * address per wave, and the accumulators are the result bits; where C is large enough, each
+ * byte of A selects one of the 256 sums of 8 rows of B that a workgroup holds in LDS (1024 x
+ * 1024).  Tile 2 reads B row-major, so it
  * serves the cubic products only (a B passed transposed is transposed back into
  * scratch first); batched leaves (the recursion, bmm_batched) given VALU tile 2 run
  * tile 1. */

@@ -1020,9 +1020,11 @@ int bmm_autotune_leaf(int semiring, int64_t m, int64_t k, int64_t n, int64_t bat
     if (rc != BMM_OK) break;
     LeafBatch p{A, kw, m * kw, BT, kw, n * kw, C, nw, m * nw, m, k, n, nb, 0};
     auto launch = [&, leaf = leaf, tile = tile]() {
-      if (leaf == BMM_LEAF_VALU && tile == 2)
-        return check_hip(launch_leaf_valu_outer(semiring, A, kw, BT, nw, C, nw, m, k, n, 0,
-                                                nullptr), "leaf launch");
+      if (leaf == BMM_LEAF_VALU && tile == 2) {
+        const auto form =
+            leaf_valu_table_fits(m, n) ? launch_leaf_valu_table : launch_leaf_valu_outer;
+        return check_hip(form(semiring, A, kw, BT, nw, C, nw, m, k, n, 0, nullptr), "leaf launch");
+      }
       return run_leaf(semiring, leaf, tile, p, nullptr);
     };
     // a timed warm-up; launches longer than 0.2 s are timed once, shorter ones 3 more times

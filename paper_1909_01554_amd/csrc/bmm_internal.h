@@ -107,11 +107,11 @@ hipError_t launch_leaf_small(int semiring, int fmt, const LeafBatch& p, bool spl
 // The k-split form on B given row-major (p.BT points at B, k x n, pitch p.ldbt), so that a
 // small product is one launch; leaf_rows_fits: where this is the faster way.
 hipError_t launch_leaf_rows(int semiring, int fmt, const LeafBatch& p, hipStream_t s);
+bool leaf_rows_fits(int64_t m, int64_t k, int64_t n);
 // Few rows times a row-major B (p.BT: B itself, p.ldbt its pitch) without a transposed copy,
 // and the shapes it is for.
 bool leaf_turn_fits(int64_t m, int64_t k, int64_t n, int64_t lda, int64_t ldb);
 hipError_t launch_leaf_turn(int semiring, int fmt, const LeafBatch& p, hipStream_t s);
-bool leaf_rows_fits(int64_t m, int64_t k, int64_t n);
 // Whether a batch of m x n results is small in this sense.
 bool leaf_small_tiles(int64_t m, int64_t n, int64_t batch);
 hipError_t launch_leaf_valu(int semiring, const LeafBatch& p, int tile, hipStream_t s);

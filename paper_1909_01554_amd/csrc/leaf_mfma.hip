@@ -1,21 +1,19 @@
-// Cubic leaf product on the int8 matrix cores of gfx950.
+// Cubic leaf product on the matrix cores of gfx950: which kernel runs a tile choice, and the
+// two int8 forms fed from registers (every other one is the panel leaf).
 //
 // The cubic product C[i][k] = SUM_j A[i][j] B[j][k] (GF(2): XOR, Boolean: OR)
 // is an integer dot product reduced at the end: the int32 count of j with
 // A[i][j] = B[j][k] = 1 gives the GF(2) bit as its parity and the Boolean bit
 // as (count > 0).  Counts stay exact because k < 2^31.
 //
-// Each wave owns a TM x TN tile of C (TM = 32*RA, TN = 32*RB) and issues
+// In the kernel here each wave owns a TM x TN tile of C (TM = 32*RA, TN = 32*RB) and issues
 // v_mfma_i32_32x32x32_i8 on RA x RB accumulator blocks held in registers.
 // Operands never touch HBM as bytes: every lane reads 64-bit words of packed
 // bits straight from its row of A (or of B transposed) and expands them in
 // registers.  The order of k inside a dot product is free as long as A and B
 // use the same one, so a 32-bit half x of a word yields the eight dwords
 // (x >> d) & 0x01010101 (d = 0..7): byte e of dword d is bit 8e + d of x, 0 or
-// 1 (for one side of the tile both halves at once, from a 64-bit shift).  GF(2) parity alone would only need the low bit of each byte, but
-// operand bytes holding the other random bits too make the matrix cores
-// switch far more on dense inputs and run at a lower rate, so both semirings
-// feed exact 0/1 bytes.
+// 1 (for one side of the tile both halves at once, from a 64-bit shift).
 //
 // The result bits go back to packed rows with wave ballots: accumulator
 // register v of a 32x32 block holds row 8*(v/4) + (v%4) in lanes 0..31 and
@@ -33,22 +31,22 @@ bool aligned16(const LeafBatch& p) {
 
 // Each workgroup owns 2 x 2 wave tiles; workgroups are ordered for L2 reuse per XCD.
 template <int SEMI, int RA, int RB, int KV, int FMT, int NB = 2, int STEPS = 0, bool WIDE = true,
-          bool SHORT = false, bool BOTH = false>
+          bool UNIFORM = false, bool BOTH = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void leaf_mfma_kernel(
     LeafBatch p, int64_t tiles_m, int64_t tiles_n) {
   const int64_t grid_m = (tiles_m + 1) >> 1, grid_n = (tiles_n + 1) >> 1;
   const TileCoord c = xcd_tile(blockIdx.x, gridDim.x, grid_m, grid_n);
-  // The wide tiles take the wave index as a uniform value (their tile coordinates then
-  // live in scalar registers, which frees the vector registers the long-k loop spilled);
-  // the narrower tiles keep the per-lane form, measured faster on the recursion's leaves.
-  const int w = RB == 4 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
+  // UNIFORM: the wave index as a uniform value (the tile coordinates then live in scalar
+  // registers, which frees the vector registers the long-k loop spilled); the unrolled tile
+  // keeps the per-lane form, measured faster there.
+  const int w = UNIFORM ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
   const int64_t tm = 2 * c.tm + (w >> 1);
   const int64_t tn = 2 * c.tn + (w & 1);
   if (c.b >= p.batch || tm >= tiles_m || tn >= tiles_n) return;  // uniform per wave
   const int64_t b = c.b;
-  mfma::tile<SEMI, RA, RB, KV, FMT, NB, STEPS, WIDE, SHORT, BOTH>(p.A + b * p.strideA, p.lda, p.BT + b * p.strideB, p.ldbt,
-                                    p.C + b * p.strideC, p.ldc, p.m, p.k, p.n, tm, tn,
-                                    p.accumulate);
+  mfma::tile<SEMI, RA, RB, KV, FMT, NB, STEPS, WIDE, BOTH>(
+      p.A + b * p.strideA, p.lda, p.BT + b * p.strideB, p.ldbt, p.C + b * p.strideC, p.ldc, p.m,
+      p.k, p.n, tm, tn, p.accumulate);
 }
 
 // int8 from k = 2^24 on, where the panel leaf's products of 2^7 would overflow int32 sums:
@@ -64,10 +62,10 @@ hipError_t launch_long(const LeafBatch& p, hipStream_t s) {
   if (!grid_fits(blocks, 256)) return kGridTooLarge;
   const dim3 g((unsigned)blocks), b(256);
   if (aligned16(p))
-    hipLaunchKernelGGL((leaf_mfma_kernel<SEMI, 2, 4, 2, mfma::FMT_I8, 2, -12>), g, b, 0, s, p,
+    hipLaunchKernelGGL((leaf_mfma_kernel<SEMI, 2, 4, 2, mfma::FMT_I8, 2, -12, true, true>), g, b, 0, s, p,
                        tiles_m, tiles_n);
   else
-    hipLaunchKernelGGL((leaf_mfma_kernel<SEMI, 2, 4, 1, mfma::FMT_I8, 2, 0, true, false>), g, b, 0,
+    hipLaunchKernelGGL((leaf_mfma_kernel<SEMI, 2, 4, 1, mfma::FMT_I8, 2, 0, true, true>), g, b, 0,
                        s, p, tiles_m, tiles_n);
   return hipGetLastError();
 }

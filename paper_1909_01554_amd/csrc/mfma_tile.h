@@ -1,5 +1,5 @@
-// Device code of one int8-MFMA leaf tile, shared by the per-launch leaf kernel
-// and the persistent batched kernel.  See leaf_mfma.hip for the method.
+// Device code of one leaf tile fed from registers: the long and the unrolled int8 leaf and
+// batched tiles 1 to 3 (int8 or E2M1).  See leaf_mfma.hip for the method.
 #pragma once
 
 #include "bmm_internal.h"
@@ -66,48 +66,14 @@ __device__ __forceinline__ v4i expand4(uint32_t x, int first) {
   return o;
 }
 
-// WIDE: expand the rows of one side of the tile with 64-bit shifts (below): the longer
-// side, or with SHORT the shorter one, which holds fewer expanded rows in registers.  The
-// LDS-staged 256 x 256 leaf widens its longer side (2-3% faster for E2M1 operands); the
-// batched items widen their shorter side (3% faster for int8, 2% for E2M1; the longer
-// side spills them); the register-fed fp4 tiles keep the 32-bit form, which either wide
-// form would spill.  BOTH (int8): both sides wide, for the recursion's unrolled 128 x 64
-// tile with two load buffers instead of three.
-template <int SEMI, int RA, int RB, int FMT, bool WIDE = true, bool SHORT = false, bool BOTH = false>
+// WIDE (int8): expand the rows of the tile's longer side with 64-bit shifts (below).  The
+// batched items keep the 32-bit form, as the wide one would spill, and so do E2M1 operands.
+// BOTH: both sides wide, for the unrolled 128 x 64 tile with two load buffers instead of
+// three.
+template <int SEMI, int RA, int RB, int FMT, bool WIDE = true, bool BOTH = false>
 __device__ __forceinline__ void mfma_word(const uint64_t (&xa)[RA], const uint64_t (&xb)[RB],
                                           typename Acc<FMT>::type (&acc)[RA][RB]) {
-  if constexpr (FMT == FMT_F4 && WIDE) {
-    // one MFMA per 32-bit half: 32 k values per lane, 64 per instruction; the rows of
-    // the longer side expand both halves at once (a 64-bit shift and two masks give
-    // dword d of each half, where the 32-bit form takes two shifts and two masks)
-    constexpr bool BW = SHORT ? RB < RA : RB >= RA;
-    constexpr int NW = BW ? RB : RA, NN = BW ? RA : RB;
-    v8i ow[2][NW];
-#pragma unroll
-    for (int g = 0; g < NW; ++g) {
-#pragma unroll
-      for (int d = 0; d < 4; ++d) {
-        const uint64_t y = ((BW ? xb[g] : xa[g]) >> d) & 0x1111111111111111ull;
-        ow[0][g][d] = (int)(uint32_t)y;
-        ow[1][g][d] = (int)(uint32_t)(y >> 32);
-      }
-#pragma unroll
-      for (int d = 4; d < 8; ++d) ow[0][g][d] = ow[1][g][d] = 0;
-    }
-#pragma unroll
-    for (int hw = 0; hw < 2; ++hw) {
-      v8i on[NN];
-#pragma unroll
-      for (int f = 0; f < NN; ++f) on[f] = expand_f4((uint32_t)((BW ? xa[f] : xb[f]) >> (32 * hw)));
-#pragma unroll
-      for (int f = 0; f < RA; ++f)
-#pragma unroll
-        for (int g = 0; g < RB; ++g)
-          acc[f][g] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-              BW ? on[f] : ow[hw][f], BW ? ow[hw][g] : on[g], acc[f][g], 4, 4, 0, 127, 0, 127);
-    }
-    return;
-  } else if constexpr (FMT == FMT_F4) {
+  if constexpr (FMT == FMT_F4) {
     // one MFMA per 32-bit half: 32 k values per lane, 64 per instruction
 #pragma unroll
     for (int hw = 0; hw < 2; ++hw) {
@@ -173,12 +139,12 @@ __device__ __forceinline__ void mfma_word(const uint64_t (&xa)[RA], const uint64
                                                                 0, 0, 0);
         continue;
       }
-      // The rows of one side (the longer, or with SHORT the shorter) expand both 32-bit
+      // The rows of the longer side expand both 32-bit
       // halves of a word at once: one 64-bit shift and two masks give dword d of each
       // half, where the 32-bit form takes two shifts and two masks.  Holding both halves
       // for every row would need more registers than two waves per SIMD leave, so the
       // other side stays 32-bit.
-      constexpr bool BW = SHORT ? RB < RA : RB >= RA;
+      constexpr bool BW = RB >= RA;
       v4i ow[2][BW ? RB : RA];
 #pragma unroll
       for (int g = 0; g < (BW ? RB : RA); ++g)
@@ -333,7 +299,7 @@ __device__ __forceinline__ void epilogue(const typename Acc<FMT>::type (&acc)[RA
 // compiler knows every load in flight, and NB register buffers keep the words
 // of step st + NB - 1 in flight while step st computes.
 template <int SEMI, int RA, int RB, int KV, int FMT, int NB = 2, int STEPS = 0, bool WIDE = true,
-          bool SHORT = false, bool BOTH = false>
+          bool BOTH = false>
 __device__ __forceinline__ void tile(const uint64_t* __restrict__ A, int64_t lda,
                                      const uint64_t* __restrict__ BT, int64_t ldbt,
                                      uint64_t* __restrict__ Cm, int64_t ldc, int64_t m,
@@ -398,7 +364,7 @@ __device__ __forceinline__ void tile(const uint64_t* __restrict__ A, int64_t lda
   };
   auto compute = [&](const uint64_t (&xa)[KV][RA], const uint64_t (&xb)[KV][RB]) {
 #pragma unroll
-    for (int v = 0; v < KV; ++v) mfma_word<SEMI, RA, RB, FMT, WIDE, SHORT, BOTH>(xa[v], xb[v], acc);
+    for (int v = 0; v < KV; ++v) mfma_word<SEMI, RA, RB, FMT, WIDE, BOTH>(xa[v], xb[v], acc);
   };
   if constexpr (STEPS > 0) {
     static_assert(STEPS >= NB, "an unrolled pipeline needs at least NB steps");
@@ -489,7 +455,7 @@ tail:
         for (int f = 0; f < RA; ++f) xa[f] = wi < kw ? arow[f][w - adv + v] : 0ull;
 #pragma unroll
         for (int g = 0; g < RB; ++g) xb[g] = wi < kw ? brow[g][w - adv + v] : 0ull;
-        mfma_word<SEMI, RA, RB, FMT, WIDE, SHORT, BOTH>(xa, xb, acc);
+        mfma_word<SEMI, RA, RB, FMT, WIDE, BOTH>(xa, xb, acc);
       }
     }
   }
