@@ -30,13 +30,13 @@ PEAK_MFMA_F4_TOPS = 10100.0       # dense fp4 (E2M1) MFMA
 PEAK_VALU_SINGLE_TBOPS = 2516.6
 PEAK_VALU_FUSED_TBOPS = 5033.2
 # Bytes that one Boolean leaf launch at n = 2^18 (sparse operands) moves between L2 and
-# memory, for the int8 leaf with the tuned tile (7: 64 x 128, chunked loop, wide operand
-# expansion, 16-byte C stores): reads from rocprofv3's request counts by size (128 x
+# memory, for the int8 leaf with the tuned tile (7, which is the panel leaf: 128 x 256 per
+# workgroup, operand rows in LDS): reads from rocprofv3's request counts by size (128 x
 # TCC_EA0_RDREQ_128B + 64 x TCC_EA0_RDREQ_64B; FETCH_SIZE counts a 128-byte read as 64
 # bytes on this device, which a 4 GiB copy in the same runs shows), writes from
 # WRITE_SIZE (the copy's 4 GiB read back exactly); see
 # profiles/pmc_traffic_leaf_boolean_n262144.md.  Valid for that kernel only.
-MEASURED_TRAFFIC = {("mfma", 7, 1 << 18): 1.76381e11 * 128 + 3.14568e7 * 64 + 1.37406e7 * 1024}
+MEASURED_TRAFFIC = {("mfma", 7, 1 << 18): 6.58905e10 * 128 + 1.94e3 * 64 + 1.03909e7 * 1024}
 
 
 def log(*a):
@@ -944,7 +944,7 @@ def main():
         "f4_leaf": f4,
         "gf2_schemes": schemes,
         "roofline": {"bound": "alu" if args.leaf == "valu" else "mfma",
-                     "kernel": ("leaf_valu_kernel" if args.leaf == "valu" else "leaf_mfma_kernel")
+                     "kernel": ("leaf_valu_kernel" if args.leaf == "valu" else "leaf_panel_kernel")
                                + f" tile {leaf_tile} (Boolean cubic product, one launch per step)",
                      "achieved": round(achieved, 1), "peak": peak,
                      "unit": "TFLOP/s", "frac": round(achieved / peak, 4),

@@ -250,9 +250,9 @@ void bmm_batched_plan_destroy(void* plan);
  * per problem); 0 / AUTO take the autotuner's record for plans of the same problem
  * count and total work (to a factor of two): its choice per size class of k
  * (k < 1024, < 4096, larger) where it recorded one, else its single choice, else the
- * table's auto_leaf (int8 without one) with tile 4.  Problems with the same matrix-core choice share one persistent launch
- * (workgroups per CU from the same record, else 4); a plan's launch enqueues the VALU
- * products, then each persistent group. */
+ * table's auto_leaf (int8 without one) with tile 4.  Problems with the same matrix-core
+ * choice share one persistent launch (workgroups per CU from the same record, else 4; tile
+ * 4 at most 2); a plan's launch enqueues the VALU products, then each persistent group. */
 
 /* Autotuner for batched plans (the paper's empirical parameter choice,
  * section 3.17, applied to the persistent launch): times one launch of the plan
@@ -333,7 +333,10 @@ int bmm_compress(int levels, int scheme, const uint64_t* src, uint64_t* dst, int
  * 1024).  Tile 2 reads B row-major, so it
  * serves the cubic products only (a B passed transposed is transposed back into
  * scratch first); batched leaves (the recursion, bmm_batched) given VALU tile 2 run
- * tile 1. */
+ * tile 1.  Matrix-core tiles 2 and 4 are the forms for small products (4: always 64 x 64
+ * per workgroup with k split over its waves), int8 tile 6 at k = 2048 and 4096 an unrolled
+ * register-fed pipeline; every other number is the panel leaf, which picks its shape
+ * itself.  With tile = 0 a product of 129 to 256 rows may read a row-major B directly. */
 int bmm_leaf_tiles(int leaf, int* count_out);
 int bmm_leaf_tile_shape(int leaf, int tile, int* rows_out, int* cols_out);
 /* The leaf kind and tile a cubic product (batch = 1) or a batch of equal leaf
