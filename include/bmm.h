@@ -336,7 +336,7 @@ int bmm_compress(int levels, int scheme, const uint64_t* src, uint64_t* dst, int
  * tile 1.  Matrix-core tiles 2 and 4 are the forms for small products (4: always 64 x 64
  * per workgroup with k split over its waves), int8 tile 6 at k = 2048 and 4096 an unrolled
  * register-fed pipeline; every other number is the panel leaf, which picks its shape
- * itself.  With tile = 0 a product of 129 to 256 rows may read a row-major B directly. */
+ * itself.  With tile = 0 a product of up to 512 rows may read a row-major B directly. */
 int bmm_leaf_tiles(int leaf, int* count_out);
 int bmm_leaf_tile_shape(int leaf, int tile, int* rows_out, int* cols_out);
 /* The leaf kind and tile a cubic product (batch = 1) or a batch of equal leaf

@@ -298,7 +298,8 @@ int cubic_product(int semiring, const uint64_t* A, int64_t lda, const uint64_t* 
     return check_hip(launch_leaf_rows(semiring, leaf == BMM_LEAF_MFMA_F4 ? 1 : 0, p, s),
                      "leaf launch");
   }
-  // so does one of few rows, whose time a transpose of B would be, unless a tile is asked for
+  // so does one of few rows, for which a transpose of B would be much of the time, unless a
+  // tile is asked for
   if (stage && (leaf == BMM_LEAF_MFMA_I8 || leaf == BMM_LEAF_MFMA_F4) && o.tile <= 0 &&
       panel >= k && leaf_turn_fits(m, k, n, lda, ldb)) {
     LeafBatch p{A, lda, 0, B, ldb, 0, C, ldc, 0, m, k, n, 1, acc ? 1 : 0};

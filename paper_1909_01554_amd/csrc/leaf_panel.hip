@@ -102,13 +102,14 @@ hipError_t launch_turn(const LeafBatch& p, hipStream_t s) {
   return hipGetLastError();
 }
 
-// E2M1: tiles of 256 columns, a workgroup of eight waves per CU, where there are more than one
-// of 128 columns per CU (k = 32768, n = 65536: 206 against 224 us, n = 32768: 193 and 130); int8
-// always takes 128 (n = 65536: 318 and 297 us).
+// E2M1: workgroups of eight waves and 256 columns, one per CU, where there are more than one
+// tile of 128 columns per CU (256 x 32768 x 65536 as called: 204 against 212 us); int8 always
+// takes 128 columns (318 against 297 us).
 template <int SEMI>
 hipError_t launch_turn_f4(const LeafBatch& p, hipStream_t s) {
-  return (p.n + 127) / 128 > 256 ? launch_turn<SEMI, mfma::FMT_F4, 4>(p, s)
-                                 : launch_turn<SEMI, mfma::FMT_F4, 2>(p, s);
+  return ((p.m + 255) / 256) * ((p.n + 127) / 128) > 256
+             ? launch_turn<SEMI, mfma::FMT_F4, 4>(p, s)
+             : launch_turn<SEMI, mfma::FMT_F4, 2>(p, s);
 }
 
 }  // namespace
@@ -153,16 +154,16 @@ hipError_t launch_leaf_rows(int semiring, int fmt, const LeafBatch& p, hipStream
 }
 
 bool leaf_turn_fits(int64_t m, int64_t k, int64_t n, int64_t lda, int64_t ldb) {
-  // One row of tiles (with two B is turned twice: 512 x 32768 x 65536 gains 9%, 1024 rows
-  // lose) of more than half a tile's rows (m = 130: 59.5 against 68 us with a transpose and
-  // the other leaves, m = 128: 58 against 50, k = 8192, n = 65536); and tiles of 128 columns
-  // that fill the CUs, one or two on each, in every round (k = 8192: n = 57344, 7/8 of a
-  // round, 56 against 64 us; 49152 equal; 81920 110 against 86; k = 32768: 32768, half a
-  // round, 129 against 149 us, 16384 152 against 84).
-  const int64_t tiles = (n + 127) / 128;
-  const int64_t round = tiles <= 256 ? 256 : 512;
-  return m > 128 && m <= 256 && k < panel::kMaxK && lda < kNearPitch && ldb < kNearPitch &&
-         8 * tiles >= 7 * round * ((tiles + round - 1) / round);
+  // Every row of tiles turns B again, so one or two of them (m = 512: 409 against 444 us with
+  // a transpose and the panel leaf, k = 32768, n = 65536; m = 1024: 734 and 728), the last
+  // more than half full (k = 8192, n = 65536: m = 130 52 against 64 us, m = 128 53 against 49).
+  // Tiles that fill the CUs, one on each or two, in the last round (k = 8192, m = 256: 192
+  // tiles 33.6 against 36.3 us, 448 53 and 63, 640 77 and 83, but 128 32.3 and 31.1, in int8
+  // 384 75.6 and 73.1).
+  const int64_t rows = (m + 255) / 256, tiles = rows * ((n + 127) / 128), last = tiles % 512;
+  return rows <= 2 && m > 256 * rows - 128 && tiles >= 192 && k < panel::kMaxK &&
+         lda < kNearPitch && ldb < kNearPitch &&
+         (last == 0 || (last >= 192 && last <= 256) || last >= 448 || tiles > 4096);
 }
 
 hipError_t launch_leaf_turn(int semiring, int fmt, const LeafBatch& p, hipStream_t s) {

@@ -427,10 +427,10 @@ __device__ __forceinline__ void tile(const uint64_t* __restrict__ A, int64_t lda
 // stage, WX words each), loaded four stages before the products they are for; two stages
 // before, every wave turns four of the 64 x 64 blocks in registers (31 VALU instructions
 // each) into the columns' rows.  So B is read once where one row of tiles covers C, and is
-// never copied.  Bound by the VALU work of the turns, which the matrix cores hide in part:
-// the two waves of a SIMD turn at different times, one before its round and one after (m =
-// 256, k = 32768, n = 65536, fp4: 206 us, all at once 211, rows loaded a stage later 221;
-// a transpose of B and the panel leaf 309).
+// never copied.  Bound by the VALU work of the turns and planes beside the matrix
+// instructions, among which the compiler spreads them (one run of code, without branches:
+// m = 256, k = 32768, n = 32768, fp4 117 us, with the turns before the products of their own
+// 129; n = 65536, dense bits, 225 and 236 us, a transpose of B and the panel leaf 303).
 // 0 < k < 2^24, pitches below kNearPitch, n of at least WX words; smem: rows_bytes(WX).
 constexpr int rows_bytes(int WX) { return (2 * 256 + 5 * 64 * WX) * kRowBytes; }
 
@@ -558,24 +558,31 @@ __device__ __forceinline__ void rows_tile(const uint64_t* __restrict__ A, int64_
   read(0, 0);
   if (stages > 1) turn(1, 1, 1);
   __builtin_amdgcn_s_setprio(1);
-  int cur = 0, third = 2;  // the buffers of stage st, and of st + 2's rows of B
-  for (int st = 0; st < stages; ++st) {
+  int cur = 0, third = 2, st = 0;  // the buffers of stage st, and of st + 2's rows of B
+  for (; st + 2 < stages; ++st) {
+    read(cur, 1);
+    mfma_round<SEMI, FMT>(xa[0], xb[0], acc);
+    // stage st's operands are in registers, st + 1's and st + 2's rows of B have come
+    // (st + 3's, if there are any, are this wave's last two loads and on their way)
+    if (st + 3 < stages) rows_sync();
+    else stage_sync();
+    const int fourth = third == 0 ? 2 : third - 1;  // of stage st + 1 and st + 4
+    load_a(st + 2, cur);
+    if (st + 4 < stages) load_b(st + 4, fourth);
+    read(cur ^ 1, 0);
+    turn(st + 2, third, cur);
+    mfma_round<SEMI, FMT>(xa[1], xb[1], acc);
+    third = third == 2 ? 0 : third + 1;
+    cur ^= 1;
+  }
+  for (; st < stages; ++st) {
     read(cur, 1);
     mfma_round<SEMI, FMT>(xa[0], xb[0], acc);
     if (st + 1 < stages) {
-      // stage st's operands are in registers, st + 1's and st + 2's rows of B have come
-      // (st + 3's, if there are any, are this wave's last two loads and on their way)
-      if (st + 3 < stages) rows_sync();
-      else stage_sync();
-      const int fourth = third == 0 ? 2 : third - 1;  // of stage st + 1 and st + 4
-      if (st + 2 < stages) load_a(st + 2, cur);
-      if (st + 4 < stages) load_b(st + 4, fourth);
+      stage_sync();
       read(cur ^ 1, 0);
-      if (st + 2 < stages && wy == 0) turn(st + 2, third, cur);
     }
-    if (st * kWords + 4 < kw) mfma_round<SEMI, FMT>(xa[1], xb[1], acc);
-    if (st + 2 < stages && wy != 0) turn(st + 2, third, cur);
-    third = third == 2 ? 0 : third + 1;
+    if (st * kWords + 4 < kw) mfma_round<SEMI, FMT>(xa[1], xb[1], acc);  // else only zero words are left
     cur ^= 1;
   }
   __builtin_amdgcn_s_setprio(0);

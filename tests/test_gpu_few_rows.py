@@ -9,12 +9,12 @@ from gpu_util import announce, empty_dev, from_dev, to_dev, words
 
 pytestmark = pytest.mark.gpu
 
-# n: up to 256 column tiles of 128 (E2M1 takes these narrow) and 448 and more (wide), whole
-# and ragged, the last wide tile one word or less; k: a bit, part of a word, of a stage, whole
-# stages, 1 to 6; the last two are just outside of what this leaf takes
-SHAPES = [(129, 1, 32641), (256, 64, 32768), (255, 512, 57217), (129, 513, 57345),
-          (200, 1000, 65536), (256, 1024, 57409), (200, 1537, 32700), (130, 2113, 57472),
-          (256, 3072, 57600), (128, 600, 65536), (256, 600, 32769)]
+# one and two rows of tiles; 192 to 256 tiles, 448 to 512 and more, whole and ragged, the last
+# tile one word or less; k: a bit, part of a word, of a stage, whole stages, 1 to 6; the last
+# three are just outside of what this leaf takes
+SHAPES = [(129, 1, 24449), (256, 64, 32768), (255, 512, 57217), (129, 513, 57345),
+          (200, 1000, 65536), (400, 1024, 12290), (512, 1537, 16384), (385, 2113, 28740),
+          (256, 3072, 57600), (128, 600, 65536), (256, 600, 32769), (384, 600, 16384)]
 
 
 @pytest.fixture(scope="module")
