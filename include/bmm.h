@@ -331,8 +331,8 @@ int bmm_compress(int levels, int scheme, const uint64_t* src, uint64_t* dst, int
  * address per wave, and the accumulators are the result bits; where C is large enough, each
  * byte of A selects one of the 256 sums of 8 rows of B that a workgroup holds in LDS (1024 x
  * 1024).  Tile 2 reads B row-major, so it
- * serves the cubic products only (a B passed transposed is transposed back into
- * scratch first); batched leaves (the recursion, bmm_batched) given VALU tile 2 run
+ * serves the cubic products only (where it is named for a B passed transposed, B is
+ * transposed back into scratch first; no automatic choice does that); batched leaves (the recursion, bmm_batched) given VALU tile 2 run
  * tile 1.  Matrix-core tiles 2 and 4 are the forms for small products (4: always 64 x 64
  * per workgroup with k split over its waves), int8 tile 6 at k = 2048 and 4096 an unrolled
  * register-fed pipeline; every other number is the panel leaf, which picks its shape

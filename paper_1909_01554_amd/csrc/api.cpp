@@ -174,17 +174,23 @@ int auto_leaf_locked(int64_t k) {
   return leaf == BMM_LEAF_MFMA_F4 && k >= kPanelMaxK ? BMM_LEAF_MFMA_I8 : leaf;
 }
 
-// row_major: the product may read B row-major (the VALU leaf's tile 2).
+// row_major: the product may read B row-major (the VALU leaf's tile 2).  Where B is passed
+// transposed only the caller names that tile: it would turn B back into the scratch buffer
+// that calls on other streams share, and B^T is what they pass to keep out of it.
 void pick_leaf(int semiring, int64_t m, int64_t k, int64_t n, int64_t batch,
                const bmm_options& o, int* leaf, int* tile, bool row_major = false) {
   *leaf = o.leaf;
   *tile = o.tile;
+  const bool b_t = (o.flags & BMM_FLAG_B_TRANSPOSED) != 0;
   if (*leaf == BMM_LEAF_AUTO || *tile <= 0) {
     std::lock_guard<std::mutex> lock(g_mu);
     auto it = g_tune.find({semiring, m, k, n, batch_bucket(batch)});
     if (it != g_tune.end()) {
       if (*leaf == BMM_LEAF_AUTO && it->second.best_leaf > 0) *leaf = it->second.best_leaf;
-      if (*tile <= 0 && *leaf >= 1 && *leaf <= 3) *tile = it->second.tile[*leaf];
+      if (*tile <= 0 && *leaf >= 1 && *leaf <= 3) {
+        *tile = it->second.tile[*leaf];
+        if (*leaf == BMM_LEAF_VALU && *tile == 2 && b_t) *tile = 1;
+      }
     }
     if (*leaf == BMM_LEAF_AUTO) *leaf = auto_leaf_locked(k);
   }
@@ -192,7 +198,8 @@ void pick_leaf(int semiring, int64_t m, int64_t k, int64_t n, int64_t batch,
     // default tile for shapes the table lacks.  VALU: tables of B's rows for large cubic
     // products, else the dot-product form; MFMA: small tiles where large ones would leave
     // CUs idle, else the panel leaf (under the numbers of the long-k tiles for long k)
-    if (*leaf == BMM_LEAF_VALU) *tile = row_major && leaf_valu_table_fits(m, n) ? 2 : 1;
+    if (*leaf == BMM_LEAF_VALU)
+      *tile = row_major && !b_t && leaf_valu_table_fits(m, n) ? 2 : 1;
     else if (leaf_small_tiles(m, n, batch)) *tile = 2;
     else if (*leaf == BMM_LEAF_MFMA_I8 && k >= 8192) *tile = 7;
     else if (*leaf == BMM_LEAF_MFMA_F4 && k >= 4096) *tile = 5;
