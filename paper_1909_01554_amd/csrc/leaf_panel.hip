@@ -45,6 +45,7 @@ hipError_t launch_semi(const LeafBatch& p, hipStream_t s) {
 }
 
 constexpr int kSplit = 4;  // waves that share a 64 x 64 tile
+static_assert(64 * kSplit == 256, "every workgroup here has 256 threads (grid_fits)");
 
 template <int SEMI, int FMT, bool BT>
 __global__ __launch_bounds__(64 * kSplit) __attribute__((amdgpu_waves_per_eu(2))) void
@@ -59,13 +60,14 @@ leaf_split_kernel(LeafBatch p, int64_t grid_m, int64_t grid_n) {
 
 template <int SEMI, int FMT>
 hipError_t launch_small(const LeafBatch& p, bool split, hipStream_t s) {
-  const int64_t grid_m = (p.m + 63) / 64, grid_n = (p.n + 63) / 64;
-  const int64_t blocks = grid_m * grid_n * p.batch;
+  auto tiles = [&](int64_t r) { return ((p.m + r - 1) / r) * ((p.n + r - 1) / r) * p.batch; };
+  const int64_t grid_m = (p.m + 63) / 64, grid_n = (p.n + 63) / 64, blocks = tiles(64);
   // up to 512 tiles of 64 x 64, two workgroups per CU, the split form is the faster one
   // (512: 10.3 against 16.7 us; 1024, at n = 2048: 9.8 against 8.1 us)
-  if (!split && blocks > 512 && p.lda < kNearPitch && p.ldbt < kNearPitch)
-    return launch_shape<SEMI, FMT, 2, 2, false>(p, s);
-  if (!grid_fits(blocks, 64 * kSplit)) return kGridTooLarge;
+  const bool large = !split && blocks > 512 && p.lda < kNearPitch && p.ldbt < kNearPitch;
+  // past the largest launch of these tiles (64 x 64: 2^36 bits of C) the panel's
+  if (!grid_fits(large ? tiles(128) : blocks, 256)) return launch_semi<SEMI, FMT>(p, s);
+  if (large) return launch_shape<SEMI, FMT, 2, 2, false>(p, s);
   hipLaunchKernelGGL((leaf_split_kernel<SEMI, FMT, true>), dim3((unsigned)blocks),
                      dim3(64 * kSplit), 0, s, p, grid_m, grid_n);
   return hipGetLastError();

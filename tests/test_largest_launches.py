@@ -1,0 +1,47 @@
+"""The largest results a named matrix-core tile is launched for.  Only the host's checks run:
+the calls are made in a child without a device, on addresses that are never read."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+CHILD = """
+import ctypes, sys
+import torch
+if torch.cuda.device_count():
+    sys.exit(77)
+import paper_1909_01554_amd as bmm
+m, k, n = (int(x) for x in sys.argv[1:4])
+o = bmm.Options(leaf=int(sys.argv[4]), tile=int(sys.argv[5]), flags=bmm.FLAG_B_TRANSPOSED)
+vp, base = ctypes.c_void_p, 1 << 44
+rc = bmm._c_gf2(vp(base), k // 64, vp(2 * base), k // 64, vp(3 * base), n // 64, m, k, n,
+                ctypes.byref(o), None)
+print(rc, bmm._c_last_error().decode())
+"""
+
+
+def status(m, k, n, leaf, tile):
+    env = dict(os.environ, HIP_VISIBLE_DEVICES="-1", CUDA_VISIBLE_DEVICES="-1")
+    r = subprocess.run([sys.executable, "-c", CHILD] + [str(x) for x in (m, k, n, leaf, tile)],
+                       cwd=ROOT, env=env, capture_output=True, text=True, timeout=300)
+    if r.returncode == 77:
+        pytest.skip("devices cannot be hidden")
+    assert r.returncode == 0, r.stderr[-2000:]
+    rc, message = r.stdout.strip().splitlines()[-1].split(" ", 1)
+    assert message.startswith("leaf launch"), r.stdout
+    return int(rc)
+
+
+# 2^24 tiles of 64 x 64 (2^32 work-items), and one more row of them
+@pytest.mark.parametrize("m,n", [(1 << 18, 1 << 18), ((1 << 18) + 1, 1 << 18)])
+@pytest.mark.parametrize("leaf", [2, 3])
+@pytest.mark.parametrize("tile", [2, 4])
+def test_small_tiles_reach_their_launch(m, n, leaf, tile):
+    assert status(m, 64, n, leaf, tile) == -5  # no device: the launch itself fails
+
+
+def test_past_the_panel_tiles_is_refused():
+    assert status(1 << 20, 64, 1 << 19, 3, 4) == -2
