@@ -333,8 +333,9 @@ int bmm_compress(int levels, int scheme, const uint64_t* src, uint64_t* dst, int
  * 1024).  Tile 2 reads B row-major, so it
  * serves the cubic products only (where it is named for a B passed transposed, B is
  * transposed back into scratch first; no automatic choice does that); batched leaves (the recursion, bmm_batched) given VALU tile 2 run
- * tile 1.  Matrix-core tiles 2 and 4 are the forms for small products (4: always 64 x 64
- * per workgroup with k split over its waves), int8 tile 6 at k = 2048 and 4096 an unrolled
+ * tile 1.  Matrix-core tiles 2 and 4 are the forms for small products (64 x 64 per workgroup
+ * with k split over its waves where those are few, with tile 4 also where k is long for
+ * them, else 128 x 128), int8 tile 6 at k = 2048 and 4096 an unrolled
  * register-fed pipeline; every other number is the panel leaf, which picks its shape
  * itself.  With tile = 0 a product of up to 512 rows may read a row-major B directly. */
 int bmm_leaf_tiles(int leaf, int* count_out);

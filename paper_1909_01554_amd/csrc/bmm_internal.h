@@ -83,7 +83,7 @@ __device__ __forceinline__ TileCoord xcd_tile(uint32_t g, uint32_t total, int64_
 }
 
 // MFMA leaf variants (rows x cols of C per wave, or per workgroup for the last and the
-// fifth).  64 x 64 is the panel leaf's small form, 64 x 32 always the one with k split over
+// fifth).  64 x 64 is the panel leaf's small form, 64 x 32 the same by preference with k split over
 // waves, and int8 has the unrolled register-fed 128 x 64 pipeline (k = 2048 and 4096) and,
 // from k = 2^24 on, the chunked 64 x 128 loop; every other choice is the panel leaf, which
 // picks its shape itself.
@@ -102,7 +102,8 @@ constexpr int64_t kNearPitch = (int64_t)1 << 20;
 // or 128 x 64, whichever the shape pads less; k < kPanelMaxK.
 hipError_t launch_leaf_panel(int semiring, int fmt, const LeafBatch& p, hipStream_t s);
 // The same on smaller tiles, for products that would leave CUs idle: 128 x 128 per workgroup,
-// or (split, and where even those are few) 64 x 64 with k split over a workgroup's waves.
+// or (where even those are few; split: while k is long for them) 64 x 64 with k split over a
+// workgroup's waves.
 hipError_t launch_leaf_small(int semiring, int fmt, const LeafBatch& p, bool split, hipStream_t s);
 // The k-split form on B given row-major (p.BT points at B, k x n, pitch p.ldbt), so that a
 // small product is one launch; leaf_rows_fits: where this is the faster way.

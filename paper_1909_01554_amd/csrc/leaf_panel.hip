@@ -63,9 +63,13 @@ hipError_t launch_small(const LeafBatch& p, bool split, hipStream_t s) {
   auto tiles = [&](int64_t r) { return ((p.m + r - 1) / r) * ((p.n + r - 1) / r) * p.batch; };
   const int64_t grid_m = (p.m + 63) / 64, grid_n = (p.n + 63) / 64, blocks = tiles(64);
   // up to 512 tiles of 64 x 64, two workgroups per CU, the split form is the faster one
-  // (512: 10.3 against 16.7 us; 1024, at n = 2048: 9.8 against 8.1 us)
-  const bool large = !split && blocks > 512 && p.lda < kNearPitch && p.ldbt < kNearPitch;
-  // past the largest launch of these tiles (64 x 64: 2^36 bits of C) the panel's
+  // (512: 10.3 against 16.7 us; 1024, at n = 2048: 9.8 against 8.1 us).  Asked for by name it
+  // also takes more tiles while k is long for them (int8, 1500 x 4096 x 1500, 576 tiles, 11.3
+  // against 13.6 us, 2000 x 8192 x 2000, 1024 tiles, 22.7 and 23.6; 2000 x 4096 x 2000 14.1
+  // and 13.6, 7000 x 1500 x 9000, 15510 tiles, 109 and 55).
+  const bool large = blocks > 512 && !(split && p.k >= 6 * blocks) && p.lda < kNearPitch &&
+                     p.ldbt < kNearPitch;
+  // past the largest launch of these tiles the panel's
   if (!grid_fits(large ? tiles(128) : blocks, 256)) return launch_semi<SEMI, FMT>(p, s);
   if (large) return launch_shape<SEMI, FMT, 2, 2, false>(p, s);
   hipLaunchKernelGGL((leaf_split_kernel<SEMI, FMT, true>), dim3((unsigned)blocks),
