@@ -844,12 +844,13 @@ hipError_t to_alt_basis(uint64_t* C, int64_t ldc, int64_t rows, int64_t words, i
   return launch_basis(C, ldc, 0, rows, words, 1, depth, 1, s, scheme, 0);
 }
 
-int strassen_alt_plan(int64_t m, int64_t k, int64_t n, int depth, const bmm_options& o,
-                      size_t* bytes, int* depth_out) {
+int strassen_alt_plan(int64_t m, int64_t k, int64_t n, const bmm_options& o, AltPlan* plan) {
   StrassenPlan P;
-  BMM_TRY(make_plan(m, k, n, depth, o, false, &P, false));
-  *bytes = P.bytes;
-  *depth_out = P.depth;
+  BMM_TRY(make_plan(m, k, n, -1, o, false, &P, false));
+  plan->bytes = P.bytes;
+  plan->depth = P.depth;
+  plan->ds = P.ds;
+  plan->dp = P.dp;
   return BMM_OK;
 }
 

@@ -312,13 +312,22 @@ hipError_t to_alt_basis(uint64_t* C, int64_t ldc, int64_t rows, int64_t words, i
 
 // The recursion's core on operands already in the alternative basis (A, and B
 // given transposed), for callers that stage their own operands (the
-// out-of-core pipeline).  depth = -1 picks it as the public product does;
-// strassen_alt_plan reports the workspace and the depth chosen.  accumulate = 1
+// out-of-core pipeline).  strassen_alt_plan chooses depth and split as the public product
+// does at depth -1 and reports the workspace; the run takes the depth from the plan and the
+// options from its split(), so that it needs just what was planned.  accumulate = 1
 // XORs the (alternative-basis) result into C.  standard = 1: operands and result are in the
 // standard basis instead (not with lean levels or the shifted leaf).  Both return a bmm
 // status.
-int strassen_alt_plan(int64_t m, int64_t k, int64_t n, int depth, const bmm_options& o,
-                      size_t* bytes, int* depth_out);
+struct AltPlan {
+  size_t bytes = 0;
+  int depth = 0, ds = 0, dp = 0;  // levels: all, depth first, breadth first
+  bmm_options split(bmm_options o) const {
+    o.depth_serial = ds;
+    o.depth_parallel = dp;
+    return o;
+  }
+};
+int strassen_alt_plan(int64_t m, int64_t k, int64_t n, const bmm_options& o, AltPlan* plan);
 int strassen_alt(const uint64_t* Ahat, int64_t lda, const uint64_t* BThat, int64_t ldbt,
                  uint64_t* C, int64_t ldc, int64_t m, int64_t k, int64_t n, int depth,
                  void* ws, size_t bytes, const bmm_options& o, int accumulate, hipStream_t s,

@@ -245,9 +245,10 @@ int ooc_host_levels(const uint64_t* A, int64_t lda, const uint64_t* B, int64_t l
   po.leaf = leaf;
   po.flags = 0;
   po.shift = 0;  // the shifted leaf takes operands already in the alternative basis
-  size_t ws_bytes = 0;
-  int d = 0;
-  if (strassen_alt_plan(b, b, b, -1, po, &ws_bytes, &d) != BMM_OK) return 1;
+  AltPlan plan;
+  if (strassen_alt_plan(b, b, b, po, &plan) != BMM_OK) return 1;
+  po = plan.split(po);
+  const size_t ws_bytes = plan.bytes;
   const int64_t bw = b / 64, nw = n / 64;
   const size_t blk = (size_t)b * bw * 8, full = (size_t)n * nw * 8;
   const size_t need = 8 * blk + full + ws_bytes;
@@ -394,8 +395,8 @@ int ooc_host_levels(const uint64_t* A, int64_t lda, const uint64_t* B, int64_t l
       OOC_TRY(hip_ok(hipEventRecord(R.ready[t], comb), "record"));
       OOC_TRY(hip_ok(hipStreamWaitEvent(R.comp, R.ready[t], 0), "wait"));
     }
-    OOC_TRY(strassen_alt(operand[0], bw, operand[1], bw, R.Q, bw, b, b, b, d, R.ws, ws_bytes, po, 0,
-                         R.comp, 1));
+    OOC_TRY(strassen_alt(operand[0], bw, operand[1], bw, R.Q, bw, b, b, b, plan.depth, R.ws,
+                         ws_bytes, po, 0, R.comp, 1));
     OOC_TRY(hip_ok(hipEventRecord(R.done[t], R.comp), "record"));
     for (int64_t q = 0; q < g * g; ++q) {
       uint64_t* const dst = R.Cres + q * b * bw;
@@ -499,27 +500,26 @@ extern "C" int bmm_ooc(int semiring, const uint64_t* A, int64_t lda, const uint6
   // GF(2): the alternative-basis recursion on each block product whose shape admits
   // it; the workspace is sized for the full block (smaller edge blocks need less).
   const bool cubic_only = o.depth_serial == 0 && o.depth_parallel == 0;
+  bmm_options po = o;
+  po.depth_serial = po.depth_parallel = -1;
+  po.leaf = leaf;
   size_t ws_bytes = 0;
   if (semiring == BMM_GF2 && !cubic_only) {
-    int d = 0;
-    bmm_options po = o;
-    po.depth_serial = po.depth_parallel = -1;
-    if (strassen_alt_plan(bm, bk, bn, -1, po, &ws_bytes, &d) != BMM_OK || d == 0) {
-      ws_bytes = 0;
-    } else if (bmm::dev_malloc(&R.ws, ws_bytes) != hipSuccess) {
-      (void)hipGetLastError();
-      return ofail(BMM_E_NOMEM, "out-of-core Strassen workspace (%zu bytes)", ws_bytes);
+    AltPlan whole;
+    if (strassen_alt_plan(bm, bk, bn, po, &whole) == BMM_OK && whole.depth > 0) {
+      ws_bytes = whole.bytes;
+      if (bmm::dev_malloc(&R.ws, ws_bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        return ofail(BMM_E_NOMEM, "out-of-core Strassen workspace (%zu bytes)", ws_bytes);
+      }
     }
   }
-  // Depth of the recursion for a block product of this shape (0: cubic leaf).
-  auto block_depth = [&](int64_t r, int64_t kk, int64_t c) -> int {
-    if (!R.ws) return 0;
-    size_t need = 0;
-    int d = 0;
-    bmm_options po = o;
-    po.depth_serial = po.depth_parallel = -1;
-    if (strassen_alt_plan(r, kk, c, -1, po, &need, &d) != BMM_OK) return 0;
-    return need <= ws_bytes ? d : 0;
+  // The recursion of a block product of this shape (depth 0: cubic leaf).
+  auto block_plan = [&](int64_t r, int64_t kk, int64_t c) -> AltPlan {
+    AltPlan plan;
+    if (!R.ws || strassen_alt_plan(r, kk, c, po, &plan) != BMM_OK || plan.bytes > ws_bytes)
+      plan.depth = 0;
+    return plan;
   };
 
   const int64_t nI = (m + bm - 1) / bm, nJ = (k + bk - 1) / bk, nK = (n + bn - 1) / bn;
@@ -556,7 +556,8 @@ extern "C" int bmm_ooc(int semiring, const uint64_t* A, int64_t lda, const uint6
         OOC_TRY(hip_ok(hipStreamWaitEvent(R.comp, R.loaded[s], 0), "wait"));
         OOC_TRY(hip_ok(launch_transpose(R.b[s], bnw, 0, R.bt, bkw, 0, depth, cols, 1, R.comp),
                        "transpose"));
-        int d = block_depth(rows, depth, cols);
+        const AltPlan plan = block_plan(rows, depth, cols);
+        int d = plan.depth;
         if (cdepth < 0) cdepth = d;
         if (d != cdepth) d = 0;  // a ragged k block: cubic, in the basis the C block is in
         if (d > 0) {
@@ -566,12 +567,8 @@ extern "C" int bmm_ooc(int semiring, const uint64_t* A, int64_t lda, const uint6
                          "basis A"));
           OOC_TRY(hip_ok(launch_basis(R.bt, bkw, 0, cols, dwords, 1, d, 0, R.comp, o.scheme, 1),
                          "basis B"));
-          bmm_options po = o;
-          po.depth_serial = po.depth_parallel = -1;
-          po.leaf = leaf;
-          po.tile = o.tile;
           OOC_TRY(strassen_alt(R.a[s], bkw, R.bt, bkw, R.c[cs], bnw, rows, depth, cols, d, R.ws,
-                               ws_bytes, po, J > 0 ? 1 : 0, R.comp));
+                               ws_bytes, plan.split(po), J > 0 ? 1 : 0, R.comp));
         } else {
           if (cdepth > 0) {
             // the C block is held in the alternative basis: change it to the standard
