@@ -851,6 +851,7 @@ int strassen_alt_plan(int64_t m, int64_t k, int64_t n, const bmm_options& o, Alt
   plan->depth = P.depth;
   plan->ds = P.ds;
   plan->dp = P.dp;
+  plan->shift = P.shift;
   return BMM_OK;
 }
 

@@ -321,9 +321,11 @@ hipError_t to_alt_basis(uint64_t* C, int64_t ldc, int64_t rows, int64_t words, i
 struct AltPlan {
   size_t bytes = 0;
   int depth = 0, ds = 0, dp = 0;  // levels: all, depth first, breadth first
+  int shift = 0;                  // of the last level into the leaf
   bmm_options split(bmm_options o) const {
     o.depth_serial = ds;
     o.depth_parallel = dp;
+    o.shift = shift;
     return o;
   }
 };

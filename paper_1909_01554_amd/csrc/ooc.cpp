@@ -244,11 +244,13 @@ int ooc_host_levels(const uint64_t* A, int64_t lda, const uint64_t* B, int64_t l
   po.depth_serial = po.depth_parallel = -1;
   po.leaf = leaf;
   po.flags = 0;
-  po.shift = 0;  // the shifted leaf takes operands already in the alternative basis
   AltPlan plan;
   if (strassen_alt_plan(b, b, b, po, &plan) != BMM_OK) return 1;
   po = plan.split(po);
   const size_t ws_bytes = plan.bytes;
+  // the shifted leaf takes operands in the alternative basis: changed before each product,
+  // and its result back, in passes of their own
+  const bool change = plan.shift > 0;
   const int64_t bw = b / 64, nw = n / 64;
   const size_t blk = (size_t)b * bw * 8, full = (size_t)n * nw * 8;
   const size_t need = 8 * blk + full + ws_bytes;
@@ -366,7 +368,7 @@ int ooc_host_levels(const uint64_t* A, int64_t lda, const uint64_t* B, int64_t l
         if (resident) {
           OOC_TRY(resident_block(side, q));
           add = block(side, q);
-          if (blocks.size() == 1) {  // the product reads it where it lies
+          if (blocks.size() == 1 && !change) {  // the product reads it where it lies
             operand[side] = add;
             break;
           }
@@ -390,14 +392,20 @@ int ooc_host_levels(const uint64_t* A, int64_t lda, const uint64_t* B, int64_t l
           ++up;
         }
       }
+      if (change)
+        OOC_TRY(hip_ok(launch_basis(acc, bw, 0, b, bw, 1, plan.depth, 0, comb, o.scheme, side),
+                       "basis"));
     }
     if (!resident) {
       OOC_TRY(hip_ok(hipEventRecord(R.ready[t], comb), "record"));
       OOC_TRY(hip_ok(hipStreamWaitEvent(R.comp, R.ready[t], 0), "wait"));
     }
     OOC_TRY(strassen_alt(operand[0], bw, operand[1], bw, R.Q, bw, b, b, b, plan.depth, R.ws,
-                         ws_bytes, po, 0, R.comp, 1));
+                         ws_bytes, po, 0, R.comp, change ? 0 : 1));
     OOC_TRY(hip_ok(hipEventRecord(R.done[t], R.comp), "record"));
+    if (change)
+      OOC_TRY(hip_ok(launch_basis(R.Q, bw, 0, b, bw, 1, plan.depth, 1, R.comp, o.scheme, 0),
+                     "basis"));
     for (int64_t q = 0; q < g * g; ++q) {
       uint64_t* const dst = R.Cres + q * b * bw;
       if (coef_c(h, q / g, q % g)) {

@@ -49,3 +49,39 @@ def test_depth_record_of_the_block(bmm, tmp_path, depth, ds, block_order):
     got = run(bmm, host(A), host(B), Ch, n, block,
               flags=bmm.FLAG_OOC_BLOCK_ORDER if block_order else 0)
     assert np.array_equal(got, oracle.mul(A, B, n, n, oracle.GF2))
+
+
+def kernels_of(call):
+    """Names of the kernels that a call runs."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as p:
+        call()
+        torch.cuda.synchronize()
+    return {e.name for e in p.events()}
+
+
+# the option, or a record's choice where the option leaves it to that
+@pytest.mark.parametrize("shift,record", [(1, None), (2, None), (-1, 1), (0, 1), (-1, None)])
+@pytest.mark.parametrize("scheme", [0, 1])
+@pytest.mark.parametrize("resident", [True, False])
+def test_shifted_leaf_in_the_host_levels(bmm, tmp_path, shift, record, scheme, resident):
+    import torch
+    n, block = 8192, 4096  # leaves of 2048 bits
+    if record is not None:
+        table = tmp_path / "t.txt"
+        table.write_text(f"depth {block} {block} {block} 1 0 {record}\n")
+        bmm.bmm_autotune_load(str(table))
+    A, B = operands(n, 61 + scheme)
+    Ah, Bh = host(A), host(B)
+    Ch = torch.full((n, words(n)), -1, dtype=torch.int64).pin_memory()
+    announce("ooc shifted leaf", shift, record, scheme, resident)
+    bmm.bmm_debug_fail_allocations(0 if resident else 1)  # the first one: A's place in HBM
+    names = kernels_of(lambda: run(bmm, Ah, Bh, Ch, n, block, leaf=2, scheme=scheme, shift=shift))
+    bmm.bmm_debug_fail_allocations(0)
+    assert any("transpose_kernel" in x for x in names), names
+    wanted = shift > 0 or (shift < 0 and bool(record))
+    assert any("leaf_shift_kernel" in x for x in names) == wanted
+    rows = bmmgen.stratified_rows(n, 128, 61)
+    got = Ch.numpy().view(np.uint64)
+    assert np.array_equal(got[rows], oracle.rows(A[rows], B, n, n, oracle.GF2))
