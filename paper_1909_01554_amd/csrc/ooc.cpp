@@ -346,6 +346,20 @@ int ooc_host_levels(const uint64_t* A, int64_t lda, const uint64_t* B, int64_t l
     return hip_ok(hipStreamWaitEvent(comb, up_event[side][q], 0), "wait");
   };
 
+  auto download = [&](int64_t q) {
+    OOC_TRY(log.begin(R.down));
+    OOC_TRY(hip_ok(hipMemcpy2DAsync(C + (q / g) * b * ldc + (q % g) * bw, ldc * 8,
+                                    R.Cres + q * b * bw, bw * 8, bw * 8, b,
+                                    hipMemcpyDeviceToHost, R.down),
+                   "D2H C"));
+    return log.end(R.down, (double)blk, 1);
+  };
+  // C in memory that A or B may share goes down once their last block is up
+  auto meet = [&](const uint64_t* X, int64_t ldx) {
+    const uintptr_t c = reinterpret_cast<uintptr_t>(C), x = reinterpret_cast<uintptr_t>(X);
+    return c < x + 8 * ((n - 1) * ldx + nw) && x < c + 8 * ((n - 1) * ldc + nw);
+  };
+  const bool shared = meet(A, lda) || meet(B, ldb);
   int64_t up = 0;  // blocks staged so far (slot up % 2)
   std::vector<char> begun(g * g, 0);
   for (int64_t i = 0; i < H; ++i) {
@@ -414,17 +428,17 @@ int ooc_host_levels(const uint64_t* A, int64_t lda, const uint64_t* B, int64_t l
                        "accumulate"));
         begun[q] = 1;
       }
-      if (last[q] != i) continue;
+      if (last[q] != i || shared) continue;
       hipEvent_t fin;
       OOC_TRY(R.event(&fin));
       OOC_TRY(hip_ok(hipEventRecord(fin, R.comp), "record"));
       OOC_TRY(hip_ok(hipStreamWaitEvent(R.down, fin, 0), "wait"));
-      OOC_TRY(log.begin(R.down));
-      OOC_TRY(hip_ok(hipMemcpy2DAsync(C + (q / g) * b * ldc + (q % g) * bw, ldc * 8, dst, bw * 8,
-                                      bw * 8, b, hipMemcpyDeviceToHost, R.down),
-                     "D2H C"));
-      OOC_TRY(log.end(R.down, (double)blk, 1));
+      OOC_TRY(download(q));
     }
+  }
+  if (shared) {  // all products are in, and so is every block they were formed from
+    OOC_TRY(hip_ok(hipStreamSynchronize(R.comp), "sync"));
+    for (int64_t q = 0; q < g * g; ++q) OOC_TRY(download(q));
   }
   OOC_TRY(hip_ok(hipStreamSynchronize(R.down), "sync"));
   OOC_TRY(hip_ok(hipStreamSynchronize(R.comp), "sync"));

@@ -85,3 +85,26 @@ def test_shifted_leaf_in_the_host_levels(bmm, tmp_path, shift, record, scheme, r
     rows = bmmgen.stratified_rows(n, 128, 61)
     got = Ch.numpy().view(np.uint64)
     assert np.array_equal(got[rows], oracle.rows(A[rows], B, n, n, oracle.GF2))
+
+
+@pytest.mark.parametrize("place", ["A", "B", "A and B", "rows of A"])
+@pytest.mark.parametrize("resident", [True, False])
+@pytest.mark.parametrize("n,block", [(1024, 256), (8192, 4096)])
+def test_result_over_an_operand(bmm, place, resident, n, block):
+    """The host levels read all of A and B before C goes down: a result written over them is
+    still their product."""
+    import torch
+    A, B = operands(n, 71)
+    if place == "A and B":
+        B = A
+    want = oracle.mul(A, B, n, n, oracle.GF2)
+    tall = torch.zeros((n + n // 4, words(n)), dtype=torch.int64).pin_memory()
+    tall[:n] = torch.from_numpy(A.view(np.int64))
+    Ah = tall[:n]
+    Bh = Ah if place == "A and B" else host(B)
+    Ch = {"B": Bh, "rows of A": tall[n // 4:]}.get(place, Ah)
+    announce("ooc over an operand", place, resident, n, block)
+    bmm.bmm_debug_fail_allocations(0 if resident else 1)  # the first one: A's place in HBM
+    got = run(bmm, Ah, Bh, Ch, n, block)
+    bmm.bmm_debug_fail_allocations(0)
+    assert np.array_equal(got, want)
