@@ -60,8 +60,8 @@ leaf_split_kernel(LeafBatch p, int64_t grid_m, int64_t grid_n) {
 
 template <int SEMI, int FMT>
 hipError_t launch_small(const LeafBatch& p, bool split, hipStream_t s) {
-  auto tiles = [&](int64_t r) { return ((p.m + r - 1) / r) * ((p.n + r - 1) / r) * p.batch; };
-  const int64_t grid_m = (p.m + 63) / 64, grid_n = (p.n + 63) / 64, blocks = tiles(64);
+  const int64_t grid_m = (p.m + 63) / 64, grid_n = (p.n + 63) / 64;
+  const int64_t blocks = grid_m * grid_n * p.batch;
   // up to 512 tiles of 64 x 64, two workgroups per CU, the split form is the faster one
   // (512: 10.3 against 16.7 us; 1024, at n = 2048: 9.8 against 8.1 us).  Asked for by name it
   // also takes more tiles while k is long for them (int8, 1500 x 4096 x 1500, 576 tiles, 11.3
@@ -69,9 +69,9 @@ hipError_t launch_small(const LeafBatch& p, bool split, hipStream_t s) {
   // and 13.6, 7000 x 1500 x 9000, 15510 tiles, 109 and 55).
   const bool large = blocks > 512 && !(split && p.k >= 6 * blocks) && p.lda < kNearPitch &&
                      p.ldbt < kNearPitch;
-  // past the largest launch of these tiles the panel's
-  if (!grid_fits(large ? tiles(128) : blocks, 256)) return launch_semi<SEMI, FMT>(p, s);
   if (large) return launch_shape<SEMI, FMT, 2, 2, false>(p, s);
+  // (far pitches: past the largest launch of these tiles the panel's)
+  if (!grid_fits(blocks, 256)) return launch_semi<SEMI, FMT>(p, s);
   hipLaunchKernelGGL((leaf_split_kernel<SEMI, FMT, true>), dim3((unsigned)blocks),
                      dim3(64 * kSplit), 0, s, p, grid_m, grid_n);
   return hipGetLastError();
@@ -126,7 +126,8 @@ bool leaf_small_tiles(int64_t m, int64_t n, int64_t batch) {
   // whole rounds over 256 CUs; a small tile is half the work of a large one, and costs
   // 4 to 13% more per unit (n = 4096, 4 rounds against 2: 25.5 and 24.0 us; n = 3072, 3
   // against 2: 16.0 and 18.7 us; 5001 x 7003 x 3333, 5 against 3: 50.5 and 58.7 us)
-  return tiles(64, 64) <= 512 || 0.54 * ((small + 255) / 256) < (double)((large + 255) / 256);
+  return tiles(64, 64) <= 512 || (0.54 * ((small + 255) / 256) < (double)((large + 255) / 256) &&
+                                  grid_fits(small, 256));
 }
 
 hipError_t launch_leaf_small(int semiring, int fmt, const LeafBatch& p, bool split,

@@ -45,3 +45,13 @@ def test_small_tiles_reach_their_launch(m, n, leaf, tile):
 
 def test_past_the_panel_tiles_is_refused():
     assert status(1 << 20, 64, 1 << 19, 3, 4) == -2
+
+
+def test_default_tile_of_a_large_batch_can_be_launched():
+    """7^7 leaves of 600 x 600: 25 tiles of 128 x 128 each would be too many work-items, 15 of
+    128 x 256 are not."""
+    import paper_1909_01554_amd as bmm
+    for leaf in (bmm.LEAF_MFMA_I8, bmm.LEAF_MFMA_F4):
+        o = bmm.Options(leaf=leaf)
+        assert bmm.bmm_leaf_choice(bmm.GF2, 600, 512, 600, batch=7 ** 4, options=o)[1] == 2
+        assert bmm.bmm_leaf_choice(bmm.GF2, 600, 512, 600, batch=7 ** 7, options=o)[1] != 2
