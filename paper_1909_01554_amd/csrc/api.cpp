@@ -438,6 +438,11 @@ int make_plan(int64_t m, int64_t k, int64_t n, int depth, const bmm_options& o, 
     auto it = g_depth.find({m, k, n});
     if (it != g_depth.end()) std::tie(depth, tuned_ds, tuned_shift) = it->second;
   }
+  // mkn / (mk + nk + mn) of the leaves at depth d
+  auto harmonic = [&](int d) {
+    const double u = (double)((int64_t)1 << d);
+    return 1.0 / (u / m + u / k + u / n);
+  };
   if (depth == -1) {
     // largest depth keeping every leaf dimension >= 2048 bits (at most 8 levels): the
     // depth tuner's optimum at n = 2^18 on gfx950 has 2048-bit leaves with the int8 leaf.
@@ -445,6 +450,9 @@ int make_plan(int64_t m, int64_t k, int64_t n, int depth, const bmm_options& o, 
     // and the result, which the twice as fast fp4 leaf repays on larger leaves only:
     // there the harmonic size mkn / (mk + nk + mn) stays >= 1250 (cubes: 3750 bits; at
     // n = 32768 leaves of 4096 take 7.6 ms, of 2048 8.1 ms, at n = 65536 54.5 and 58 ms).
+    // Not with operands in the alternative basis: there the depth says what the words of
+    // A, B and C mean, so no leaf kind and no table line for one may change it.
+    const bool by_leaf = f4 && !(o.flags & BMM_FLAG_ALT_BASIS_IO);
     auto admits = [&](int d) {
       const int64_t u = (int64_t)1 << d;
       return m % u == 0 && k % (64 * u) == 0 && n % (64 * u) == 0 && m / u >= 2048 &&
@@ -452,15 +460,14 @@ int make_plan(int64_t m, int64_t k, int64_t n, int depth, const bmm_options& o, 
     };
     depth = 0;
     while (depth < 8 && admits(depth + 1)) {
-      const double u = (double)((int64_t)2 << depth);
-      if (f4 && 1.0 / (u / m + u / k + u / n) < 1250.0) break;
+      if (by_leaf && harmonic(depth + 1) < 1250.0) break;
       ++depth;
     }
     // a second level is merged into the first one's passes, so it still pays on half that
     // leaf (n = 8192: 185 us with two levels, 196 with one, 212 without; n = 12288: 480, 509,
     // 546); a single level does not where k is short, which is when the result's passes
     // weigh most (22528 x 4608 x 18432: 617 us with it, 568 without)
-    if (f4 && depth <= 1) {
+    if (by_leaf && depth <= 1) {
       if (admits(2)) depth = 2;
       else if (k < 6000) depth = 0;
     }

@@ -1,0 +1,27 @@
+"""The depth and split of the recursion without a table record (host logic only)."""
+import pytest
+
+
+@pytest.fixture
+def bmm(tmp_path):
+    import paper_1909_01554_amd as bmm
+    bmm.bmm_finalize()
+    p = tmp_path / "t.txt"
+    p.write_text("auto_leaf 3\n")
+    bmm.bmm_autotune_load(str(p))
+    yield bmm
+    bmm.bmm_finalize()
+
+
+@pytest.mark.parametrize("m,k,n,depth", [
+    (4096, 4096, 4096, 1), (8192, 8192, 8192, 2), (16384, 16384, 16384, 3),
+    (1 << 16, 1 << 16, 1 << 16, 5), (1 << 20, 1 << 20, 1 << 20, 8), (16384, 4096, 16384, 1),
+    (2048, 8192, 8192, 0), (20480, 20480, 20480, 3)])
+@pytest.mark.parametrize("leaf", [0, 1, 2, 3])
+def test_alternative_basis_depth_is_the_sizes_alone(bmm, m, k, n, depth, leaf):
+    """A-hat, B-hat and C-hat are words at one depth: the largest whose leaves keep every
+    dimension at 2048 bits and more, whatever multiplies the leaves."""
+    for bt in (False, True):
+        _, ds, dp = bmm.bmm_gf2_strassen_workspace(m, k, n, -1, bmm.Options(leaf=leaf),
+                                                   alt_basis_io=True, b_transposed=bt)
+        assert ds + dp == depth
