@@ -482,10 +482,13 @@ int make_plan(int64_t m, int64_t k, int64_t n, int depth, const bmm_options& o, 
     ds = tuned_ds;
     dp = depth - ds;
   } else if (dp < 0 && ds < 0) {
-    // four breadth-first levels keep the int8 leaf's launches long; with the fp4 leaf two
-    // are better, whose operands and results stay near the caches from the expansion to
-    // the leaf and back (n = 32768: 7.9 against 8.4 ms with three)
-    dp = std::min(depth, f4 ? 2 : 4);
+    // four breadth-first levels keep the leaf's launches long; with the fp4 leaf two are
+    // better on leaves of the size where its depth rule stops, whose operands and results
+    // stay near the caches from the expansion to the leaf and back (leaves of 4096: n = 32768
+    // 7.4 against 7.8 ms with three, n = 65536 52.4 and 53.3 ms with four).  Smaller leaves
+    // are too short for launches of 49 (leaves of 2048: n = 16384 1.21 ms with two and 1.12
+    // with three, of 1024: 2.37 and, with four, 1.45 ms; n = 1024, leaves of 64: 495 and 33 us).
+    dp = std::min(depth, f4 && harmonic(depth) >= 1250.0 ? 2 : 4);
     ds = depth - dp;
   } else if (dp < 0) {
     ds = std::min(ds, depth);

@@ -25,3 +25,18 @@ def test_alternative_basis_depth_is_the_sizes_alone(bmm, m, k, n, depth, leaf):
         _, ds, dp = bmm.bmm_gf2_strassen_workspace(m, k, n, -1, bmm.Options(leaf=leaf),
                                                    alt_basis_io=True, b_transposed=bt)
         assert ds + dp == depth
+
+
+@pytest.mark.parametrize("n,depth,dp", [(1024, 4, 4), (1024, 2, 2), (4096, 5, 4), (16384, 3, 3),
+                                        (16384, 4, 4), (32768, 3, 2), (65536, 4, 2),
+                                        (65536, 5, 4), (1 << 18, 7, 4), (1 << 18, 6, 2)])
+@pytest.mark.parametrize("alt", [False, True])
+def test_split_of_a_given_depth(bmm, n, depth, dp, alt):
+    """Two breadth-first levels of the fp4 leaf where leaves are large, else four."""
+    for leaf in (0, 3):
+        _, ds, got = bmm.bmm_gf2_strassen_workspace(n, n, n, depth, bmm.Options(leaf=leaf),
+                                                    alt_basis_io=alt)
+        assert (ds, got) == (depth - dp, dp)
+    _, ds, got = bmm.bmm_gf2_strassen_workspace(n, n, n, depth, bmm.Options(leaf=2),
+                                                alt_basis_io=alt)
+    assert (ds, got) == (depth - min(depth, 4), min(depth, 4))
