@@ -1,7 +1,7 @@
 // Bit-matrix transpose in 64 x 64 bit blocks.
 //
 // A workgroup of RB waves transposes a tile of 64 RB rows x CW words: wave i loads rows
-// 64 i .. + 63, a row per lane (16 bytes at a time where rows are 16-byte aligned), turns
+// 64 i .. + 63, a row per lane (16 bytes at a time), turns
 // each word's 64 x 64 block in registers (bit_transpose.h: 31 VALU instructions, no
 // cross-lane traffic through LDS), and leaves the 64-bit pieces of the transposed rows in
 // LDS, from where they go out RB words (8 RB bytes) at a time.  Bits of rows past the end
@@ -10,18 +10,21 @@
 // Bound by memory (large) and by latency (small).  8 x 8 blocks move whole 64-byte halves of
 // a line both ways, in bands of 8 tiles whose pieces of a row are neighbours (16384 x 16384
 // bits: 14.0 us, 4.8 TB/s; in row order 18.7 us; with shuffles through LDS, in row order,
-// 26.6 us; 65536 x 65536: 292, 385 and 402 us).  Matrices of fewer than 256 such tiles take
+// 26.6 us; 65536 x 65536: 292, 385 and 402 us; with odd pitches 391 us, with 8-byte loads for
+// them 558).  Matrices of fewer than 256 such tiles take
 // 4 x 2 blocks: 2048 x 2048 bits are 128 workgroups instead of 16, 3.5 us instead of 10.1.
 #include "bit_transpose.h"
 
 namespace bmm {
 namespace {
 
+// 16 bytes of a row: the device loads them at the 8-byte alignment that rows of odd pitch have
+typedef uint64_t pair_t __attribute__((ext_vector_type(2), aligned(8)));
+
 template <int RB, int CW>
 __global__ __launch_bounds__(64 * RB) void transpose_kernel(
     const uint64_t* __restrict__ src, int64_t lds, int64_t strideS, uint64_t* __restrict__ dst,
-    int64_t ldd, int64_t strideD, int64_t rows, int64_t cols, uint32_t n_rt, uint32_t n_wt,
-    int vec) {
+    int64_t ldd, int64_t strideD, int64_t rows, int64_t cols, uint32_t n_rt, uint32_t n_wt) {
   constexpr int STR = RB + 1;  // padded LDS row (in words)
   __shared__ uint64_t tile[64 * CW * STR];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -33,13 +36,13 @@ __global__ __launch_bounds__(64 * RB) void transpose_kernel(
   uint64_t* D = dst + b * strideD;
   const int64_t r = r0 + 64 * wave + lane;
   uint64_t x[CW];
-  if (vec && w0 + CW <= src_words) {  // uniform
-    const ulonglong2* p = reinterpret_cast<const ulonglong2*>(S + (r < rows ? r : rows - 1) * lds + w0);
+  if (w0 + CW <= src_words) {  // uniform
+    const pair_t* p = reinterpret_cast<const pair_t*>(S + (r < rows ? r : rows - 1) * lds + w0);
 #pragma unroll
     for (int i = 0; i < CW / 2; ++i) {
-      const ulonglong2 v = p[i];
-      x[2 * i] = r < rows ? v.x : 0ull;
-      x[2 * i + 1] = r < rows ? v.y : 0ull;
+      const pair_t v = p[i];
+      x[2 * i] = r < rows ? v[0] : 0ull;
+      x[2 * i + 1] = r < rows ? v[1] : 0ull;
     }
   } else {
 #pragma unroll
@@ -68,10 +71,8 @@ hipError_t launch(const uint64_t* src, int64_t lds, int64_t strideS, uint64_t* d
   const int64_t n_wt = ((cols + 63) / 64 + CW - 1) / CW;
   const int64_t blocks = n_rt * n_wt * batch;
   if (!grid_fits(blocks, 64 * RB)) return kGridTooLarge;
-  const int vec = (reinterpret_cast<uintptr_t>(src) & 15) == 0 && ((lds | strideS) & 1) == 0;
   hipLaunchKernelGGL((transpose_kernel<RB, CW>), dim3((unsigned)blocks), dim3(64 * RB), 0, s, src,
-                     lds, strideS, dst, ldd, strideD, rows, cols, (uint32_t)n_rt, (uint32_t)n_wt,
-                     vec);
+                     lds, strideS, dst, ldd, strideD, rows, cols, (uint32_t)n_rt, (uint32_t)n_wt);
   return hipGetLastError();
 }
 

@@ -40,3 +40,25 @@ def test_tile_4_past_two_workgroups_per_cu(bmm, k, sr, leaf):
     got = from_dev(C)
     assert np.array_equal(got[:, :words(n)], oracle.mul(A, B, k, n, sr))
     assert (got[:, -1] == np.uint64(2**64 - 1)).all()
+
+
+@pytest.mark.parametrize("rows,cols", [(8300, 8130), (300, 450)])  # large and small blocks
+@pytest.mark.parametrize("start,src_pad,dst_pad", [(0, 1, 0), (1, 0, 1), (1, 1, 1), (0, 0, 0)])
+def test_transpose_of_rows_at_8_bytes(bmm, rows, cols, start, src_pad, dst_pad):
+    """Sources that start 8 bytes past a 16-byte line and pitches that keep rows there."""
+    import torch
+    X = bmmgen.fill_cpu(rows, cols, 11, bmmgen.TAG_A, bmmgen.Dist.half())
+    ld = words(cols) + (words(cols) + src_pad) % 2  # odd where src_pad says so
+    flat = torch.full((start + rows * ld,), -1, dtype=torch.int64, device="cuda")
+    S = flat[start:].view(rows, ld)
+    S[:, :words(cols)] = to_dev(X)
+    D = empty_dev(cols, words(rows) + dst_pad, fill=-1)
+    announce("transpose", rows, cols, start, src_pad, dst_pad)
+    bmm.bmm_transpose(S, D, rows, cols)
+    bits = np.unpackbits(X.view(np.uint8), axis=1, bitorder="little")[:, :cols]
+    want = np.zeros((cols, words(rows) * 64), dtype=np.uint8)
+    want[:, :rows] = bits.T
+    got = from_dev(D)
+    assert np.array_equal(got[:, :words(rows)],
+                          np.packbits(want, axis=1, bitorder="little").view(np.uint64))
+    assert dst_pad == 0 or (got[:, -1] == np.uint64(2**64 - 1)).all()
