@@ -111,12 +111,12 @@ __device__ __forceinline__ void expand2(const Operand& a, int64_t words, int64_t
   }
 }
 
-// Both operands in one launch: the left one in grid row 0, the right one in row 1 (a null
-// operand has no rows).
+// Both operands in one launch: the left one in grid row 0, the right one in row 1, or in row 0
+// where there is no left one (no rows).
 template <int SCH, int LEVELS, int BASIS, class I>
 __global__ __launch_bounds__(256) void expand_kernel(Operand left, Operand right, int64_t words,
                                                      int64_t parents) {
-  if (blockIdx.y == 0) {
+  if (blockIdx.y == 0 && left.rows > 0) {
     if constexpr (LEVELS == 2) expand2<SCH, 0, BASIS, I>(left, words, parents);
     else expand1<SCH, 0, BASIS, I>(left, words, parents);
   } else {
@@ -323,7 +323,7 @@ hipError_t expand_sch(int levels, const Operand& l, const Operand& r, int64_t wo
   const int64_t rows = l.rows > r.rows ? l.rows : r.rows;
   const int64_t total = (rows >> sh) * (words >> sh) * parents;
   if (total <= 0) return hipSuccess;
-  const dim3 g(grid_for(total), r.rows > 0 ? 2 : 1);
+  const dim3 g(grid_for(total), l.rows > 0 && r.rows > 0 ? 2 : 1);
   const bool narrow = fits32(total);
   if (basis) narrow ? launch_expand_t<SCH, 1, uint32_t>(levels, l, r, words, parents, g, s)
                     : launch_expand_t<SCH, 1, int64_t>(levels, l, r, words, parents, g, s);
