@@ -339,7 +339,8 @@ int bmm_compress(int levels, int scheme, const uint64_t* src, uint64_t* dst, int
  * with k split over its waves where those are few, with tile 4 also where k is long for
  * them, else 128 x 128), int8 tile 6 at k = 2048 and 4096 an unrolled
  * register-fed pipeline; every other number is the panel leaf, which picks its shape
- * itself.  With tile = 0 a product of up to 512 rows may read a row-major B directly. */
+ * itself.  With tile = 0 and no table entry a product of up to 512 rows may read a row-major
+ * B directly. */
 int bmm_leaf_tiles(int leaf, int* count_out);
 int bmm_leaf_tile_shape(int leaf, int tile, int* rows_out, int* cols_out);
 /* The leaf kind and tile a cubic product (batch = 1) or a batch of equal leaf

@@ -177,8 +177,10 @@ int auto_leaf_locked(int64_t k) {
 // row_major: the product may read B row-major (the VALU leaf's tile 2).  Where B is passed
 // transposed only the caller names that tile: it would turn B back into the scratch buffer
 // that calls on other streams share, and B^T is what they pass to keep out of it.
+// by_rule: whether the tile is the default rule's (neither named nor tuned).
 void pick_leaf(int semiring, int64_t m, int64_t k, int64_t n, int64_t batch,
-               const bmm_options& o, int* leaf, int* tile, bool row_major = false) {
+               const bmm_options& o, int* leaf, int* tile, bool row_major = false,
+               bool* by_rule = nullptr) {
   *leaf = o.leaf;
   *tile = o.tile;
   const bool b_t = (o.flags & BMM_FLAG_B_TRANSPOSED) != 0;
@@ -194,6 +196,7 @@ void pick_leaf(int semiring, int64_t m, int64_t k, int64_t n, int64_t batch,
     }
     if (*leaf == BMM_LEAF_AUTO) *leaf = auto_leaf_locked(k);
   }
+  if (by_rule) *by_rule = *tile <= 0;
   if (*tile <= 0) {
     // default tile for shapes the table lacks.  VALU: tables of B's rows for large cubic
     // products, else the dot-product form; MFMA: small tiles where large ones would leave
@@ -284,7 +287,8 @@ int cubic_product(int semiring, const uint64_t* A, int64_t lda, const uint64_t* 
     return BMM_OK;
   }
   int leaf, tile;
-  pick_leaf(semiring, m, k, n, 1, o, &leaf, &tile, caller_bt == nullptr);
+  bool by_rule;
+  pick_leaf(semiring, m, k, n, 1, o, &leaf, &tile, caller_bt == nullptr, &by_rule);
   // The VALU leaf's outer-product form (tile 2) reads B row-major; every other leaf reads
   // B^T. Whichever form the leaf needs and the caller did not pass is staged in scratch.
   const bool outer = leaf == BMM_LEAF_VALU && tile == 2;
@@ -306,8 +310,8 @@ int cubic_product(int semiring, const uint64_t* A, int64_t lda, const uint64_t* 
                      "leaf launch");
   }
   // so does one of few rows, for which a transpose of B would be much of the time, unless a
-  // tile is asked for
-  if (stage && (leaf == BMM_LEAF_MFMA_I8 || leaf == BMM_LEAF_MFMA_F4) && o.tile <= 0 &&
+  // tile is asked for or tuned
+  if (stage && (leaf == BMM_LEAF_MFMA_I8 || leaf == BMM_LEAF_MFMA_F4) && by_rule &&
       panel >= k && leaf_turn_fits(m, k, n, lda, ldb)) {
     LeafBatch p{A, lda, 0, B, ldb, 0, C, ldc, 0, m, k, n, 1, acc ? 1 : 0};
     return check_hip(launch_leaf_turn(semiring, leaf == BMM_LEAF_MFMA_F4 ? 1 : 0, p, s),

@@ -62,3 +62,32 @@ def test_transpose_of_rows_at_8_bytes(bmm, rows, cols, start, src_pad, dst_pad):
     assert np.array_equal(got[:, :words(rows)],
                           np.packbits(want, axis=1, bitorder="little").view(np.uint64))
     assert dst_pad == 0 or (got[:, -1] == np.uint64(2**64 - 1)).all()
+
+
+# a small product and products of few rows are one launch on a row-major B; the last ones,
+# and a tile that is named or tuned, go through the scratch copy of B^T
+@pytest.mark.parametrize("m,k,n,direct", [(256, 256, 256, True), (256, 64, 24576, True),
+                                          (512, 600, 16384, True), (128, 64, 65536, False),
+                                          (513, 64, 65536, False)])
+@pytest.mark.parametrize("leaf", [2, 3])
+@pytest.mark.parametrize("how", ["rule", "named", "tuned"])
+def test_which_products_read_b_directly(bmm, m, k, n, direct, leaf, how):
+    sr = oracle.GF2
+    A, B = operands(m, k, n, sr, 23)
+    bmm.bmm_finalize()  # no scratch, no tables
+    if how == "tuned":
+        bmm.bmm_autotune_set(sr, m, k, n, leaf, 5)
+    o = bmm.Options(leaf=leaf, tile=5 if how == "named" else 0)
+    C = empty_dev(m, words(n), fill=-1)
+    Ad, Bd = to_dev(A), to_dev(B)
+    announce("reads B directly", m, k, n, leaf, how)
+    bmm.bmm_debug_fail_allocations(1)
+    if direct and how == "rule":
+        bmm.bmm_gf2(Ad, Bd, C, m, k, n, options=o)
+    else:
+        with pytest.raises(bmm.BmmError) as e:
+            bmm.bmm_gf2(Ad, Bd, C, m, k, n, options=o)
+        assert e.value.status == -4
+        bmm.bmm_gf2(Ad, Bd, C, m, k, n, options=o)
+    bmm.bmm_debug_fail_allocations(0)
+    assert np.array_equal(from_dev(C), oracle.mul(A, B, k, n, sr))
