@@ -91,3 +91,23 @@ def test_which_products_read_b_directly(bmm, m, k, n, direct, leaf, how):
         bmm.bmm_gf2(Ad, Bd, C, m, k, n, options=o)
     bmm.bmm_debug_fail_allocations(0)
     assert np.array_equal(from_dev(C), oracle.mul(A, B, k, n, sr))
+
+
+@pytest.mark.parametrize("m,k,n", [(129, 513, 57345), (256, 1100, 32768), (400, 1024, 28672),
+                                   (512, 2113, 16384)])
+@pytest.mark.parametrize("leaf", [2, 3])
+def test_few_rows_that_differ(bmm, m, k, n, leaf):
+    """OR products of few rows in which every row of A has ones of its own, about two, so that
+    a row in another's place shows."""
+    sr = oracle.BOOLEAN
+    rng = np.random.default_rng(m + k)
+    A = np.zeros((m, words(k)), dtype=np.uint64)
+    for j in rng.integers(0, k, (2, m)):
+        A[np.arange(m), j // 64] |= np.uint64(1) << (j % 64).astype(np.uint64)
+    B = bmmgen.fill_cpu(k, n, 29, bmmgen.TAG_B, bmmgen.Dist.half())
+    want = oracle.mul(A, B, k, n, sr)
+    assert len(np.unique(want, axis=0)) > m // 2
+    C = empty_dev(m, words(n), fill=-1)
+    announce("few rows that differ", m, k, n, leaf)
+    bmm.bmm_boolean(to_dev(A), to_dev(B), C, m, k, n, options=bmm.Options(leaf=leaf))
+    assert np.array_equal(from_dev(C), want)
