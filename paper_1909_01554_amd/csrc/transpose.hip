@@ -82,9 +82,24 @@ hipError_t launch_transpose(const uint64_t* src, int64_t lds, int64_t strideS, u
                             int64_t ldd, int64_t strideD, int64_t rows, int64_t cols,
                             int64_t batch, hipStream_t s) {
   if (rows <= 0 || cols <= 0 || batch <= 0) return hipSuccess;
-  const bool small = ((rows + 511) / 512) * ((cols + 511) / 512) * batch < 256;
-  return small ? launch<4, 2>(src, lds, strideS, dst, ldd, strideD, rows, cols, batch, s)
-               : launch<8, 8>(src, lds, strideS, dst, ldd, strideD, rows, cols, batch, s);
+  const int64_t n_rt = (rows + 511) / 512, n_wt = (cols + 511) / 512;
+  if (n_rt * n_wt * batch < 256)
+    return launch<4, 2>(src, lds, strideS, dst, ldd, strideD, rows, cols, batch, s);
+  // 512 threads per 512 x 512 bits: up to twice the largest launch goes in pieces
+  if (batch == 1 && !grid_fits(n_rt * n_wt, 512) && grid_fits(n_rt * n_wt, 256)) {
+    const bool by_rows = n_rt > n_wt;
+    const int64_t step = (((int64_t)1 << 23) - 1) / (by_rows ? n_wt : n_rt) * 512;
+    for (int64_t at = 0; at < (by_rows ? rows : cols); at += step) {
+      const int64_t r = by_rows ? (rows - at < step ? rows - at : step) : rows;
+      const int64_t c = by_rows ? cols : (cols - at < step ? cols - at : step);
+      const hipError_t e =
+          by_rows ? launch<8, 8>(src + at * lds, lds, 0, dst + at / 64, ldd, 0, r, c, 1, s)
+                  : launch<8, 8>(src + at / 64, lds, 0, dst + at * ldd, ldd, 0, r, c, 1, s);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+  return launch<8, 8>(src, lds, strideS, dst, ldd, strideD, rows, cols, batch, s);
 }
 
 }  // namespace bmm

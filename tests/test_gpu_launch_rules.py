@@ -111,3 +111,31 @@ def test_few_rows_that_differ(bmm, m, k, n, leaf):
     announce("few rows that differ", m, k, n, leaf)
     bmm.bmm_boolean(to_dev(A), to_dev(B), C, m, k, n, options=bmm.Options(leaf=leaf))
     assert np.array_equal(from_dev(C), want)
+
+
+@pytest.mark.parametrize("tall", [False, True])
+def test_transpose_in_several_launches(bmm, tall):
+    """One row (or column) of 2^32 + 700 bits: more 512 x 512 blocks than a launch takes."""
+    import torch
+    n = (1 << 32) + 700
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    line = torch.randint(-(1 << 63), (1 << 63) - 1, (words(n),), dtype=torch.int64,
+                         device="cuda", generator=gen)
+    line[-1] &= (1 << (n % 64)) - 1
+    shifts = torch.arange(64, device="cuda")
+    step = 1 << 22  # words at a time
+    announce("transpose in several launches", tall)
+    if tall:
+        src = torch.empty((n, 1), dtype=torch.int64, device="cuda")
+        for i in range(0, words(n), step):
+            part = ((line[i:i + step, None] >> shifts) & 1).flatten()
+            src[64 * i:64 * i + part.numel(), 0] = part[:n - 64 * i]
+        dst = torch.full((1, words(n)), -1, dtype=torch.int64, device="cuda")
+        bmm.bmm_transpose(src, dst, n, 1)
+        assert torch.equal(dst[0], line)
+        return
+    dst = torch.full((n, 1), -1, dtype=torch.int64, device="cuda")
+    bmm.bmm_transpose(line[None, :], dst, 1, n)
+    for i in range(0, words(n), step):
+        part = ((line[i:i + step, None] >> shifts) & 1).flatten()[:n - 64 * i]
+        assert torch.equal(dst[64 * i:64 * i + part.numel(), 0], part), i

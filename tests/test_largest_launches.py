@@ -55,3 +55,29 @@ def test_default_tile_of_a_large_batch_can_be_launched():
         o = bmm.Options(leaf=leaf)
         assert bmm.bmm_leaf_choice(bmm.GF2, 600, 512, 600, batch=7 ** 4, options=o)[1] == 2
         assert bmm.bmm_leaf_choice(bmm.GF2, 600, 512, 600, batch=7 ** 7, options=o)[1] != 2
+
+
+TRANSPOSE = """
+import ctypes, sys
+import torch
+if torch.cuda.device_count():
+    sys.exit(77)
+import paper_1909_01554_amd as bmm
+rows, cols = int(sys.argv[1]), int(sys.argv[2])
+vp, base = ctypes.c_void_p, 1 << 44
+print(bmm._c_transpose(vp(base), (cols + 63) // 64, vp(2 * base), (rows + 63) // 64, rows, cols,
+                       None))
+"""
+
+
+# 512 x 512 bits per workgroup of 512 threads: 2^23 of them in several launches, 2^24 refused
+@pytest.mark.parametrize("rows,cols,want", [(64, 1 << 32, -5), (1 << 32, 64, -5),
+                                            (1, (1 << 33) - 513, -5), (64, 1 << 33, -2)])
+def test_transposes_past_one_launch(rows, cols, want):
+    env = dict(os.environ, HIP_VISIBLE_DEVICES="-1", CUDA_VISIBLE_DEVICES="-1")
+    r = subprocess.run([sys.executable, "-c", TRANSPOSE, str(rows), str(cols)], cwd=ROOT, env=env,
+                       capture_output=True, text=True, timeout=300)
+    if r.returncode == 77:
+        pytest.skip("devices cannot be hidden")
+    assert r.returncode == 0, r.stderr[-2000:]
+    assert int(r.stdout.strip().splitlines()[-1]) == want
