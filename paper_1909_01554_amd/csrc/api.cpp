@@ -203,7 +203,7 @@ void pick_leaf(int semiring, int64_t m, int64_t k, int64_t n, int64_t batch,
     // CUs idle, else the panel leaf (under the numbers of the long-k tiles for long k)
     if (*leaf == BMM_LEAF_VALU)
       *tile = row_major && !b_t && leaf_valu_table_fits(m, n) ? 2 : 1;
-    else if (leaf_small_tiles(m, n, batch)) *tile = 2;
+    else if (leaf_small_tiles(*leaf == BMM_LEAF_MFMA_F4 ? 1 : 0, m, k, n, batch)) *tile = 2;
     else if (*leaf == BMM_LEAF_MFMA_I8 && k >= 8192) *tile = 7;
     else if (*leaf == BMM_LEAF_MFMA_F4 && k >= 4096) *tile = 5;
     else *tile = 1;

@@ -31,15 +31,32 @@ hipError_t launch_shape(const LeafBatch& p, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Workgroups of r x c bits of C, and the rounds of them over 256 CUs.
+int64_t tiles(int64_t m, int64_t n, int64_t batch, int64_t r, int64_t c) {
+  return ((m + r - 1) / r) * ((n + c - 1) / c) * batch;
+}
+int64_t rounds(int64_t count) { return (count + 255) / 256; }
+
+// Rounds of tall workgroups (256 x 128), in wide ones: their rows of C go out 8 bytes at a
+// time, which weighs while k is short (15633 x 128 x 8192, 16 rounds of either, fp4, 38.5
+// against 35.0 us, k = 2048 93.4 and 91.7; one round, 4000 x 512 x 1500, 6.5 and 5.0 us, k =
+// 4096 15.9 and 14.9).
+double tall_rounds(int64_t m, int64_t k, int64_t n, int64_t batch) {
+  return 0.15 + (k <= 1024 ? 1.1 : 1.02) * (double)rounds(tiles(m, n, batch, 256, 128));
+}
+
 template <int SEMI, int FMT>
 hipError_t launch_semi(const LeafBatch& p, hipStream_t s) {
   // 64-bit row addresses take registers that only the tall shape has left
   if (p.lda >= kNearPitch || p.ldbt >= kNearPitch) return launch_shape<SEMI, FMT, 4, 2, true>(p, s);
-  // Wide wave tiles (64 x 128) are 2 to 6% faster than tall ones (n = 4096: 23.6 against
-  // 24.3 us, 16384: 1.20 against 1.21 ms in fp4): C's rows are stored 16 bytes at a time.
-  // Tall ones where they need fewer workgroups (n up to 128 columns past a multiple of 256).
-  const bool wide = ((p.m + 127) / 128) * ((p.n + 255) / 256) <=
-                    ((p.m + 255) / 256) * ((p.n + 127) / 128);
+  // Wide wave tiles (64 x 128): C's rows are stored 16 bytes at a time.  Tall ones where they
+  // take fewer rounds (4342 x 8192 x 1831, 255 against 272 workgroups: 41.1 against 68.2 us;
+  // 1000 x 1024 x 6000, 188 and 192, 9.6 and 8.4 us); in int8 from k = 8192 on, where they are
+  // the faster ones otherwise too, where they are fewer (7872 x 8192 x 2944 99.6 and 102.4 us).
+  const int64_t wides = tiles(p.m, p.n, p.batch, 128, 256);
+  const bool wide = FMT == mfma::FMT_I8 && p.k >= 8192
+                        ? wides <= tiles(p.m, p.n, p.batch, 256, 128)
+                        : (double)rounds(wides) <= tall_rounds(p.m, p.k, p.n, p.batch);
   return wide ? launch_shape<SEMI, FMT, 2, 4, false>(p, s)
               : launch_shape<SEMI, FMT, 4, 2, false>(p, s);
 }
@@ -120,14 +137,17 @@ hipError_t launch_turn_f4(const LeafBatch& p, hipStream_t s) {
 
 }  // namespace
 
-bool leaf_small_tiles(int64_t m, int64_t n, int64_t batch) {
-  auto tiles = [&](int64_t r, int64_t c) { return ((m + r - 1) / r) * ((n + c - 1) / c) * batch; };
-  const int64_t large = std::min(tiles(128, 256), tiles(256, 128)), small = tiles(128, 128);
+bool leaf_small_tiles(int fmt, int64_t m, int64_t k, int64_t n, int64_t batch) {
+  if (tiles(m, n, batch, 64, 64) <= 512) return true;
   // whole rounds over 256 CUs; a small tile is half the work of a large one, and costs
   // 4 to 13% more per unit (n = 4096, 4 rounds against 2: 25.5 and 24.0 us; n = 3072, 3
-  // against 2: 16.0 and 18.7 us; 5001 x 7003 x 3333, 5 against 3: 50.5 and 58.7 us)
-  return tiles(64, 64) <= 512 || (0.54 * ((small + 255) / 256) < (double)((large + 255) / 256) &&
-                                  grid_fits(small, 256));
+  // against 2: 16.0 and 18.7 us; 5001 x 7003 x 3333, 5 against 3: 50.5 and 58.7 us), 16% in
+  // fp4 while k is one stage (12000 x 512 x 2400, 7 against 4: 12.8 and 10.9 us).
+  const int64_t small = tiles(m, n, batch, 128, 128);
+  const double unit = fmt == mfma::FMT_F4 && k <= 512 ? 0.58 : 0.54;
+  const double wide = (double)rounds(tiles(m, n, batch, 128, 256));
+  return unit * (double)rounds(small) < std::min(wide, tall_rounds(m, k, n, batch)) &&
+         grid_fits(small, 256);
 }
 
 hipError_t launch_leaf_small(int semiring, int fmt, const LeafBatch& p, bool split,
