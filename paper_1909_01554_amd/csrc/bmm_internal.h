@@ -113,6 +113,9 @@ bool leaf_rows_fits(int64_t m, int64_t k, int64_t n);
 // and the shapes it is for.
 bool leaf_turn_fits(int64_t m, int64_t k, int64_t n, int64_t lda, int64_t ldb);
 hipError_t launch_leaf_turn(int semiring, int fmt, const LeafBatch& p, hipStream_t s);
+// Where tile 2 runs the register-fed 64 x 64 wave tiles instead: short k, and one row or column
+// of tiles.
+bool leaf_regs_fits(int fmt, int64_t m, int64_t k, int64_t n, int64_t batch);
 // Whether a batch of m x k x n products is small in this sense.
 bool leaf_small_tiles(int fmt, int64_t m, int64_t k, int64_t n, int64_t batch);
 hipError_t launch_leaf_valu(int semiring, const LeafBatch& p, int tile, hipStream_t s);

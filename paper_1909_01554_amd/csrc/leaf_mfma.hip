@@ -19,6 +19,8 @@
 // register v of a 32x32 block holds row 8*(v/4) + (v%4) in lanes 0..31 and
 // row 8*(v/4) + 4 + (v%4) in lanes 32..63, one column per lane, so one ballot
 // yields two 32-bit row words.
+#include <algorithm>
+
 #include "panel_tile.h"
 
 namespace bmm {
@@ -85,6 +87,26 @@ hipError_t launch_deep(const LeafBatch& p, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Short k, and results of one row or column of tiles (leaf_regs_fits): 64 x 64 wave tiles, 2 x
+// 2 of them per workgroup.  A step takes 2 KV words of k, where a round of the panel leaf is
+// four whatever k has left, and nothing goes through LDS.
+template <int SEMI, int FMT>
+hipError_t launch_regs(const LeafBatch& p, hipStream_t s) {
+  const int64_t tiles_m = (p.m + 63) / 64, tiles_n = (p.n + 63) / 64;
+  const int64_t blocks = ((tiles_m + 1) / 2) * ((tiles_n + 1) / 2) * p.batch;
+  if (!grid_fits(blocks, 256)) return kGridTooLarge;
+  const dim3 g((unsigned)blocks), b(256);
+  constexpr bool kWide = FMT == mfma::FMT_I8;  // (E2M1 operands have the 32-bit form only)
+  // (words past the last step are taken one by one)
+  if (aligned16(p) && (p.k + 63) / 64 % 4 == 0)
+    hipLaunchKernelGGL((leaf_mfma_kernel<SEMI, 2, 2, 2, FMT, 2, 0, kWide>), g, b, 0, s, p, tiles_m,
+                       tiles_n);
+  else
+    hipLaunchKernelGGL((leaf_mfma_kernel<SEMI, 2, 2, 1, FMT, 2, 0, kWide>), g, b, 0, s, p, tiles_m,
+                       tiles_n);
+  return hipGetLastError();
+}
+
 template <int SEMI, int FMT>
 hipError_t launch_semi(const LeafBatch& p, int tile, hipStream_t s) {
   if constexpr (FMT == mfma::FMT_I8) {
@@ -94,12 +116,28 @@ hipError_t launch_semi(const LeafBatch& p, int tile, hipStream_t s) {
       if (p.k == 4096) return launch_deep<SEMI, 16>(p, s);
     }
   }
+  if (tile == MFMA_64x64 && leaf_regs_fits(FMT, p.m, p.k, p.n, p.batch))
+    return launch_regs<SEMI, FMT>(p, s);
   if (tile == MFMA_64x64 || tile == MFMA_64x32)
     return launch_leaf_small(SEMI, FMT, p, tile == MFMA_64x32, s);
   return launch_leaf_panel(SEMI, FMT, p, s);
 }
 
 }  // namespace
+
+bool leaf_regs_fits(int fmt, int64_t m, int64_t k, int64_t n, int64_t batch) {
+  const int64_t tiles = ((m + 63) / 64) * ((n + 63) / 64) * batch;
+  // One row or column of tiles, more of them than the k-split form likes: a 128 x 128 tile
+  // would be half empty (60 x 768 x 200000, int8 13.2 against 16.5 us, fp4 10.9 and 15.0; 40000
+  // x 1024 x 30 5.9 and 7.2, 5.3 and 5.5).  From k = 2048 on the k-split form takes them.
+  if (std::min(m, n) <= 64 && tiles > 512) return k < 2048;
+  // Short k, until the larger tiles fill the CUs (int8, 640 x 320 x 6336, 990 tiles, 4.5 against
+  // 5.5 us, k = 384 4.7 and 5.4; 4342 x 256 x 1831, 1972 tiles, 4.9 and 6.0; 4096 x 64 x 4096
+  // 6.8 and 6.6); for up to 512 tiles only in int8 (64 x 64 x 64 3.1 and 3.4 us, 1000 x 256 x
+  // 1000 3.8 and 3.9; fp4 3.3 and 3.3, 3.8 and 3.7; 640 x 256 x 6336 3.9 and 4.7).
+  if (fmt == mfma::FMT_I8) return tiles <= 2304 && k <= (tiles > 512 ? 320 : 256);
+  return tiles <= 2304 && k <= 256 && tiles > 512;
+}
 
 int leaf_mfma_tile_rows(int tile) {
   switch (tile) {

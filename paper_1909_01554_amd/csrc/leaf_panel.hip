@@ -84,8 +84,12 @@ hipError_t launch_small(const LeafBatch& p, bool split, hipStream_t s) {
   // also takes more tiles while k is long for them (int8, 1500 x 4096 x 1500, 576 tiles, 11.3
   // against 13.6 us, 2000 x 8192 x 2000, 1024 tiles, 22.7 and 23.6; 2000 x 4096 x 2000 14.1
   // and 13.6, 7000 x 1500 x 9000, 15510 tiles, 109 and 55).
-  const bool large = blocks > 512 && !(split && p.k >= 6 * blocks) && p.lda < kNearPitch &&
-                     p.ldbt < kNearPitch;
+  // So does one row or column of them from k = 2048 on, where a 128 x 128 tile would be half
+  // empty (40000 x 3000 x 30, 625 tiles, fp4, 8.6 against 11.1 us; 60 x 2048 x 200000, 3125,
+  // int8, 26.3 and 32.1).
+  const bool thin = std::min(p.m, p.n) <= 64 && p.k >= 2048;
+  const bool large = blocks > 512 && !(split && p.k >= 6 * blocks) && !thin &&
+                     p.lda < kNearPitch && p.ldbt < kNearPitch;
   if (large) return launch_shape<SEMI, FMT, 2, 2, false>(p, s);
   // (far pitches: past the largest launch of these tiles the panel's)
   if (!grid_fits(blocks, 256)) return launch_semi<SEMI, FMT>(p, s);
@@ -138,7 +142,7 @@ hipError_t launch_turn_f4(const LeafBatch& p, hipStream_t s) {
 }  // namespace
 
 bool leaf_small_tiles(int fmt, int64_t m, int64_t k, int64_t n, int64_t batch) {
-  if (tiles(m, n, batch, 64, 64) <= 512) return true;
+  if (tiles(m, n, batch, 64, 64) <= 512 || leaf_regs_fits(fmt, m, k, n, batch)) return true;
   // whole rounds over 256 CUs; a small tile is half the work of a large one, and costs
   // 4 to 13% more per unit (n = 4096, 4 rounds against 2: 25.5 and 24.0 us; n = 3072, 3
   // against 2: 16.0 and 18.7 us; 5001 x 7003 x 3333, 5 against 3: 50.5 and 58.7 us), 16% in

@@ -139,3 +139,33 @@ def test_transpose_in_several_launches(bmm, tall):
     for i in range(0, words(n), step):
         part = ((line[i:i + step, None] >> shifts) & 1).flatten()[:n - 64 * i]
         assert torch.equal(dst[64 * i:64 * i + part.numel(), 0], part), i
+
+
+# 528 and more tiles of 64 x 64, whole and ragged; one row, one column of them; k: a bit, words
+# that fill steps of two and four of them and that do not, the last lengths before the next form
+@pytest.mark.parametrize("m,n,ks", [(1472, 1473, (1, 64, 128, 193, 256, 257, 320, 321)),
+                                    (300, 310, (1, 65, 128, 256)), (1, 1, (1, 200)),
+                                    (33, 33000, (64, 700, 1024, 2047, 2048)),
+                                    (33001, 64, (100, 513, 2040, 2050))])
+@pytest.mark.parametrize("leaf", [2, 3])
+@pytest.mark.parametrize("sr", [oracle.GF2, oracle.BOOLEAN])
+def test_short_k_and_one_row_of_tiles(bmm, m, n, ks, leaf, sr):
+    for k in ks:
+        A, B = operands(m, k, n, sr, 31 + k)
+        want = oracle.mul(A, B, k, n, sr)
+        C0 = bmmgen.fill_cpu(m, n, 31 + k, 0xC0, bmmgen.Dist.half())
+        BT = to_dev(np.zeros((n, words(k)), dtype=np.uint64))
+        bmm.bmm_transpose(to_dev(B), BT, k, n)
+        for pad, acc in ((0, False), (1, True), (2, False)):
+            announce("short k", m, k, n, leaf, sr, pad, acc)
+            C = empty_dev(m, words(n) + pad, fill=-1)
+            if acc:
+                C[:, :words(n)] = to_dev(C0)
+            Bp = empty_dev(n, words(k) + pad, fill=-1)
+            Bp[:, :words(k)] = BT
+            product(bmm, sr)(to_dev(A, words(k) + pad), Bp, C, m, k, n, b_transposed=True,
+                             accumulate=acc, options=bmm.Options(leaf=leaf))
+            got = from_dev(C)
+            ref = want if not acc else (want ^ C0 if sr == oracle.GF2 else want | C0)
+            assert np.array_equal(got[:, :words(n)], ref), (k, pad, acc)
+            assert (got[:, words(n):] == np.uint64(2**64 - 1)).all()

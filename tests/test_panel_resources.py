@@ -42,3 +42,13 @@ def test_small_and_few_rows(panel, kernel, count):
 def test_no_scratch(source, kernel):
     for name, (vgpr, priv) in _pick(_descriptors(source), kernel).items():
         assert vgpr <= 256 and priv == 0, (name, vgpr, priv)
+
+
+# 64 x 64 wave tiles by 8- and 16-byte loads, two semirings
+@pytest.mark.slow
+@pytest.mark.parametrize("format", ["Li0ELi2ELi0ELb1E", "Li1ELi2ELi0ELb0E"])
+def test_short_k(format):
+    hits = _pick(_descriptors("leaf_mfma.hip"), "leaf_mfma_kernel", format, "ELi2ELi2E")
+    assert len(hits) == 4
+    for name, (vgpr, priv) in hits.items():
+        assert vgpr <= 168 and priv == 0, (name, vgpr, priv)
