@@ -169,3 +169,31 @@ def test_short_k_and_one_row_of_tiles(bmm, m, n, ks, leaf, sr):
             ref = want if not acc else (want ^ C0 if sr == oracle.GF2 else want | C0)
             assert np.array_equal(got[:, :words(n)], ref), (k, pad, acc)
             assert (got[:, words(n):] == np.uint64(2**64 - 1)).all()
+
+
+@pytest.mark.parametrize("leaf", [2, 3])
+def test_result_of_2_to_the_36_bits(bmm, leaf):
+    """Every named tile runs it, and the leaf tuner with them."""
+    import torch
+    m = n = 1 << 18
+    k = 64
+    A, B = operands(m, k, 64, oracle.GF2, 41)[0], operands(n, k, 64, oracle.GF2, 43)[0]  # B^T
+    Ad, Bd = to_dev(A), to_dev(B)
+    rows = bmmgen.stratified_rows(m, 64, 47)
+    from oracle import brute
+    want = oracle.rows(A[rows], brute.pack(brute.unpack(B, k).T.copy()), k, n, oracle.GF2)
+    first = None
+    for tile in (5, 2, 4):
+        C = empty_dev(m, words(n), fill=-1)
+        announce("2^36 bits", leaf, tile)
+        bmm.bmm_gf2(Ad, Bd, C, m, k, n, b_transposed=True,
+                    options=bmm.Options(leaf=leaf, tile=tile))
+        if first is None:
+            assert np.array_equal(from_dev(C[torch.from_numpy(np.asarray(rows, dtype=np.int64)).cuda()]), want)
+            first = C
+        else:
+            assert torch.equal(C, first)
+    if leaf == 3:
+        announce("tuner, 2^36 bits")
+        chosen, tile, secs = bmm.bmm_autotune_cubic(oracle.GF2, m, k, n)
+        assert chosen in (1, 2, 3) and tile >= 1 and secs > 0
