@@ -93,12 +93,13 @@ typedef enum {
                                          result quadrants by gamma) instead of all seven:
                                          their workspace shrinks 7-fold, for more reads
                                          of the parents */
-#define BMM_FLAG_INPLACE_BASIS 0x20u /* Strassen only: change A (and B when passed
-                                        transposed) to the alternative basis in place
-                                        and restore them afterwards, instead of
-                                        copying them into the workspace (the basis
-                                        changes are invertible in place, section 2.2
-                                        and section 3.6) */
+#define BMM_FLAG_INPLACE_BASIS 0x20u /* Strassen only: no room in the workspace for
+                                        copies of A (and of B when passed transposed);
+                                        where they have to be changed to the
+                                        alternative basis, that is done in place and
+                                        undone afterwards (the basis changes are
+                                        invertible in place, section 2.2 and section
+                                        3.6) */
 
 typedef struct {
   int leaf;           /* bmm_leaf; 0 = auto */
@@ -142,7 +143,7 @@ void bmm_options_init(bmm_options* opt);
  * hip_stream, then returns once C is complete; BMM_FLAG_ACCUMULATE and
  * BMM_FLAG_B_TRANSPOSED are then BMM_E_UNSUPPORTED.
  * Errors: BMM_E_INVAL (negative size, null pointer with nonzero size, pitch too
- * small, C overlapping A or B, host memory not page-locked), BMM_E_NOMEM,
+ * small, C overlapping A or B on the device, host memory not page-locked), BMM_E_NOMEM,
  * BMM_E_DEVICE. */
 int bmm_gf2(const uint64_t* A, int64_t lda, const uint64_t* B, int64_t ldb, uint64_t* C,
             int64_t ldc, int64_t m, int64_t k, int64_t n, const bmm_options* opt,
@@ -169,13 +170,16 @@ int bmm_boolean(const uint64_t* A, int64_t lda, const uint64_t* B, int64_t ldb, 
  * With BMM_FLAG_ALT_BASIS_IO the inputs are taken as A-hat, B-hat and C-hat is
  * returned (no basis changes; B given transposed is then read where it lies).
  * With BMM_FLAG_ACCUMULATE the product is XORed into C (into C-hat under
- * BMM_FLAG_ALT_BASIS_IO; otherwise C is taken to the alternative basis and back).
- * With BMM_FLAG_INPLACE_BASIS the forward change is applied to the caller's A
- * (and to B^T when B is passed transposed; an untransposed B is transposed into
- * the workspace as always) and undone after the product, in stream order: the
- * workspace shrinks by those copies, A and B hold alternative-basis words while
- * the call's work runs (nothing else may read or write them until it finishes),
- * and they hold their original words again once it has.  A and B must not
+ * BMM_FLAG_ALT_BASIS_IO).
+ * With BMM_FLAG_INPLACE_BASIS the workspace has no room for copies of A (and of
+ * B^T when B is passed transposed; an untransposed B is transposed into the
+ * workspace as always).  Where the product changes its operands' basis in a pass
+ * of its own (BMM_FLAG_LEAN_WORKSPACE, the shifted leaf), the forward change is
+ * then applied to the caller's A and B^T and undone after the product, in stream
+ * order: they hold alternative-basis words while the call's work runs (nothing
+ * else may read or write them until it finishes), and their original words again
+ * once it has.  Elsewhere the changes are part of the first expansion, which
+ * reads A and B^T where they lie, with or without the flag.  A and B must not
  * overlap (BMM_E_INVAL).  Should a launch fail midway (BMM_E_DEVICE) their
  * contents are unspecified.
  * With BMM_FLAG_HOST_OPERANDS the operands are page-locked host memory and the
@@ -279,6 +283,14 @@ int bmm_autotune_batched(const bmm_problem* problems, int64_t count, int* leaf_o
  * are basis-changed on the device, the products of one C block accumulate in
  * the alternative basis, and the C block changes back once before download
  * (depth_serial = depth_parallel = 0 in opt forces the cubic leaf).
+ * Square GF(2) operands of 2^h blocks per side run h recursion levels above that
+ * on the device (BMM_FLAG_OOC_BLOCK_ORDER: not), which keep C in HBM until its
+ * blocks are final, each of which then downloads while the products go on, and A
+ * and B as well where they fit beside the rest (each block is then uploaded
+ * once): up to three times n * n / 8 bytes of HBM and the workspace, of what is
+ * free when the call starts.  opt->shift applies to their products.
+ * C must not overlap A or B; this is not checked here (the host levels read all
+ * of A and B before they write over them).
  * Synchronous: returns after C is complete; *seconds_out (if not NULL)
  * receives the wall time.  Allocates and frees its HBM buffers. */
 int bmm_ooc(int semiring, const uint64_t* A, int64_t lda, const uint64_t* B, int64_t ldb,
@@ -326,18 +338,20 @@ int bmm_compress(int levels, int scheme, const uint64_t* src, uint64_t* dst, int
                  void* hip_stream);
 
 /* Number of tile variants of a leaf (valid values of bmm_options.tile are
- * 1..count; 0 = auto), and the C tile (rows x columns) of a variant (per workgroup for
- * the VALU leaf, per wave for the matrix-core leaves).  The VALU leaf's tile 1 is the
+ * 1..count; 0 = auto), and the C tile (rows x columns) that a variant is named after (per
+ * workgroup for the VALU leaf, per wave for the matrix-core leaves; the forms that several
+ * numbers share pick their own, see below).  The VALU leaf's tile 1 is the
  * dot-product form against B^T (128 x 128); tile 2 is the outer-product form (512 x
  * 1024): each bit of A selects a row of B, whose words the waves read from LDS at one
  * address per wave, and the accumulators are the result bits; where C is large enough, each
  * byte of A selects one of the 256 sums of 8 rows of B that a workgroup holds in LDS (1024 x
- * 1024).  Tile 2 reads B row-major, so it
- * serves the cubic products only (where it is named for a B passed transposed, B is
- * transposed back into scratch first; no automatic choice does that); batched leaves (the recursion, bmm_batched) given VALU tile 2 run
- * tile 1.  Matrix-core tiles 2 and 4 are the forms for small products (64 x 64 per workgroup
+ * 1024).  Tile 2 reads B row-major, so it serves the cubic products only (where it is named
+ * for a B passed transposed, B is transposed back into scratch first; no automatic choice
+ * does that); batched leaves (the recursion, bmm_batched) given VALU tile 2 run tile 1.
+ * Matrix-core tiles 2 and 4 are the forms for small products (64 x 64 per workgroup
  * with k split over its waves where those are few, with tile 4 also where k is long for
- * them, else 128 x 128), int8 tile 6 at k = 2048 and 4096 an unrolled
+ * them, else 128 x 128; tile 2 from registers where k is short or C has one row or column
+ * of tiles), int8 tile 6 at k = 2048 and 4096 an unrolled
  * register-fed pipeline; every other number is the panel leaf, which picks its shape
  * itself.  With tile = 0 and no table entry a product of up to 512 rows may read a row-major
  * B directly. */

@@ -326,9 +326,9 @@ void set_free(PlanSet* S) {
 // pitches, semirings), the leaf and tile options and the device.  An entry owns the
 // device problem table, a staging buffer for right operands not given transposed,
 // and a HIP graph of its launch sequence (the transposes into staging, then the plan's
-// kernels: VALU products, and per persistent group the counter reset and the persistent
-// kernel), captured on its first call and replayed on the caller's stream by later
-// calls.  Launches of one entry are ordered by its event.
+// kernels: VALU products, and the persistent kernel of each group), captured on its first
+// call and replayed on the caller's stream by later calls.  Launches of one entry are ordered
+// by its event.
 struct BatchedEntry {
   std::vector<bmm_problem> key;
   int leaf = 0, tile = 0, device = 0;

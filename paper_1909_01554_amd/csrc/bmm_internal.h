@@ -83,10 +83,11 @@ __device__ __forceinline__ TileCoord xcd_tile(uint32_t g, uint32_t total, int64_
 }
 
 // MFMA leaf variants (rows x cols of C per wave, or per workgroup for the last and the
-// fifth).  64 x 64 is the panel leaf's small form, 64 x 32 the same by preference with k split over
-// waves, and int8 has the unrolled register-fed 128 x 64 pipeline (k = 2048 and 4096) and,
-// from k = 2^24 on, the chunked 64 x 128 loop; every other choice is the panel leaf, which
-// picks its shape itself.
+// fifth).  64 x 64 is the panel leaf's small form, or 64 x 64 wave tiles from registers where
+// leaf_regs_fits says so; 64 x 32 the small form by preference with k split over waves.  int8
+// has the unrolled register-fed 128 x 64 pipeline (k = 2048 and 4096) and, from k = 2^24 on,
+// the chunked 64 x 128 loop; every other choice is the panel leaf, which picks its shape
+// itself.
 enum MfmaTile { MFMA_128x64 = 0, MFMA_64x64 = 1, MFMA_64x128 = 2, MFMA_64x32 = 3,
                 MFMA_LDS_256x256 = 4, MFMA_DEEP_128x64 = 5, MFMA_CHUNK_64x128 = 6,
                 MFMA_LDS4_256x128 = 7, MFMA_NUM_TILES };

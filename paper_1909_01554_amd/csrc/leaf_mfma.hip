@@ -1,5 +1,6 @@
 // Cubic leaf product on the matrix cores of gfx950: which kernel runs a tile choice, and the
-// two int8 forms fed from registers (every other one is the panel leaf).
+// forms fed from registers: int8's long and unrolled ones, and 64 x 64 wave tiles for short k
+// and thin results in int8 and fp4 (every other one is the panel leaf).
 //
 // The cubic product C[i][k] = SUM_j A[i][j] B[j][k] (GF(2): XOR, Boolean: OR)
 // is an integer dot product reduced at the end: the int32 count of j with
@@ -7,8 +8,8 @@
 // as (count > 0).  Counts stay exact because k < 2^31.
 //
 // In the kernel here each wave owns a TM x TN tile of C (TM = 32*RA, TN = 32*RB) and issues
-// v_mfma_i32_32x32x32_i8 on RA x RB accumulator blocks held in registers.
-// Operands never touch HBM as bytes: every lane reads 64-bit words of packed
+// v_mfma_i32_32x32x32_i8 (fp4: v_mfma_scale_f32_32x32x64_f8f6f4) on RA x RB accumulator
+// blocks held in registers.  Operands never touch HBM as bytes: every lane reads 64-bit words of packed
 // bits straight from its row of A (or of B transposed) and expands them in
 // registers.  The order of k inside a dot product is free as long as A and B
 // use the same one, so a 32-bit half x of a word yields the eight dwords

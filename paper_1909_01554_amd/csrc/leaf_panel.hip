@@ -190,7 +190,9 @@ bool leaf_turn_fits(int64_t m, int64_t k, int64_t n, int64_t lda, int64_t ldb) {
   // more than half full (k = 8192, n = 65536: m = 130 52 against 64 us, m = 128 53 against 49).
   // Tiles that fill the CUs, one on each or two, in the last round (k = 8192, m = 256: 192
   // tiles 33.6 against 36.3 us, 448 53 and 63, 640 77 and 83, but 128 32.3 and 31.1, in int8
-  // 384 75.6 and 73.1).
+  // 384 75.6 and 73.1).  Whatever k: what is saved at short k is the transpose's launch (fp4, 256
+  // x 64 x 32768 5.7 against 7.1 us, 512 x 64 x 16384 5.5 and 7.0, 400 x 512 x 28672 7.9 and
+  // 9.0; at the most, 512 x 64 x 65536, 12.8 and 12.5).
   const int64_t rows = (m + 255) / 256, tiles = rows * ((n + 127) / 128), last = tiles % 512;
   return rows <= 2 && m > 256 * rows - 128 && tiles >= 192 && k < panel::kMaxK &&
          lda < kNearPitch && ldb < kNearPitch &&

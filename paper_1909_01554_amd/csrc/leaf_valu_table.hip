@@ -215,8 +215,10 @@ leaf_valu_table_kernel(const uint64_t* __restrict__ A, int64_t lda, const uint64
 
 bool leaf_valu_table_fits(int64_t m, int64_t n) {
   // One workgroup per CU and round, of 88 ns per bit of k, against the dot-product form's 3.2
-  // bit operations per fs: the tables are faster from 1.43e8 bits of C per round on (n = 8192,
-  // where 64 tiles leave three CUs in four idle, takes 0.7 ms with them and 0.38 ms without).
+  // bit operations per fs: the two would meet at 1.43e8 bits of C per round.  The line lies
+  // above that (12672 x 4096 x 12672, 1.606e8: 442 against 540 us, k = 64 22 and 96; 16384 x
+  // 4096 x 20000, two rounds of 1.64e8, 833 and 1050; n = 8192, where 64 tiles leave three CUs
+  // in four idle, takes 0.7 ms with them and 0.38 ms without).
   const double rounds = (double)((((m + TR - 1) / TR) * ((n + 64 * TW - 1) / (64 * TW)) + 255) / 256);
   return (double)m * (double)n >= 1.6e8 * rounds;
 }
