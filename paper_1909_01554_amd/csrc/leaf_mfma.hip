@@ -127,7 +127,10 @@ hipError_t launch_semi(const LeafBatch& p, int tile, hipStream_t s) {
 }  // namespace
 
 bool leaf_regs_fits(int fmt, int64_t m, int64_t k, int64_t n, int64_t batch) {
-  const int64_t tiles = ((m + 63) / 64) * ((n + 63) / 64) * batch;
+  const int64_t tiles_m = (m + 63) / 64, tiles_n = (n + 63) / 64;
+  const int64_t tiles = tiles_m * tiles_n * batch;
+  // (one column of 2^31 rows: the tall panel tiles still fit a launch)
+  if (!grid_fits(((tiles_m + 1) / 2) * ((tiles_n + 1) / 2) * batch, 256)) return false;
   // One row or column of tiles, more of them than the k-split form likes: a 128 x 128 tile
   // would be half empty (60 x 768 x 200000, int8 13.2 against 16.5 us, fp4 10.9 and 15.0; 40000
   // x 1024 x 30 5.9 and 7.2, 5.3 and 5.5).  From k = 2048 on the k-split form takes them.

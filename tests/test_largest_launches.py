@@ -47,6 +47,14 @@ def test_past_the_panel_tiles_is_refused():
     assert status(1 << 20, 64, 1 << 19, 3, 4) == -2
 
 
+# one column or row of tiles, twice as many as the register-fed form can launch
+@pytest.mark.parametrize("leaf", [2, 3])
+@pytest.mark.parametrize("m,k,n", [((1 << 31) - 64, 64, 64), ((1 << 31) - 64, 2048, 64),
+                                   (64, 64, (1 << 31) - 64)])
+def test_default_tile_of_a_single_column_can_be_launched(m, k, n, leaf):
+    assert status(m, k, n, leaf, 0) == -5
+
+
 def test_default_tile_of_a_large_batch_can_be_launched():
     """7^7 leaves of 600 x 600: 25 tiles of 128 x 128 each would be too many work-items, 15 of
     128 x 256 are not."""
