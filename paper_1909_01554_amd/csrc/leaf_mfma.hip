@@ -117,10 +117,16 @@ hipError_t launch_semi(const LeafBatch& p, int tile, hipStream_t s) {
       if (p.k == 4096) return launch_deep<SEMI, 16>(p, s);
     }
   }
-  if (tile == MFMA_64x64 && leaf_regs_fits(FMT, p.m, p.k, p.n, p.batch))
-    return launch_regs<SEMI, FMT>(p, s);
-  if (tile == MFMA_64x64 || tile == MFMA_64x32)
+  if (tile == MFMA_64x64 || tile == MFMA_64x32) {
+    // Results that 2 x 2 wave tiles of the named size per workgroup would not hold in one
+    // launch are refused, whichever form would run.
+    const int64_t cols = 2 * leaf_mfma_tile_cols(tile);
+    if (!grid_fits((p.m + 127) / 128 * ((p.n + cols - 1) / cols) * p.batch, 256))
+      return kGridTooLarge;
+    if (tile == MFMA_64x64 && leaf_regs_fits(FMT, p.m, p.k, p.n, p.batch))
+      return launch_regs<SEMI, FMT>(p, s);
     return launch_leaf_small(SEMI, FMT, p, tile == MFMA_64x32, s);
+  }
   return launch_leaf_panel(SEMI, FMT, p, s);
 }
 

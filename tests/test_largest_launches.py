@@ -15,18 +15,20 @@ if torch.cuda.device_count():
     sys.exit(77)
 import paper_1909_01554_amd as bmm
 m, k, n = (int(x) for x in sys.argv[1:4])
+pitch = int(sys.argv[6])
 o = bmm.Options(leaf=int(sys.argv[4]), tile=int(sys.argv[5]), flags=bmm.FLAG_B_TRANSPOSED)
-vp, base = ctypes.c_void_p, 1 << 44
-rc = bmm._c_gf2(vp(base), k // 64, vp(2 * base), k // 64, vp(3 * base), n // 64, m, k, n,
+vp, base = ctypes.c_void_p, 1 << 56
+rc = bmm._c_gf2(vp(base), pitch, vp(2 * base), pitch, vp(3 * base), n // 64, m, k, n,
                 ctypes.byref(o), None)
 print(rc, bmm._c_last_error().decode())
 """
 
 
-def status(m, k, n, leaf, tile):
+def status(m, k, n, leaf, tile, pitch=0):
     env = dict(os.environ, HIP_VISIBLE_DEVICES="-1", CUDA_VISIBLE_DEVICES="-1")
-    r = subprocess.run([sys.executable, "-c", CHILD] + [str(x) for x in (m, k, n, leaf, tile)],
-                       cwd=ROOT, env=env, capture_output=True, text=True, timeout=300)
+    args = [str(x) for x in (m, k, n, leaf, tile, pitch or k // 64)]
+    r = subprocess.run([sys.executable, "-c", CHILD] + args, cwd=ROOT, env=env,
+                       capture_output=True, text=True, timeout=300)
     if r.returncode == 77:
         pytest.skip("devices cannot be hidden")
     assert r.returncode == 0, r.stderr[-2000:]
@@ -41,6 +43,15 @@ def status(m, k, n, leaf, tile):
 @pytest.mark.parametrize("tile", [2, 4])
 def test_small_tiles_reach_their_launch(m, n, leaf, tile):
     assert status(m, 64, n, leaf, tile) == -5  # no device: the launch itself fails
+
+
+# 2^24 workgroups of 2 x 2 wave tiles of the named size
+@pytest.mark.parametrize("m,n,tile", [(1 << 20, 1 << 18, 2), (1 << 19, 1 << 18, 4),
+                                      ((1 << 31) - 64, 64, 2), (64, 1 << 30, 4)])
+@pytest.mark.parametrize("pitch", [32, 1 << 20])
+@pytest.mark.parametrize("leaf", [2, 3])
+def test_past_the_named_tiles_is_refused(m, n, tile, pitch, leaf):
+    assert status(m, 2048, n, leaf, tile, pitch) == -2
 
 
 def test_past_the_panel_tiles_is_refused():
