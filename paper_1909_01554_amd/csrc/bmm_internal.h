@@ -100,7 +100,7 @@ hipError_t launch_leaf_mfma_f4(int semiring, const LeafBatch& p, int tile, hipSt
 constexpr int64_t kPanelMaxK = (int64_t)1 << 24;
 constexpr int64_t kNearPitch = (int64_t)1 << 20;
 // The LDS-staged leaf of panel_tile.h (fmt: mfma::MfmaFormat) on 2 x 2 wave tiles of 64 x 128
-// or 128 x 64, whichever the shape pads less; k < kPanelMaxK.
+// or 128 x 64, whichever takes fewer rounds of the CUs; k < kPanelMaxK.
 hipError_t launch_leaf_panel(int semiring, int fmt, const LeafBatch& p, hipStream_t s);
 // The same on smaller tiles, for products that would leave CUs idle: 128 x 128 per workgroup,
 // or (where even those are few; split: while k is long for them) 64 x 64 with k split over a

@@ -9,9 +9,9 @@
 //
 // In the kernel here each wave owns a TM x TN tile of C (TM = 32*RA, TN = 32*RB) and issues
 // v_mfma_i32_32x32x32_i8 (fp4: v_mfma_scale_f32_32x32x64_f8f6f4) on RA x RB accumulator
-// blocks held in registers.  Operands never touch HBM as bytes: every lane reads 64-bit words of packed
-// bits straight from its row of A (or of B transposed) and expands them in
-// registers.  The order of k inside a dot product is free as long as A and B
+// blocks held in registers.  Operands never touch HBM as bytes: every lane reads
+// 64-bit words of packed bits straight from its row of A (or of B transposed) and
+// expands them in registers.  The order of k inside a dot product is free as long as A and B
 // use the same one, so a 32-bit half x of a word yields the eight dwords
 // (x >> d) & 0x01010101 (d = 0..7): byte e of dword d is bit 8e + d of x, 0 or
 // 1 (for one side of the tile both halves at once, from a 64-bit shift).

@@ -1,5 +1,6 @@
 // Device code of one leaf tile fed from registers: the long and the unrolled int8 leaf, the
-// 64 x 64 wave tiles for short k and batched tiles 1 to 3 (int8 or E2M1).  See leaf_mfma.hip for the method.
+// 64 x 64 wave tiles for short k and batched tiles 1 to 3 (int8 or E2M1).  See leaf_mfma.hip
+// for the method.
 #pragma once
 
 #include "bmm_internal.h"
