@@ -290,7 +290,7 @@ int bmm_autotune_batched(const bmm_problem* problems, int64_t count, int* leaf_o
  * once): up to three times n * n / 8 bytes of HBM and the workspace, of what is
  * free when the call starts.  opt->shift applies to their products.
  * C must not overlap A or B; this is not checked here (the host levels read all
- * of A and B before they write over them).
+ * of A and B before they write over them).  After an error C's contents are unspecified.
  * Synchronous: returns after C is complete; *seconds_out (if not NULL)
  * receives the wall time.  Allocates and frees its HBM buffers. */
 int bmm_ooc(int semiring, const uint64_t* A, int64_t lda, const uint64_t* B, int64_t ldb,
