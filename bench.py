@@ -378,7 +378,7 @@ def run_cubic(args, torch, np, bmm, bmmgen):
         del Bh
         fn = bmm.bmm_gf2 if sr == bmm.GF2 else bmm.bmm_boolean
         for leaf in (bmm.LEAF_VALU, bmm.LEAF_MFMA_I8, bmm.LEAF_MFMA_F4):
-            o = bmm.Options(leaf=leaf)
+            o = bmm.Options(leaf=leaf, flags=bmm.FLAG_B_TRANSPOSED)
             _, tile = bmm.bmm_leaf_choice(sr, n, n, n, 1, o)
             for _ in range(args.warmup):
                 fn(A, BT, C, n, n, n, options=o, b_transposed=True)
